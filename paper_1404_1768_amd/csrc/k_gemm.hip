@@ -604,6 +604,171 @@ void k_gemm_grp_pipe(const GemmArgs<T> *__restrict__ tab, int count, int64_t gri
   gemm_tile<T, 64, 64, 0, true, 16, false, false, true>(d, lin - d.tile0);
 }
 
+// Products whose output is too small to fill the chip with 64 x 64 tiles (inner
+// products U^* V of n x m blocks, n x m blocks times m x m or n x n matrices with a
+// small m, the small calls): one workgroup per 16 FM x 16 FN output tile, its W
+// wavefronts taking consecutive ranges of K and adding their sums in LDS in
+// wavefront order (deterministic, no workspace, one launch).
+//   bound: the latency of one wavefront's load -> MFMA chain, then the matrix
+//   cores of the few compute units in use; operands go from global memory (or
+//   L2) straight into the MFMA lane layout -- 16 consecutive columns of a row per
+//   16 lanes, or 8 consecutive k per row of an untransposed A -- so that no
+//   barrier stands between a load and its use, and the next step's loads are in
+//   flight while the current one is multiplied.
+// A lane holds k = 8 s + 2 (lane / 16) + {0, 1} of step s: the two MFMAs of a step
+// take the even and the odd ones (any assignment of k to lanes is the same sum
+// as long as A and B agree), and a row of A is read in 128-byte runs.
+// Measured against the 64 x 64 tiles (complex128, us a call): 157 x 157 x 4001 of
+// op = ^* 609 -> 40, 64 x 64 x 2003 307 -> 22, 2003 x 64 x 2003 308 -> 44,
+// 200 x 30 x 200 35 -> 11, 4000 x 160 x 160 31 -> 26.
+template <typename T, int TA, int FM, int FN, int W>
+__global__ __launch_bounds__(64 * W) void k_gemm_ks(const GemmArgs<T> d, int64_t grid_total) {
+  using Ops = mfma_ops<T>;
+  using real = typename Ops::real;
+  using acc_t = typename Ops::acc_t;
+  __shared__ real red[W][8 * FM * FN][64];
+  const int64_t tm = (d.M + 16 * FM - 1) / (16 * FM), tn = (d.N + 16 * FN - 1) / (16 * FN);
+  int64_t lin = xcd_remap(blockIdx.x, grid_total);
+  if (lin >= tm * tn * d.batch * d.splits) return;
+  const int64_t tile = lin % (tm * tn);
+  lin /= tm * tn;
+  const int64_t bidx = lin % d.batch, split = lin / d.batch;
+  const int64_t m0 = (tile / tn) * (16 * FM), n0 = (tile % tn) * (16 * FN);
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  const int c16 = lane & 15, g = lane >> 4;
+  // this workgroup's K range [8 t0, K) (kchunk is a multiple of 8 when split)
+  const int64_t K = (split + 1) * d.kchunk < d.K ? (split + 1) * d.kchunk : d.K;
+  const int64_t t0 = split * d.kchunk / 8, steps = (K + 7) / 8 - t0;
+  const int64_t s0 = t0 + steps * w / W, s1 = t0 + steps * (w + 1) / W;
+
+  // rows of C past M and columns past N read row M - 1 and column N - 1: their
+  // sums are never stored
+  const T *pa[FM], *pb[FN];
+#pragma unroll
+  for (int a = 0; a < FM; ++a) {
+    const int64_t r = m0 + 16 * a + c16, rc = r < d.M ? r : d.M - 1;
+    pa[a] = d.A + bidx * d.sA + (TA == 0 ? rc * d.lda : rc);
+  }
+#pragma unroll
+  for (int b = 0; b < FN; ++b) {
+    const int64_t c = n0 + 16 * b + c16;
+    pb[b] = d.B + bidx * d.sB + (c < d.N ? c : d.N - 1);
+  }
+  T ra[2][FM][2], rb[2][FN][2];
+  auto load = [&](int64_t s, int o) {
+    const int64_t k0 = 8 * s + 2 * g;
+    if (8 * s + 8 <= K) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int a = 0; a < FM; ++a) ra[o][a][h] = pa[a][TA == 0 ? k0 + h : (k0 + h) * d.lda];
+#pragma unroll
+        for (int b = 0; b < FN; ++b) rb[o][b][h] = pb[b][(k0 + h) * d.ldb];
+      }
+    } else {  // the last, partial step: k past K read k = K - 1 and count as zero
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const bool in = k0 + h < K;
+        const int64_t k = in ? k0 + h : K - 1;
+#pragma unroll
+        for (int a = 0; a < FM; ++a) {
+          const T v = pa[a][TA == 0 ? k : k * d.lda];
+          ra[o][a][h].x = in ? v.x : real(0);
+          ra[o][a][h].y = in ? v.y : real(0);
+        }
+#pragma unroll
+        for (int b = 0; b < FN; ++b) {
+          const T v = pb[b][k * d.ldb];
+          rb[o][b][h].x = in ? v.x : real(0);
+          rb[o][b][h].y = in ? v.y : real(0);
+        }
+      }
+    }
+  };
+  acc_t cr[FM][FN], ci[FM][FN];
+#pragma unroll
+  for (int a = 0; a < FM; ++a)
+#pragma unroll
+    for (int b = 0; b < FN; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) cr[a][b][r] = ci[a][b][r] = 0;
+  auto mul = [&](int o) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      real ar[FM], ai[FM];
+#pragma unroll
+      for (int a = 0; a < FM; ++a) {
+        ar[a] = ra[o][a][h].x;
+        ai[a] = TA == 0 ? ra[o][a][h].y : -ra[o][a][h].y;  // op(A) = A^*
+      }
+#pragma unroll
+      for (int a = 0; a < FM; ++a)
+#pragma unroll
+        for (int b = 0; b < FN; ++b) {
+          cr[a][b] = Ops::mma(ar[a], rb[o][b][h].x, cr[a][b]);
+          ci[a][b] = Ops::mma(ar[a], rb[o][b][h].y, ci[a][b]);
+        }
+#pragma unroll
+      for (int a = 0; a < FM; ++a)
+#pragma unroll
+        for (int b = 0; b < FN; ++b) {
+          cr[a][b] = Ops::mma(-ai[a], rb[o][b][h].y, cr[a][b]);
+          ci[a][b] = Ops::mma(ai[a], rb[o][b][h].x, ci[a][b]);
+        }
+    }
+  };
+  if (s0 < s1) load(s0, 0);
+  for (int64_t s = s0; s < s1; s += 2) {  // two steps a turn: the buffer index is a constant
+    if (s + 1 < s1) load(s + 1, 1);
+    mul(0);
+    if (s + 2 < s1) load(s + 2, 0);
+    if (s + 1 < s1) mul(1);
+  }
+
+#pragma unroll
+  for (int a = 0; a < FM; ++a)
+#pragma unroll
+    for (int b = 0; b < FN; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        red[w][2 * ((a * FN + b) * 4 + r)][lane] = cr[a][b][r];
+        red[w][2 * ((a * FN + b) * 4 + r) + 1][lane] = ci[a][b][r];
+      }
+  __syncthreads();
+  const real alr = static_cast<real>(d.alpha.x), ali = static_cast<real>(d.alpha.y);
+  const real ber = static_cast<real>(d.beta.x), bei = static_cast<real>(d.beta.y);
+  const bool use_beta = (ber != 0 || bei != 0);
+  T *C = d.C + bidx * d.sC;
+  T *P = (d.splits > 1) ? d.work + (split * d.batch + bidx) * d.M * d.N : nullptr;
+  for (int q = w; q < 4 * FM * FN; q += W) {  // q = (tile, element of the lane)
+    const int64_t row = m0 + 16 * (q / (4 * FN)) + Ops::out_row(lane, q & 3);
+    const int64_t col = n0 + 16 * ((q >> 2) % FN) + c16;
+    real xr = 0, xi = 0;
+#pragma unroll
+    for (int v = 0; v < W; ++v) {
+      xr += red[v][2 * q][lane];
+      xi += red[v][2 * q + 1][lane];
+    }
+    if (row < d.M && col < d.N) {
+      T v;
+      v.x = alr * xr - ali * xi;
+      v.y = alr * xi + ali * xr;
+      if (P) {
+        P[row * d.N + col] = v;
+        continue;
+      }
+      T *p = C + row * d.ldc + col;
+      if (use_beta) {
+        const T o = *p;
+        v.x += ber * o.x - bei * o.y;
+        v.y += ber * o.y + bei * o.x;
+      }
+      *p = v;
+    }
+  }
+}
+
 // Deterministic reduction of split-K partials: C = sum_s W_s + beta C.
 template <typename T>
 __global__ __launch_bounds__(256) void k_splitk_reduce(const GemmArgs<T> d) {
@@ -659,6 +824,57 @@ void launch_cfg(hipStream_t s, const GemmArgs<T> &d, int ta, bool update = false
   }
 }
 
+template <typename T, int FM, int FN, int W>
+void launch_ks(hipStream_t s, const GemmArgs<T> &d, int ta) {
+  const int64_t total = ((d.M + 16 * FM - 1) / (16 * FM)) * ((d.N + 16 * FN - 1) / (16 * FN)) *
+                        d.batch * d.splits;
+  const int64_t padded = (total + 7) / 8 * 8;
+  const dim3 grid(static_cast<unsigned>(padded));
+  if (ta == 0)
+    hipLaunchKernelGGL((k_gemm_ks<T, 0, FM, FN, W>), grid, dim3(64 * W), 0, s, d, padded);
+  else
+    hipLaunchKernelGGL((k_gemm_ks<T, 2, FM, FN, W>), grid, dim3(64 * W), 0, s, d, padded);
+}
+
+template <typename T> void launch_splitk_reduce(hipStream_t s, const GemmArgs<T> &d) {
+  const int64_t n = d.M * d.N * d.batch;
+  hipLaunchKernelGGL((k_splitk_reduce<T>), dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0,
+                     s, d);
+}
+
+// complex128 products of at most kSmallTiles 64 x 64 output tiles (no more than
+// compute units: each unit would run one 64 x 64 workgroup at most) take
+// k_gemm_ks; above, the 64 x 64 tiles read less per flop and are as fast or
+// faster (512 tiles, K = 128: 42 us against 46; 1024 tiles, K = 40: 42 against
+// 58).  In-place products (C is A or B) need one workgroup per column block and
+// keep the 64 x 64 tiles.  Sixteen wavefronts while that leaves units idle
+// (157 x 157 x 4001, 100 tiles: 41 us against 46 with eight); 32 x 16 tiles for
+// many tiles with a long sum (4000 x 160 x 4000: 349 us against 380), where the
+// operands' traffic counts.
+constexpr int64_t kSmallTiles = 256;
+
+template <typename T>
+void gemm_small(hipStream_t s, GemmArgs<T> d, int ta, int64_t work_elems) {
+  const int64_t t16 = ((d.M + 15) / 16) * ((d.N + 15) / 16) * d.batch;
+  // K ranges over several workgroups where the tiles leave compute units idle,
+  // each range at least 512 long (32 k a wavefront), if the caller has a workspace
+  if (d.work && t16 <= 128 && d.K >= 1024) {
+    int64_t sp = std::min<int64_t>(256 / t16, d.K / 512);
+    sp = std::min<int64_t>(sp, work_elems / (d.M * d.N * d.batch));
+    if (sp > 1) {
+      d.kchunk = ((d.K + sp - 1) / sp + 7) / 8 * 8;
+      d.splits = static_cast<int32_t>((d.K + d.kchunk - 1) / d.kchunk);
+    }
+  }
+  if (t16 * d.splits <= 256 && t16 <= 128)
+    launch_ks<T, 1, 1, 16>(s, d, ta);
+  else if (t16 > 1024 && d.K >= 1024)
+    launch_ks<T, 2, 1, 8>(s, d, ta);
+  else
+    launch_ks<T, 1, 1, 8>(s, d, ta);
+  if (d.splits > 1) launch_splitk_reduce<T>(s, d);
+}
+
 template <typename T>
 void gemm_impl(hipStream_t s, GemmArgs<T> d, int ta, int cfg, int64_t work_elems) {
   if (d.M <= 0 || d.N <= 0 || d.batch <= 0) return;
@@ -671,6 +887,10 @@ void gemm_impl(hipStream_t s, GemmArgs<T> d, int ta, int cfg, int64_t work_elems
   // (a 128 x 128 complex64 tile measured slower than 64 x 64 in the LU update,
   // and the FP64 one needs more than the 512 registers of a lane: not used)
   const int BM = (cfg == GEMM_TALL || cfg == GEMM_UPDATE_TALL) ? 128 : 64;
+  if constexpr (sizeof(T) == 16)
+    if (BM == 64 && d.A != d.C && d.B != d.C &&
+        ((d.M + 63) / 64) * ((d.N + 63) / 64) * d.batch <= kSmallTiles)
+      return gemm_small<T>(s, d, ta, work_elems);
   const int64_t tiles = ((d.M + BM - 1) / BM) * ((d.N + 63) / 64);
   // Split K when the output is too small to fill the chip (aiming at about
   // three workgroups per compute unit, each K chunk at least 64 long: the
@@ -698,11 +918,7 @@ void gemm_impl(hipStream_t s, GemmArgs<T> d, int ta, int cfg, int64_t work_elems
   } else {
     launch_cfg<T, 64, 64>(s, d, ta, cfg == GEMM_UPDATE);
   }
-  if (d.splits > 1) {
-    const int64_t n = d.M * d.N * d.batch;
-    hipLaunchKernelGGL((k_splitk_reduce<T>), dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256),
-                       0, s, d);
-  }
+  if (d.splits > 1) launch_splitk_reduce<T>(s, d);
 }
 
 }  // namespace
