@@ -95,24 +95,101 @@ template <> struct PivKey<z64> {
   }
 };
 
-// Rows of the leaf staged through LDS in blocks of at most NT rows, so that
-// global loads and stores walk along rows (IB consecutive lanes per row)
-// instead of one row per lane.
-template <typename T, int NT, int IB> struct LeafStage {
-  static constexpr int kRows = (NT * (IB + 1) * static_cast<int>(sizeof(T)) <= 81920) ? NT : NT / 2;
-};
+// Maxima of a key over the 64 lanes of a wavefront (returned uniformly) and over
+// each row of 16 lanes (left in every lane of the row).  A lane that a pattern
+// gives no source keeps its own value.  Keys are never NaN (v_max returns the
+// other operand then) and -1 marks "no candidate".
+template <int CTRL> __device__ inline float dpp_of(float x) {
+  const int i = __float_as_int(x);
+  return __int_as_float(__builtin_amdgcn_update_dpp(i, i, CTRL, 0xF, 0xF, false));
+}
+template <int CTRL> __device__ inline double dpp_of(double x) {
+  const int lo = __double2loint(x), hi = __double2hiint(x);
+  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xF, 0xF, false),
+                          __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xF, 0xF, false));
+}
+template <typename R> __device__ inline R row16_max(R x) {
+  x = fmax(x, dpp_of<0xb1>(x));   // quad_perm [1,0,3,2]
+  x = fmax(x, dpp_of<0x4e>(x));   // quad_perm [2,3,0,1]
+  x = fmax(x, dpp_of<0x124>(x));  // row_ror:4
+  return fmax(x, dpp_of<0x128>(x));  // row_ror:8
+}
+__device__ inline float lane_of(float x, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
+}
+__device__ inline double lane_of(double x, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l),
+                          __builtin_amdgcn_readlane(__double2loint(x), l));
+}
+template <typename R> __device__ inline R first_lane(R x) { return lane_of(x, 0); }
+template <typename R> __device__ inline R wave_max(R x) {
+  x = row16_max(x);
+  x = fmax(x, dpp_of<0x142>(x));  // row_bcast:15
+  x = fmax(x, dpp_of<0x143>(x));  // row_bcast:31: lane 63 holds the maximum
+  return lane_of(x, 63);
+}
+
+// Complex products by fused multiply-adds (four per complex multiply-add).
+template <typename T> __device__ inline T fmul(T a, T b) {
+  T r;
+  r.x = fma(a.x, b.x, -(a.y * b.y));
+  r.y = fma(a.x, b.y, a.y * b.x);
+  return r;
+}
+template <typename T> __device__ inline T ffms(T a, T b, T c) {  // a - b c
+  a.x = fma(b.y, c.y, fma(-b.x, c.x, a.x));
+  a.y = fma(-b.y, c.x, fma(-b.x, c.y, a.y));
+  return a;
+}
+// 1 / a for finite a != 0: a scaled by the power of two of its larger part, so
+// that |a|^2 is in [1/4, 2), one real reciprocal (the hardware's estimate and
+// Newton steps to full precision), scaled back.  No intermediate overflows or
+// underflows.
+__device__ inline double rcp_newton(double d) {
+  double r = __builtin_amdgcn_rcp(d);
+  r = fma(r, fma(-d, r, 1.0), r);
+  return fma(r, fma(-d, r, 1.0), r);
+}
+__device__ inline float rcp_newton(float d) {
+  const float r = __builtin_amdgcn_rcpf(d);
+  return fmaf(r, fmaf(-d, r, 1.0f), r);
+}
+__device__ inline int exp_of(double x) { return __builtin_amdgcn_frexp_exp(x); }
+__device__ inline int exp_of(float x) { return __builtin_amdgcn_frexp_expf(x); }
+template <typename T> __device__ inline T recip_scaled(T a) {
+  const int e = exp_of(fmax(fabs(a.x), fabs(a.y)));
+  const auto x = ldexp(a.x, -e), y = ldexp(a.y, -e);
+  const auto r = rcp_newton(fma(x, x, y * y));
+  T o;
+  o.x = ldexp(x * r, -e);
+  o.y = -ldexp(y * r, -e);
+  return o;
+}
+
+// Orders a wavefront's LDS writes before its later reads by other lanes (and
+// reads before later writes); the hardware runs one wavefront's LDS accesses in
+// order, so only the compiler is held.
+__device__ inline void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
 
 // One workgroup of NT threads per matrix holds the leaf columns [c0, c0+w)
 // of rows [c0, n) in registers (thread t owns rows c0 + t + NT q) and factors
 // them column by column with partial pivoting (largest |re|+|im|, lowest row
 // on ties; Section 4.3 reuses these factors for every filter).
-// Per column: each wavefront reduces its pivot key with DPP, the winning lane
-// posts its key and whole row to LDS, the owner of the diagonal row posts
-// that row, and after one barrier every thread picks the winner among the
-// posts, exchanges the two rows and applies the rank-1 update.  Posts are
-// double-buffered by column parity, so one barrier per column suffices.
-// The per-column selection work is repeated by every wavefront, so fewer,
-// fuller wavefronts (NT < 1024, more rows per thread) shorten a column.
+// Bound by latency: one chain per column -- key, DPP maximum over the wavefront
+// (ballots find its row, so no second reduction for the index), post to LDS,
+// one barrier, maximum over the posts, row exchange, rank-1 update by fused
+// multiply-adds.  The winning lane posts its row and its pivot's reciprocal;
+// posts are double-buffered by column parity, so one barrier per column
+// suffices.  Loads and stores walk along rows and turn through LDS of the
+// wavefront's own, without barriers.
+// Measured (us a leaf of 8 columns, all matrices at once, before -> now):
+// complex128 200 rows 18.3 -> 13.5, 1000 rows 24.7 -> 18.1, 2000 rows 30.7 -> 24.7;
+// complex64 1000 rows 16.7 -> 14.0, 2000 rows 22.6 -> 17.2, 4000 rows 33.0 -> 24.9.
+// A leaf costs 4.6 to 15 us (200 complex128 to 4000 complex64 rows) plus 0.9 to
+// 1.7 us a column.
 template <typename T, int NT, int RPT, int IB>
 __global__ __launch_bounds__(NT) void k_leaf(T *__restrict__ Mall, int64_t ld_in, int64_t stride,
                                              int64_t n_in, int64_t c0, int w, int64_t pk0,
@@ -120,20 +197,22 @@ __global__ __launch_bounds__(NT) void k_leaf(T *__restrict__ Mall, int64_t ld_in
                                              int32_t *__restrict__ info_all,
                                              const GrpMat *__restrict__ grp, int nodes) {
   using Tr = cplx_traits<T>;
-  using PK = PivKey<T>;
-  constexpr int SR = LeafStage<T, NT, IB>::kRows;
+  using real = typename Tr::real;
   constexpr int NW = NT / 64;
-  static_assert(NW <= 16, "at most 16 wavefronts");
+  constexpr int SB = IB < 8 ? IB : 8, SG = IB / SB;  // staged columns, column groups
+  static_assert(NW <= 16 && IB % SB == 0, "at most 16 wavefronts; whole column groups");
   const int b = blockIdx.x;
   const MatRef<T> mr = mat_of<T>(grp, nodes, Mall, ld_in, stride, n_in, b);
   T *M = mr.M;
   const int64_t ld = mr.ld, n = mr.n;
   if (c0 + w > n) return;  // (grouped: this matrix is already factored)
   int32_t *ipiv = ipiv_all + b * n_in;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  __shared__ T stg[SR][IB + 1];
-  __shared__ uint64_t s_key[2][16];
-  __shared__ uint32_t s_row[2][16];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  __shared__ T stg_all[NW][64][SB + 1];
+  __shared__ real s_key[2][16];
+  __shared__ int s_row[2][16];
+  __shared__ T s_inv[2][16];
   __shared__ T s_post[2][16][IB];
   __shared__ T s_crow[2][IB];
   __shared__ int s_pivs[IB];
@@ -141,173 +220,167 @@ __global__ __launch_bounds__(NT) void k_leaf(T *__restrict__ Mall, int64_t ld_in
   // rows of this thread relative to c0: tid + NT q (32-bit: rows < 2^31)
   const int nrel = static_cast<int>(n - c0);
 
+  // Each wavefront moves its own 64 rows of block q (SB consecutive lanes per row)
+  // and turns them through LDS of its own into one row per lane: no barrier, and
+  // every block's loads are in flight before the first is waited for (addresses
+  // clamped into the matrix, a select instead of a branch).
+  auto &stg = stg_all[wave];
+  const int er = lane / SB, ec = lane % SB;  // this lane's row and column of 64 / SB rows
+  const int row0 = 64 * wave + er;
+  T *Mw = M + c0 * (ld + 1) + row0 * ld + ec;
   T a[RPT][IB];
 #pragma unroll
   for (int q = 0; q < RPT; ++q)
 #pragma unroll
-    for (int h = 0; h < NT / SR; ++h) {
-      const int64_t base = c0 + NT * q + SR * h;
-      const T *Mb = M + base * ld + c0;
-      const int lim = static_cast<int>(n - base < SR ? n - base : SR);  // rows of this block
-      if (lim <= 0) {  // the block lies below the matrix (uniform): nothing to read
-        if (tid >= SR * h && tid < SR * (h + 1))
+    for (int h = 0; h < SG; ++h)
 #pragma unroll
-          for (int c = 0; c < IB; ++c) a[q][c] = czero<T>();
-        continue;
-      }
-      // addresses clamped into the block's rows (lim >= 1), so all loads issue
-      // before the first wait
-      T t[SR * IB / NT];
-#pragma unroll
-      for (int k = 0; k < SR * IB / NT; ++k) {
-        const int e = tid + NT * k, i = e / IB, c = e % IB;
-        t[k] = Mb[(i < lim ? i : 0) * static_cast<int>(ld) + (c < w ? c : 0)];
+      for (int k = 0; k < SB; ++k) {
+        const int dr = NT * q + (64 / SB) * k;
+        a[q][SB * h + k] = Mw[(row0 + dr < nrel ? dr : -row0) * ld + (SB * h + ec < w ? SB * h : -ec)];
       }
 #pragma unroll
-      for (int k = 0; k < SR * IB / NT; ++k) {
-        const int e = tid + NT * k, i = e / IB, c = e % IB;
-        stg[i][c] = (i < lim && c < w) ? t[k] : czero<T>();
-      }
-      __syncthreads();
-      if (tid >= SR * h && tid < SR * (h + 1))
+  for (int q = 0; q < RPT; ++q)
 #pragma unroll
-        for (int c = 0; c < IB; ++c) a[q][c] = stg[tid - SR * h][c];
-      __syncthreads();
+    for (int h = 0; h < SG; ++h) {
+#pragma unroll
+      for (int k = 0; k < SB; ++k) {
+        const bool in = row0 + NT * q + (64 / SB) * k < nrel && SB * h + ec < w;
+        stg[er + (64 / SB) * k][ec] = in ? a[q][SB * h + k] : czero<T>();
+      }
+      wave_lds_order();
+#pragma unroll
+      for (int c = 0; c < SB; ++c) a[q][SB * h + c] = stg[lane][c];
+      wave_lds_order();
     }
 
 #pragma unroll
   for (int c = 0; c < IB; ++c) {
     if (c >= w) break;
-    const int64_t rc = c0 + c;
     const int par = c & 1;
-    // this thread's best candidate (relative rows c .. nrel-1)
-    uint64_t best = 0;
-    int bq = 0;
+    // keys of this thread's candidates (relative rows c .. nrel-1; -1: none)
+    real v[RPT];
+    real best = -1;
+    T cand = czero<T>();
 #pragma unroll
     for (int q = 0; q < RPT; ++q) {
       const int r = tid + NT * q;
-      const uint64_t k = (r >= c && r < nrel) ? PK::key(a[q][c], static_cast<int>(c0) + r) : 0;
-      if (k > best) {  // strict: the lowest row of this thread wins a tie
-        best = k;
-        bq = q;
+      const real k = fabs(a[q][c].x) + fabs(a[q][c].y);
+      v[q] = (r >= c && r < nrel && k >= 0) ? k : real(-1);  // (NaN is no candidate)
+      if (v[q] > best) {
+        best = v[q];
+        cand = a[q][c];
       }
     }
-    const int myrow = static_cast<int>(c0) + tid + NT * bq;
-    const uint64_t wbest = wave_max_u64(best);
-    bool mine = best == wbest && wbest != 0;
-    if constexpr (!PK::kPacked) {
-      // ties in value: the lowest row among the lanes holding the maximum
-      const uint64_t ik = mine ? 0xFFFFFFFFull - static_cast<uint32_t>(myrow) : 0;
-      const uint64_t wi = wave_max_u64(ik);
-      mine = mine && ik == wi;
-    }
-    if (mine) {
-      s_key[par][wave] = wbest;
-      s_row[par][wave] = static_cast<uint32_t>(myrow);
+    const real wbest = wave_max(best);
+    if (wbest >= 0) {
+      // the lowest row holding the maximum: lowest q, then lowest lane (uniform)
+      int wq = 0, wl = 0;
+#pragma unroll
+      for (int q = RPT - 1; q >= 0; --q) {
+        const uint64_t hit = __builtin_amdgcn_ballot_w64(v[q] == wbest);
+        if (hit) {
+          wq = q;
+          wl = static_cast<int>(__builtin_ctzll(hit));
+        }
+      }
 #pragma unroll
       for (int q = 0; q < RPT; ++q)
-        if (q == bq)
+        if (wq == q && lane == wl) {
 #pragma unroll
           for (int k = 0; k < IB; ++k) s_post[par][wave][k] = a[q][k];
+          // (cand is a[q][c]: an equal candidate of a lower q would have been hit)
+          s_inv[par][wave] = recip_scaled(cand);
+          s_key[par][wave] = wbest;
+          s_row[par][wave] = tid + NT * q;
+        }
+    } else if (lane == 0) {
+      s_key[par][wave] = -1;  // no candidate in this wavefront
     }
-    if (wbest == 0 && lane == 0) s_key[par][wave] = 0;  // no candidate in this wavefront
     if (tid == c)
 #pragma unroll
       for (int k = 0; k < IB; ++k) s_crow[par][k] = a[0][k];
     __syncthreads();
     // the winner among the posts: lane v of every row of 16 reads post v
     const int pv = lane & 15;
-    const uint64_t pk = pv < NW ? s_key[par][pv] : 0;
-    const uint32_t prw = pv < NW ? s_row[par][pv] : 0xFFFFFFFFu;
-    const uint64_t gk = uniform_u64(row16_max_u64(pk));
-    uint32_t grow = 0xFFFFFFFFu - static_cast<uint32_t>(gk);
-    if constexpr (!PK::kPacked) {  // ties in value: the lowest row
-      const uint64_t rk = (pk == gk && gk != 0) ? 0xFFFFFFFFull - prw : 0;
-      grow = 0xFFFFFFFFu - static_cast<uint32_t>(uniform_u64(row16_max_u64(rk)));
-    }
-    const uint64_t hit = __builtin_amdgcn_ballot_w64(gk != 0 && pk == gk && prw == grow);
-    const int gw = hit ? static_cast<int>(__builtin_ctzll(hit) & 15) : -1;
-    int64_t p = rc;
+    const real pk = pv < NW ? s_key[par][pv] : real(-1);
+    const int prw = pv < NW ? s_row[par][pv] : 0;
+    const real gk = first_lane(row16_max(pk));
+    int prel = c;  // pivot row relative to c0
     T prow[IB];
-    if (gw >= 0) {
-      p = grow;
+    T inv = czero<T>();
+    if (gk >= 0) {
+      uint64_t hit = __builtin_amdgcn_ballot_w64(pk == gk) & 0xFFFF;
+      int gw = static_cast<int>(__builtin_ctzll(hit));
+      prel = __builtin_amdgcn_readlane(prw, gw);
+      for (hit &= hit - 1; hit; hit &= hit - 1) {  // ties in value: the lowest row
+        const int o = static_cast<int>(__builtin_ctzll(hit));
+        const int orow = __builtin_amdgcn_readlane(prw, o);
+        if (orow < prel) {
+          prel = orow;
+          gw = o;
+        }
+      }
 #pragma unroll
       for (int k = 0; k < IB; ++k) prow[k] = s_post[par][gw][k];
+      inv = s_inv[par][gw];
+      if (!(gk < INFINITY)) inv = Tr::recip(prow[c]);
     } else {  // no comparable entry (NaN column): keep the diagonal row
 #pragma unroll
       for (int k = 0; k < IB; ++k) prow[k] = s_crow[par][k];
+      inv = Tr::recip(prow[c]);
     }
-    const T piv = prow[c];
-    const bool zero = (piv.x == 0 && piv.y == 0);
-    if ((zero || gw < 0) && info_local == 0) info_local = static_cast<int>(rc) + 1;
-    if (tid == 0) s_pivs[c] = static_cast<int>(p);
-    if (p != rc) {
-      const int prel = static_cast<int>(p - c0);
+    if (gk == 0) inv = czero<T>();  // exact zero pivot
+    if (!(gk > 0) && info_local == 0) info_local = static_cast<int>(c0) + c + 1;
+    if (tid == 0) s_pivs[c] = static_cast<int>(c0) + prel;
+    if (prel != c) {
       const int ptid = prel % NT, pq = prel / NT;
       if (tid == c)
 #pragma unroll
         for (int k = 0; k < IB; ++k) a[0][k] = prow[k];
-      if (tid == ptid)
+      if (wave == ptid / 64)
 #pragma unroll
         for (int q = 0; q < RPT; ++q)
-          if (q == pq)
+          if (q == pq && tid == ptid)
 #pragma unroll
             for (int k = 0; k < IB; ++k) a[q][k] = s_crow[par][k];
     }
-    const T inv = zero ? czero<T>() : Tr::recip(piv);
 #pragma unroll
     for (int q = 0; q < RPT; ++q) {
       const int r = tid + NT * q;
       if (r > c && r < nrel) {
-        const T l = Tr::mul(a[q][c], inv);
+        const T l = fmul(a[q][c], inv);
         a[q][c] = l;
 #pragma unroll
-        for (int k = c + 1; k < IB; ++k) a[q][k] = Tr::fms(a[q][k], l, prow[k]);
+        for (int k = c + 1; k < IB; ++k) a[q][k] = ffms(a[q][k], l, prow[k]);
       }
     }
   }
 
-  // leaf columns back through LDS (row-contiguous stores), then the pivots
-#pragma unroll
-  for (int q = 0; q < RPT; ++q)
-#pragma unroll
-    for (int h = 0; h < NT / SR; ++h) {
-      const int64_t base = c0 + NT * q + SR * h;
-      __syncthreads();
-      if (tid >= SR * h && tid < SR * (h + 1))
-#pragma unroll
-        for (int c = 0; c < IB; ++c) stg[tid - SR * h][c] = a[q][c];
-      __syncthreads();
-      T *Mb = M + base * ld + c0;
-      const int lim = static_cast<int>(n - base < SR ? n - base : SR);
-#pragma unroll
-      for (int k = 0; k < SR * IB / NT; ++k) {
-        const int e = tid + NT * k, i = e / IB, c = e % IB;
-        if (i < lim && c < w) Mb[i * static_cast<int>(ld) + c] = stg[i][c];
-      }
-    }
+  __syncthreads();  // s_pivs
   if (tid < w) ipiv[c0 + tid] = s_pivs[tid];
   // The leaf's swaps (c0 + c <-> s_pivs[c], in order) applied to the other
   // columns of the panel as one gather.  Destinations: the w leaf rows and
   // each distinct pivot row below them; each thread finds the source of its
   // destination by walking the swaps backwards, and all sources are read
   // before any destination is written.
+  // (two wavefronts walk one destination row's panel columns, so the walk is
+  // wave-uniform)
   int pv_[IB];
 #pragma unroll
-  for (int c = 0; c < IB; ++c) pv_[c] = c < w ? s_pivs[c] : -1;
+  for (int c = 0; c < IB; ++c) pv_[c] = c < w ? __builtin_amdgcn_readfirstlane(s_pivs[c]) : -1;
   // panel columns (clipped to the matrix: in a grouped launch a wide panel can
   // extend past a smaller matrix's last column); the leaf's own columns are skipped
   const int ncol = static_cast<int>(pk0 + pkb <= n ? pkb : n - pk0);
-  constexpr int H = 2048 / NT;  // 2 w pkb <= 2048 elements
+  constexpr int H = (2 * IB * 128 + NT - 1) / NT;  // 2 w rows of pkb <= 128 columns
+  const int64_t pcol = pk0 + (tid & 127);
+  const bool pin = (tid & 127) < ncol && (pcol < c0 || pcol >= c0 + w);
   T v[H];
-  int64_t dst[H], col[H];
+  int dst[H];  // destination row of slot h (uniform), -1: none
 #pragma unroll
   for (int h = 0; h < H; ++h) {
-    const int e = tid + NT * h;
+    const int k = 2 * NT / 256 * h + (wave >> 1);
     v[h] = czero<T>();
-    col[h] = 0;
     dst[h] = -1;
-    const int k = e / ncol;
     if (k < 2 * w) {
       int key = -1;
       if (k < w) {
@@ -333,18 +406,32 @@ __global__ __launch_bounds__(NT) void k_leaf(T *__restrict__ Mall, int64_t ld_in
             if (src == top) src = pv_[c];
             else if (src == pv_[c]) src = top;
           }
-        col[h] = pk0 + e % ncol;
-        if ((col[h] < c0 || col[h] >= c0 + w) && src != key) {
-          v[h] = M[static_cast<int64_t>(src) * ld + col[h]];
+        if (src != key) {
           dst[h] = key;
+          if (pin) v[h] = M[static_cast<int64_t>(src) * ld + pcol];
         }
       }
     }
   }
-  __syncthreads();
+  // leaf columns back through the wavefront's LDS (row-contiguous stores)
+#pragma unroll
+  for (int q = 0; q < RPT; ++q)
+#pragma unroll
+    for (int h = 0; h < SG; ++h) {
+#pragma unroll
+      for (int c = 0; c < SB; ++c) stg[lane][c] = a[q][SB * h + c];
+      wave_lds_order();
+#pragma unroll
+      for (int k = 0; k < SB; ++k) {
+        const int dr = NT * q + (64 / SB) * k;
+        if (row0 + dr < nrel && SB * h + ec < w) Mw[dr * ld + SB * h] = stg[er + (64 / SB) * k][ec];
+      }
+      wave_lds_order();
+    }
+  __syncthreads();  // every source of the exchanges has been read
 #pragma unroll
   for (int h = 0; h < H; ++h)
-    if (dst[h] >= 0) M[dst[h] * ld + col[h]] = v[h];
+    if (dst[h] >= 0 && pin) M[static_cast<int64_t>(dst[h]) * ld + pcol] = v[h];
   if (tid == 0 && info_local != 0 && info_all[b] == 0) info_all[b] = info_local;
 }
 
@@ -902,9 +989,16 @@ bool leaf_lu<z64>(hipStream_t s, z64 *M, int64_t ld, int64_t stride, int32_t bat
                   int64_t c0, int w, int64_t pk0, int pkb, int32_t *ipiv, int32_t *info,
                   const GrpMat *grp, int nodes) {
   const int64_t rows = n - c0;
-  if (w < 1 || w > leaf_max_width<z64>(rows) || 2 * w * pkb > 2048) return false;
-  // (complex128 leaves of up to 2048 rows run a little faster with 512 threads)
-  if (rows <= 1024)
+  if (w < 1 || w > leaf_max_width<z64>(rows) || pkb > 128) return false;
+  // (as few threads as give one row each up to 512 rows: 200 rows 13.5 us a leaf
+  // against 14.7 with 512 threads; 512 threads up to 2048 rows: 1000 rows 18.1 us
+  // against 19.8 with 256 and 20.4 with 1024 threads, 2000 rows 24.6 against 25.6
+  // with 1024)
+  if (rows <= 256)
+    launch_leaf<z64, 1, 8, 256>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ipiv, info, grp, nodes);
+  else if (rows <= 512)
+    launch_leaf<z64, 1, 8, 512>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ipiv, info, grp, nodes);
+  else if (rows <= 1024)
     launch_leaf<z64, 2, 8, 512>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ipiv, info, grp, nodes);
   else if (rows <= 2048)
     launch_leaf<z64, 4, 8, 512>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ipiv, info, grp, nodes);
@@ -922,7 +1016,7 @@ bool leaf_lu<c64>(hipStream_t s, c64 *M, int64_t ld, int64_t stride, int32_t bat
                   int64_t c0, int w, int64_t pk0, int pkb, int32_t *ipiv, int32_t *info,
                   const GrpMat *grp, int nodes) {
   const int64_t rows = n - c0;
-  if (w < 1 || w > leaf_max_width<c64>(rows) || 2 * w * pkb > 2048) return false;
+  if (w < 1 || w > leaf_max_width<c64>(rows) || pkb > 128) return false;
   if (rows <= 1024)
     launch_leaf<c64, 1, 8>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ipiv, info, grp, nodes);
   else if (rows <= 2048)
