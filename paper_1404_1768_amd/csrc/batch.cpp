@@ -368,7 +368,7 @@ void lu_grouped(feast_batch *b, bool record) {
       const int64_t off = static_cast<int64_t>(nbig) * N;
       feast::lu_small<T>(b->gs, g + nbig, N, nsmall, b->nmax, piv + off * b->nmax,
                          b->info.as<int32_t>() + off);
-      feast::diag_block_inverse<T>(b->gs, nullptr, 0, 0, nsmall, b->nmax, 64, 0,
+      feast::diag_block_inverse<T>(b->gs, nullptr, 0, 0, nsmall, b->nmax, 0,
                                    b->np[nbig] / 64, true, Linv + off * is, is, g + nbig, N);
     }
   }
@@ -380,7 +380,7 @@ void lu_grouped(feast_batch *b, bool record) {
     const int actp = active(kp), nmat = actp * N;
     if (!record) {
       panel_grp<T>(b, F, nmat, kp, static_cast<int>(kPanel), kp, static_cast<int>(NB));
-      feast::diag_block_inverse<T>(b->gs, F, 0, 0, nmat, b->nmax, 64, jp, jp + 1, true, Linv, is,
+      feast::diag_block_inverse<T>(b->gs, F, 0, 0, nmat, b->nmax, jp, jp + 1, true, Linv, is,
                                    g, N);
     }
     const int acth = NB > kPanel ? active(kp + kPanel) : 0;
@@ -401,7 +401,7 @@ void lu_grouped(feast_batch *b, bool record) {
       if (!record) {
         panel_grp<T>(b, F, acth * N, kp + kPanel, static_cast<int>(kPanel), kp,
                      static_cast<int>(NB));
-        feast::diag_block_inverse<T>(b->gs, F, 0, 0, acth * N, b->nmax, 64, jp + 1, jp + 2, true,
+        feast::diag_block_inverse<T>(b->gs, F, 0, 0, acth * N, b->nmax, jp + 1, jp + 2, true,
                                      Linv, is, g, N);
       }
     }
@@ -476,7 +476,7 @@ void lu_grouped(feast_batch *b, bool record) {
   }
   if (!record) {
     const int nmat = b->P * N;
-    feast::diag_block_inverse<T>(b->gs, F, 0, 0, nmat, b->nmax, 64, 0, b->nblk, false, Uinv, is, g,
+    feast::diag_block_inverse<T>(b->gs, F, 0, 0, nmat, b->nmax, 0, b->nblk, false, Uinv, is, g,
                                  N);
     feast::perm_from_ipiv(b->gs, piv, b->perm.as<int32_t>(), b->nmax, nmat, g, N);
   }

@@ -197,7 +197,7 @@ void lu_batched(const LuStreams &st, T *M, int64_t ld, int64_t stride, int32_t b
     const int64_t k1 = k0 + kb, rest = n - k1;
     // the panel [k0, k1) is factored (on `s`, or on the side stream joined below)
     feast::laswp_outside<T>(s, M, ld, stride, batch, n, k0, kb, k0, k1, ipiv);
-    feast::diag_block_inverse<T>(s, M, ld, stride, batch, n, kIB, k0 / kIB,
+    feast::diag_block_inverse<T>(s, M, ld, stride, batch, n, k0 / kIB,
                                  (k1 + kIB - 1) / kIB, true, Linv, istride);
     if (rest <= 0) break;
     // U12 = L11^{-1} A12
@@ -233,7 +233,7 @@ void lu_batched(const LuStreams &st, T *M, int64_t ld, int64_t stride, int32_t b
                    M + ks * ld + ks);
         panel_rec<T>(s, M, ld, stride, batch, n, ks, nb, ks, nb, ipiv, info);
         feast::laswp_outside<T>(s, M, ld, stride, batch, n, ks, nb, ks, ke, ipiv);
-        feast::diag_block_inverse<T>(s, M, ld, stride, batch, n, kIB, ks / kIB,
+        feast::diag_block_inverse<T>(s, M, ld, stride, batch, n, ks / kIB,
                                      (ke + kIB - 1) / kIB, true, Linv, istride);
         timed_gemm(nb, n - ke, ks - k0, M + ks * ld + k0, M + k0 * ld + ke, M + ks * ld + ke);
         trsm_lower_rec<T>(s, M, ld, stride, batch, Linv, istride, ks, ke, M + ke, ld, stride,
@@ -250,7 +250,7 @@ void lu_batched(const LuStreams &st, T *M, int64_t ld, int64_t stride, int32_t b
     }
   }
   const int64_t nblk = (n + kIB - 1) / kIB;
-  feast::diag_block_inverse<T>(s, M, ld, stride, batch, n, kIB, 0, nblk, false, Uinv, istride);
+  feast::diag_block_inverse<T>(s, M, ld, stride, batch, n, 0, nblk, false, Uinv, istride);
 }
 
 // Triangular solves with the cached factors, in place on Y (per node: n x m,
@@ -1905,8 +1905,8 @@ void zgetrs_enqueue(hipStream_t s, int64_t n, int64_t nrhs, int32_t batch, const
                     int64_t strideM, const int32_t *dPiv, z64 *Xz, int64_t ldx, int64_t strideX,
                     int32_t trans, const GetrsScratch &w) {
   const int64_t nblk = (n + 63) / 64, ist = nblk * 64 * 64;
-  feast::diag_block_inverse<z64>(s, F, ldm, strideM, batch, n, 64, 0, nblk, true, w.Li, ist);
-  feast::diag_block_inverse<z64>(s, F, ldm, strideM, batch, n, 64, 0, nblk, false, w.Ui, ist);
+  feast::diag_block_inverse<z64>(s, F, ldm, strideM, batch, n, 0, nblk, true, w.Li, ist);
+  feast::diag_block_inverse<z64>(s, F, ldm, strideM, batch, n, 0, nblk, false, w.Ui, ist);
   feast::perm_from_ipiv(s, dPiv, w.perm, n, batch);
   if (trans == 0) {
     feast::gather_rows<z64>(s, Xz, ldx, strideX, w.perm, n, nrhs, batch, w.T, nrhs, n * nrhs);

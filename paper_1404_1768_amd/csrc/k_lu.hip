@@ -9,6 +9,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "tri64.h"
 
 namespace feast {
 
@@ -129,18 +130,6 @@ template <typename R> __device__ inline R wave_max(R x) {
   return lane_of(x, 63);
 }
 
-// Complex products by fused multiply-adds (four per complex multiply-add).
-template <typename T> __device__ inline T fmul(T a, T b) {
-  T r;
-  r.x = fma(a.x, b.x, -(a.y * b.y));
-  r.y = fma(a.x, b.y, a.y * b.x);
-  return r;
-}
-template <typename T> __device__ inline T ffms(T a, T b, T c) {  // a - b c
-  a.x = fma(b.y, c.y, fma(-b.x, c.x, a.x));
-  a.y = fma(-b.y, c.x, fma(-b.x, c.y, a.y));
-  return a;
-}
 // 1 / a for finite a != 0: a scaled by the power of two of its larger part, so
 // that |a|^2 is in [1/4, 2), one real reciprocal (the hardware's estimate and
 // Newton steps to full precision), scaled back.  No intermediate overflows or
@@ -164,14 +153,6 @@ template <typename T> __device__ inline T recip_scaled(T a) {
   o.x = ldexp(x * r, -e);
   o.y = -ldexp(y * r, -e);
   return o;
-}
-
-// Orders a wavefront's LDS writes before its later reads by other lanes (and
-// reads before later writes); the hardware runs one wavefront's LDS accesses in
-// order, so only the compiler is held.
-__device__ inline void wave_lds_order() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
 }
 
 // One workgroup of NT threads per matrix holds the leaf columns [c0, c0+w)
@@ -742,130 +723,65 @@ __global__ __launch_bounds__(256) void k_lu_small(const GrpMat *__restrict__ grp
 // owners of row i write all four of their rows and readers take block i / 16:
 // choosing the register block by i would put the array in scratch memory.
 
-// Inverse of one nb x nb diagonal block (nb = 64; lower unit or upper
-// non-unit) of each matrix, X = D^{-1} with X = I to start:
-//   lower: forward, row i of X is final at step i; rows r > i take
-//          X_r. -= D_ri X_i.;
-//   upper: backward, X_i. = X_i. / D_ii at step i; rows r < i take
-//          X_r. -= D_ri X_i..
-// Written zero padded to 64 x 64 at out + b out_stride + I 64^2.
+// Inverse of one 64 x 64 diagonal block of each matrix (lower unit or upper
+// non-unit), zero padded at out + b out_stride + I 64^2.  An upper block is
+// inverted as the lower one it is with rows and columns in reverse order; rows
+// past the matrix count as the identity.
+// 64-row blocks of 16 complex128 matrices: 42 us a launch by substitution over 64
+// rows, 10 us by halves (tri64.h).
 template <typename T>
 __global__ __launch_bounds__(256) void k_diag_inv(const T *__restrict__ Mall, int64_t ld_in,
-                                                  int64_t stride, int64_t n_in, int nb, int64_t blk0,
+                                                  int64_t stride, int64_t n_in, int64_t blk0,
                                                   bool lower, T *__restrict__ out,
                                                   int64_t out_stride,
                                                   const GrpMat *__restrict__ grp, int nodes) {
-  using Tr = cplx_traits<T>;
-  __shared__ T sD[64][65];
-  __shared__ T rowb[2][4][64];
+  __shared__ T S[64][kTP];
   const int64_t I = blk0 + blockIdx.x;
   const int b = blockIdx.y;
   const MatRef<const T> mr = mat_of<const T>(grp, nodes, Mall, ld_in, stride, n_in, b);
-  const T *M = mr.M;
-  const int64_t ld = mr.ld, n = mr.n;
-  const int64_t r0 = I * nb;
-  const int rb = static_cast<int>((n - r0 < nb) ? n - r0 : nb);
-  const int tid = threadIdx.x, ti = tid >> 4, tj = tid & 15;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  for (int e = tid; e < 64 * 64; e += 256) {
-    const int i = e >> 6, j = e & 63;
-    sD[i][j] = (i < rb && j < rb) ? M[(r0 + i) * ld + r0 + j] : czero<T>();
+  const int64_t ld = mr.ld, r0 = I * 64;
+  const int rb = static_cast<int>((mr.n - r0 < 64) ? mr.n - r0 : 64);  // (<= 0: past a smaller matrix)
+  const T *D = mr.M + r0 * (ld + 1);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rev = lower ? 0 : 63;  // index i of S is index i ^ rev of the block
+  T v[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const int i = wave + 4 * k;
+    const bool in = i < rb && lane < rb;
+    v[k] = in ? D[i * ld + lane] : cplx_traits<T>::make(i == lane ? 1.0 : 0.0, 0.0);
   }
-  T x[4][4];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-      x[a][c] = (ti + 16 * a == tj + 16 * c && ti + 16 * a < rb) ? Tr::make(1.0, 0.0) : czero<T>();
+  for (int k = 0; k < 16; ++k) S[(wave + 4 * k) ^ rev][lane ^ rev] = v[k];
   __syncthreads();
-  if (lower) {
-    for (int i = 0; i + 1 < rb; ++i) {
-      if (ti == (i & 15))  // the owners of row i publish it (all four row blocks)
+  tri64_inverse(S, lower, lane, wave);
+  T *o = out + b * out_stride + I * 4096;
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-          for (int c = 0; c < 4; ++c) rowb[i & 1][a][tj + 16 * c] = x[a][c];
-      __syncthreads();
-      T la[4], xb[4];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) la[a] = sD[ti + 16 * a][i];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) xb[c] = rowb[i & 1][i >> 4][tj + 16 * c];
-      // masked operands (rows r > i, columns j <= i) instead of masked results:
-      // a select on the register array would move it to scratch memory
-#pragma unroll
-      for (int c = 0; c < 4; ++c) xb[c] = (tj + 16 * c <= i) ? xb[c] : czero<T>();
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        if (16 * a + 4 * wv + 3 <= i) continue;
-        const T l = (ti + 16 * a > i) ? la[a] : czero<T>();
-#pragma unroll
-        for (int c = 0; c <= a; ++c) {  // X_rj = 0 for j > r
-          if (16 * c > i) continue;
-          x[a][c] = Tr::fms(x[a][c], l, xb[c]);
-        }
-      }
-    }
-  } else {
-    for (int i = rb - 1; i >= 0; --i) {
-      {  // the owners of row i scale and publish it (selects keep x in registers)
-        const T di = Tr::recip(sD[i][i]);
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          const T f = (ti + 16 * a == i) ? di : Tr::make(1.0, 0.0);
-#pragma unroll
-          for (int c = 0; c < 4; ++c) x[a][c] = Tr::mul(x[a][c], f);
-        }
-        if (ti == (i & 15))
-#pragma unroll
-          for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) rowb[i & 1][a][tj + 16 * c] = x[a][c];
-      }
-      __syncthreads();
-      if (i == 0) break;
-      T ua[4], xb[4];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) ua[a] = sD[ti + 16 * a][i];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) xb[c] = rowb[i & 1][i >> 4][tj + 16 * c];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) xb[c] = (tj + 16 * c >= i) ? xb[c] : czero<T>();
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        if (16 * a + 4 * wv >= i) continue;
-        const T u = (ti + 16 * a < i) ? ua[a] : czero<T>();  // rows r < i only
-#pragma unroll
-        for (int c = a; c < 4; ++c) {  // X_rj = 0 for j < r
-          if (16 * c + 15 < i) continue;
-          x[a][c] = Tr::fms(x[a][c], u, xb[c]);
-        }
-      }
-    }
+  for (int k = 0; k < 16; ++k) {
+    const int i = wave + 4 * k;
+    const bool in = i < rb && lane < rb && (lower ? lane <= i : lane >= i);
+    o[i * 64 + lane] = in ? S[i ^ rev][lane ^ rev] : czero<T>();
   }
-  T *o = out + b * out_stride + I * static_cast<int64_t>(nb) * nb;
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) o[(ti + 16 * a) * nb + tj + 16 * c] = x[a][c];
 }
 
 // Inverse of a 128-row diagonal block of a triangular factor from the inverses
 // I1, I2 of its two 64-row halves (zero padded past the order) and the
 // off-diagonal 64 x 64 block C of the factor:
-//   lower (unit):  [L11 0; C L22]^{-1} = [I1 0; -I2 C I1  I2]
-//   upper:         [U11 C; 0 U22]^{-1} = [I1  -I1 C I2; 0 I2]
-// One workgroup per (block, matrix); the two 64 x 64 x 64 products run from
-// LDS, 16 outputs per thread.
+//   lower (unit):  [L11 0; C L22]^{-1} = [I1 0; -(I2 C) I1  I2]
+//   upper:         [U11 C; 0 U22]^{-1} = [I1  -(I1 C) I2; 0 I2]
+// One workgroup per (block, matrix); the two 64 x 64 x 64 products run on the
+// matrix cores from LDS, one 16-row strip of the output per wavefront.  (16
+// complex128 matrices of order 200: 94 us a launch with each thread summing its
+// entries from LDS, 35 us so.)
 template <typename T>
 __global__ __launch_bounds__(256) void k_inv_pair(const T *__restrict__ F, int64_t ld,
                                                   int64_t fstride, int64_t n,
                                                   const T *__restrict__ inv64, int64_t istride,
                                                   T *__restrict__ inv128, int64_t istride2,
                                                   bool lower) {
-  using Tr = cplx_traits<T>;
-  __shared__ T sA[64][65];
-  __shared__ T sB[64][65];
+  __shared__ T sA[64][kTP];
+  __shared__ T sB[64][kTP];
   const int64_t B = blockIdx.x, b = blockIdx.y;
   const int64_t r0 = 128 * B;
   const int h2 = static_cast<int>((n - r0 - 64 < 64) ? n - r0 - 64 : 64);  // rows of the second half
@@ -873,61 +789,49 @@ __global__ __launch_bounds__(256) void k_inv_pair(const T *__restrict__ F, int64
   const T *I1 = inv64 + b * istride + (2 * B) * 4096;
   const T *I2 = I1 + 4096;
   T *out = inv128 + b * istride2 + B * 16384;
-  const int tid = threadIdx.x;
-  // the two diagonal halves (the second one absent when h2 <= 0)
-  for (int e = tid; e < 128 * 128; e += 256) {
-    const int i = e >> 7, j = e & 127;
-    T v = czero<T>();
-    if (i < 64 && j < 64) v = I1[i * 64 + j];
-    else if (i >= 64 && j >= 64 && h2 > 0) v = I2[(i - 64) * 64 + (j - 64)];
-    out[e] = v;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // the diagonal halves (the second one absent when h2 <= 0) and the zero block
+  for (int i = wave; i < 64; i += 4) {
+    const T d1 = I1[i * 64 + lane], d2 = h2 > 0 ? I2[i * 64 + lane] : czero<T>();
+    out[i * 128 + lane] = d1;
+    out[(64 + i) * 128 + 64 + lane] = d2;
+    if (lower) out[i * 128 + 64 + lane] = czero<T>();
+    else out[(64 + i) * 128 + lane] = czero<T>();
+    // first product: lower I2 C (C = rows [r0+64, r0+64+h2) x cols [r0, r0+64)),
+    //                upper I1 C (C = rows [r0, r0+64) x cols [r0+64, r0+64+h2))
+    sA[i][lane] = lower ? d2 : d1;
+    if (lower) sB[i][lane] = i < h2 ? M[(r0 + 64 + i) * ld + r0 + lane] : czero<T>();
+    else sB[i][lane] = lane < h2 ? M[(r0 + i) * ld + r0 + 64 + lane] : czero<T>();
+    if (h2 <= 0) {
+      if (lower) out[(64 + i) * 128 + lane] = czero<T>();
+      else out[i * 128 + 64 + lane] = czero<T>();
+    }
   }
   if (h2 <= 0) return;
-  // first product: lower T = C I1 (C = rows [r0+64, r0+64+h2) x cols [r0, r0+64)),
-  //                upper T = I1 C (C = rows [r0, r0+64) x cols [r0+64, r0+64+h2))
-  for (int e = tid; e < 64 * 64; e += 256) {
-    const int i = e >> 6, j = e & 63;
-    if (lower) {
-      sA[i][j] = (i < h2) ? M[(r0 + 64 + i) * ld + r0 + j] : czero<T>();
-      sB[i][j] = I1[i * 64 + j];
-    } else {
-      sA[i][j] = I1[i * 64 + j];
-      sB[i][j] = (j < h2) ? M[(r0 + i) * ld + r0 + 64 + j] : czero<T>();
+  __syncthreads();
+  Tile16<T> t[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) t[c].template mac<false>(sA, 16 * wave, 0, sB, 0, 16 * c, 16, lane);
+  __syncthreads();
+  // second product with the negated first one: lower (-I2 C) I1, upper (-I1 C) I2
+#pragma unroll
+  for (int c = 0; c < 4; ++c) t[c].put(sA, 16 * wave, 16 * c, lane, -1);
+  for (int i = wave; i < 64; i += 4) sB[i][lane] = (lower ? I1 : I2)[i * 64 + lane];
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    Tile16<T> x;
+    x.template mac<false>(sA, 16 * wave, 0, sB, 0, 16 * c, 16, lane);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = 16 * wave + mfma_ops<T>::out_row(lane, r), j = 16 * c + (lane & 15);
+      T v;
+      v.x = x.re[r];
+      v.y = x.im[r];
+      if (lower) out[(64 + i) * 128 + j] = v;
+      else out[i * 128 + 64 + j] = v;
     }
-  }
-  __syncthreads();
-  T acc[16];
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int e = tid + 256 * q, i = e >> 6, j = e & 63;
-    T x = czero<T>();
-    for (int l = 0; l < 64; ++l) x = Tr::fms(x, sA[i][l], sB[l][j]);  // accumulates -(A B)
-    acc[q] = x;
-  }
-  __syncthreads();
-  // second product with the negated first one: lower X = I2 (-C I1), upper X = (-I1 C) I2
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int e = tid + 256 * q, i = e >> 6, j = e & 63;
-    if (lower) {
-      sB[i][j] = acc[q];
-      sA[i][j] = I2[i * 64 + j];
-    } else {
-      sA[i][j] = acc[q];
-      sB[i][j] = I2[i * 64 + j];
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int e = tid + 256 * q, i = e >> 6, j = e & 63;
-    T x = czero<T>();
-    for (int l = 0; l < 64; ++l) x = Tr::fms(x, sA[i][l], sB[l][j]);
-    // x = -(sA sB): negate back to the product of the (already negated) factors
-    x.x = -x.x;
-    x.y = -x.y;
-    if (lower) out[(64 + i) * 128 + j] = x;
-    else out[i * 128 + 64 + j] = x;
   }
 }
 
@@ -1088,17 +992,17 @@ int panel_update_max_width() { return kPU; }
 
 template <typename T>
 void diag_block_inverse(hipStream_t s, const T *M, int64_t ld, int64_t stride, int32_t batch,
-                        int64_t n, int nb, int64_t blk0, int64_t blk1, bool lower, T *out,
+                        int64_t n, int64_t blk0, int64_t blk1, bool lower, T *out,
                         int64_t out_stride, const GrpMat *grp, int nodes) {
   if (blk1 <= blk0) return;
   hipLaunchKernelGGL((k_diag_inv<T>), dim3(static_cast<unsigned>(blk1 - blk0), batch), dim3(256),
-                     0, s, M, ld, stride, n, nb, blk0, lower, out, out_stride, grp, nodes);
+                     0, s, M, ld, stride, n, blk0, lower, out, out_stride, grp, nodes);
 }
 template void diag_block_inverse<z64>(hipStream_t, const z64 *, int64_t, int64_t, int32_t,
-                                      int64_t, int, int64_t, int64_t, bool, z64 *, int64_t,
+                                      int64_t, int64_t, int64_t, bool, z64 *, int64_t,
                                       const GrpMat *, int);
 template void diag_block_inverse<c64>(hipStream_t, const c64 *, int64_t, int64_t, int32_t,
-                                      int64_t, int, int64_t, int64_t, bool, c64 *, int64_t,
+                                      int64_t, int64_t, int64_t, bool, c64 *, int64_t,
                                       const GrpMat *, int);
 
 template <typename T>

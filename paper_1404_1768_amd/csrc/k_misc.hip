@@ -3,6 +3,7 @@
 // and the small t x t kernels of the orthonormalisation.
 #include "common.h"
 #include "kernels.h"
+#include "tri64.h"
 
 namespace feast {
 
@@ -303,176 +304,177 @@ __global__ __launch_bounds__(256) void k_add_shift(z64 *__restrict__ G, int64_t 
   for (int64_t i = threadIdx.x; i < t; i += 256) G[i * t + i].x += sh;
 }
 
-// Cholesky of one jb x jb (jb <= 64) Hermitian diagonal block and the inverse
-// of its factor, by one workgroup of S*S threads (S = 32: 1024 threads).  The
-// upper triangle of the block is read; R (upper) is written over it with the
-// strict lower part zeroed, and R^{-1} (jb x jb, upper) to Rinv (leading
-// dimension ldi).  Thread (ti, tj) holds the E*E entries (ti + S a, tj + S b),
-// a, b < E = 64/S, in registers; wave wv holds the rows ti in
-// [RW wv, RW (wv + 1)), RW = 64/S.  Cholesky step k subtracts
-// conj(G_ki) G_kj / G_kk from every entry with k < i <= j (row k is read-only
-// during the step); the inverse runs the same way from the bottom,
-// X_i. = B_i. / R_ii and B_r. -= R_ri X_i. for r < i with B = I to start.
-// Each step passes one finished row through LDS (double-buffered; its owners
-// write all E of their row blocks and readers take block i / S, because
-// choosing a register block by i would move the array to scratch memory), so
-// it needs one barrier, and skips the blocks whose entries it cannot change.
+// Cholesky of one jb x jb (jb <= 64) Hermitian diagonal block and the inverse of
+// its factor, by one workgroup.  The upper triangle of the block is read; R
+// (upper) is written over it with the strict lower part zeroed, and R^{-1}
+// (jb x jb, upper) to Rinv (leading dimension ldi).  Worked in LDS on the lower
+// factor L = R^*, 16 columns at a time: one wavefront factors the 16 x 16
+// diagonal block (chol16) and inverts it, the blocks below become
+// A_ik L_kk^{-*} and the rest A_ij - L_ik L_jk^* on the matrix cores; the
+// inverses of the diagonal blocks then join to L^{-1} (tri64.h).  Bound by the
+// chain of 64 pivots (about 0.25 us each) and the barriers; a barrier per pivot
+// and per substitution row on 1024 threads took 60 us a 64-row block and 35 us a
+// 30-row one, this takes 36 and 19.
 // flag[0] = 1 + col0 + k for the first non-positive pivot k (a unit pivot is
 // used in its place so the kernel finishes).
-template <int S>
+
+// The 16 x 16 diagonal block at (o, o) of S -> its Cholesky factor (lower
+// triangle; the strict upper one holds nothing of use), by one wavefront: lane
+// (g, c) = (lane / 16, lane % 16) holds the entries (c, 4 e + g), e < 4, and a
+// step passes its column through LDS, divided by nothing: the columns are scaled
+// by 1 / sqrt(pivot) at the end, together.
+// Returns 1 + the first non-positive pivot of the block, or 0.
+__device__ inline int chol16(z64 (*S)[feast::kTP], int o, int lane) {
+  const int c = lane & 15, g = lane >> 4;
+  z64 a[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) a[e] = S[o + c][o + 4 * e + g];
+  int bad = 0;
+  double mine = 1.0;  // row c's pivot
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    feast::wave_lds_order();
+    if (g == (k & 3)) S[o + c][o + k] = a[k >> 2];
+    feast::wave_lds_order();
+    double d = S[o + k][o + k].x;
+    const z64 ai = S[o + c][o + k];
+    z64 aj[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) aj[e] = S[o + 4 * e + g][o + k];
+    if (!(d > 0.0)) {
+      if (!bad) bad = k + 1;
+      d = 1.0;
+    }
+    if (c == k) mine = d;
+    double rd = __builtin_amdgcn_rcp(d);  // (d is a positive Gram entry; two Newton steps)
+    rd = fma(rd, fma(-d, rd, 1.0), rd);
+    rd = fma(rd, fma(-d, rd, 1.0), rd);
+    const double qr = ai.x * rd, qi = ai.y * rd;
+    // a_cj -= (a_ck / d) conj(a_jk) for j > k (columns of finished steps are dead)
+#pragma unroll
+    for (int e = k >> 2; e < 4; ++e) {
+      a[e].x = fma(-qi, aj[e].y, fma(-qr, aj[e].x, a[e].x));
+      a[e].y = fma(qr, aj[e].y, fma(-qi, aj[e].x, a[e].y));
+    }
+  }
+  const double sq = sqrt(mine), sc = 1.0 / sq;
+  feast::wave_lds_order();
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int j = 4 * e + g;
+    const double f = __shfl(sc, j);
+    z64 v = S[o + c][o + j];
+    v = c == j ? make_double2(sq, 0.0) : make_double2(v.x * f, v.y * f);
+    if (j <= c) S[o + c][o + j] = v;
+  }
+  feast::wave_lds_order();
+  return bad;
+}
+
 __device__ __forceinline__ void chol_inv_body(z64 *__restrict__ G, int64_t ld, int jb, int col0,
                                               int32_t *__restrict__ flag,
                                               z64 *__restrict__ Rinv, int64_t ldi) {
-  constexpr int E = 64 / S, RW = 64 / S;
-  __shared__ z64 row[2][E][64];
-  __shared__ z64 Rs[64][65];
-  __shared__ double dg[64];
-  const int tid = threadIdx.x, ti = tid / S, tj = tid % S;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  z64 v[E][E];
+  using feast::kTP;
+  __shared__ z64 S[64][kTP];
+  __shared__ z64 X[64][kTP];  // inverses of the diagonal blocks, then L^{-1}
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  {
+    z64 v[16];
 #pragma unroll
-  for (int a = 0; a < E; ++a)
-#pragma unroll
-    for (int b = 0; b < E; ++b) {
-      const int i = ti + S * a, j = tj + S * b;
-      v[a][b] = (i <= j && j < jb) ? G[i * ld + j] : make_double2(0.0, 0.0);
+    for (int k = 0; k < 16; ++k) {
+      const int i = wave + 4 * k;
+      v[k] = (i <= lane && lane < jb) ? G[i * ld + lane]
+                                      : make_double2(i == lane ? 1.0 : 0.0, 0.0);
     }
-  if (ti == 0)
 #pragma unroll
-    for (int a = 0; a < E; ++a)
-#pragma unroll
-      for (int b = 0; b < E; ++b) row[0][a][tj + S * b] = v[a][b];
-  __syncthreads();
-  for (int k = 0; k < jb; ++k) {
-    const z64 *rk = row[k & 1][k / S];
-    double d = rk[k].x;
-    if (!(d > 0.0)) {
-      if (tid == 0 && flag[0] == 0) flag[0] = col0 + k + 1;
-      d = 1.0;
-    }
-    if (tid == 0) dg[k] = d;
-    // all LDS reads of the step first, then branch-free updates (masked rows
-    // and columns take a zero update), so the reads overlap
-    z64 ri[E], rj[E];
-#pragma unroll
-    for (int a = 0; a < E; ++a) ri[a] = rk[ti + S * a];
-#pragma unroll
-    for (int b = 0; b < E; ++b) rj[b] = rk[tj + S * b];
-    const double rd = 1.0 / d;
-#pragma unroll
-    for (int a = 0; a < E; ++a) {
-      if (S * a + RW * wv + RW - 1 <= k) continue;  // the wave's rows of this block are done
-      const int i = ti + S * a;
-      const bool on = i > k && i < jb;
-      const double qr = on ? ri[a].x * rd : 0.0, qi = on ? -ri[a].y * rd : 0.0;  // conj(G_ki)/G_kk
-#pragma unroll
-      for (int b = a; b < E; ++b) {  // columns j >= i only
-        const int j = tj + S * b;
-        const bool up = j >= i && j < jb;
-        const double dx = qr * rj[b].x - qi * rj[b].y, dy = qr * rj[b].y + qi * rj[b].x;
-        v[a][b].x -= up ? dx : 0.0;
-        v[a][b].y -= up ? dy : 0.0;
-      }
-    }
-    const int nk = k + 1;
-    if (nk < jb && ti == nk % S)  // the owners of row k + 1 publish it
-#pragma unroll
-      for (int a = 0; a < E; ++a)
-#pragma unroll
-        for (int b = 0; b < E; ++b) row[nk & 1][a][tj + S * b] = v[a][b];
-    __syncthreads();
-  }
-  // R_ij = G_ij / sqrt(d_i) for i <= j (row i stops changing after step i - 1)
-#pragma unroll
-  for (int a = 0; a < E; ++a) {
-    const int i = ti + S * a;
-    const double sq = (i < jb) ? sqrt(dg[i]) : 1.0, sc = 1.0 / sq;
-#pragma unroll
-    for (int b = 0; b < E; ++b) {
-      const int j = tj + S * b;
-      z64 r = (i <= j && j < jb) ? make_double2(v[a][b].x * sc, v[a][b].y * sc)
-                                 : make_double2(0.0, 0.0);
-      if (i == j && i < jb) r = make_double2(sq, 0.0);
-      Rs[i][j] = r;
-      if (i < jb && j < jb) G[i * ld + j] = r;
-      v[a][b] = make_double2(i == j && i < jb ? 1.0 : 0.0, 0.0);
-    }
+    for (int k = 0; k < 16; ++k)  // A = lower triangle, conj of the upper one
+      if (wave + 4 * k <= lane) S[lane][wave + 4 * k] = zconj(v[k]);
   }
   __syncthreads();
-  // X = R^{-1}, from the bottom: at step i the owners scale row i by 1/R_ii
-  // (a factor per row block, not a select on v) and publish it
-  for (int i = jb - 1; i >= 0; --i) {
-    const double rii = 1.0 / Rs[i][i].x;
-#pragma unroll
-    for (int a = 0; a < E; ++a) {
-      const double f = (ti + S * a == i) ? rii : 1.0;
-#pragma unroll
-      for (int b = 0; b < E; ++b) {
-        v[a][b].x *= f;
-        v[a][b].y *= f;
-      }
+  const int nb16 = (jb + 15) / 16;  // (rows past jb are the identity)
+  for (int k = 0; k < nb16; ++k) {
+    const int o = 16 * k;
+    if (wave == 0) {
+      const int bad = chol16(S, o, lane);
+      if (bad && lane == 0 && flag[0] == 0) flag[0] = col0 + o + bad;
+      feast::wave_lds_order();
+      for (int e = lane; e < 256; e += 64)
+        X[o + (e >> 4)][o + (e & 15)] =
+            (e & 15) <= (e >> 4) ? S[o + (e >> 4)][o + (e & 15)] : make_double2(0.0, 0.0);
+      feast::wave_lds_order();
+      feast::wave_tri16(X, o, false, lane);
     }
-    if (i == 0) break;
-    if (ti == i % S)
-#pragma unroll
-      for (int a = 0; a < E; ++a)
-#pragma unroll
-        for (int b = 0; b < E; ++b) row[i & 1][a][tj + S * b] = v[a][b];
     __syncthreads();
-    const z64 *xi = row[i & 1][i / S];
-    z64 qa[E], xb[E];
+    if (wave > k && wave < nb16) {  // L_ik = A_ik L_kk^{-*} for the wavefront's row block
+      feast::Tile16<z64> t;
+      t.mac<true>(S, 16 * wave, o, X, o, o, 4, lane);
+      feast::wave_lds_order();
+      t.put(S, 16 * wave, o, lane, 1.0);
+    }
+    __syncthreads();
+    // A_ij -= L_ik L_jk^*, k < j <= i: at most six tiles over four wavefronts
+    for (int e = wave, n = 0, i = k + 1; i < nb16; ++i)
+      for (int j = k + 1; j <= i; ++j, ++n)
+        if (n == e) {
+          e += 4;
+          feast::Tile16<z64> t;
+          t.mac<true>(S, 16 * i, o, S, o, 16 * j, 4, lane);
 #pragma unroll
-    for (int a = 0; a < E; ++a) qa[a] = Rs[ti + S * a][i];
+          for (int r = 0; r < 4; ++r) {
+            const int row = 16 * i + feast::mfma_ops<z64>::out_row(lane, r);
+            const int col = 16 * j + (lane & 15);
+            z64 v = S[row][col];
+            v.x -= t.re[r];
+            v.y -= t.im[r];
+            S[row][col] = v;
+          }
+        }
+    __syncthreads();
+  }
+  if (wave >= nb16) {  // identity blocks past jb
+    for (int e = lane; e < 256; e += 64)
+      X[16 * wave + (e >> 4)][16 * wave + (e & 15)] =
+          make_double2((e >> 4) == (e & 15) ? 1.0 : 0.0, 0.0);
+  }
+  // blocks below the diagonal of L beside the inverted diagonal blocks
+  for (int e = tid; e < 6 * 256; e += 256) {
+    const int q = e >> 8, i = q < 1 ? 1 : q < 3 ? 2 : 3, j = q < 1 ? 0 : q < 3 ? q - 1 : q - 3;
+    const int row = 16 * i + ((e >> 4) & 15), col = 16 * j + (e & 15);
+    X[row][col] = S[row][col];
+  }
+  __syncthreads();
+  if (nb16 > 1) feast::tri_join<z64, 16>(X, lane, wave);
+  if (nb16 > 2) feast::tri_join<z64, 32>(X, lane, wave);
 #pragma unroll
-    for (int b = 0; b < E; ++b) xb[b] = xi[tj + S * b];
-#pragma unroll
-    for (int a = 0; a < E; ++a) {
-      if (S * a + RW * wv >= i) continue;  // none of the wave's rows of this block is above i
-      const int r = ti + S * a;
-      const bool on = r < i;
-      const double qr = on ? qa[a].x : 0.0, qi = on ? qa[a].y : 0.0;
-#pragma unroll
-      for (int b = a; b < E; ++b) {  // X_rj = 0 for j < r
-        if (S * b + S - 1 < i) continue;
-        const int j = tj + S * b;
-        const bool up = j >= i && j < jb;
-        const double dx = qr * xb[b].x - qi * xb[b].y, dy = qr * xb[b].y + qi * xb[b].x;
-        v[a][b].x -= up ? dx : 0.0;
-        v[a][b].y -= up ? dy : 0.0;
-      }
+  for (int k = 0; k < 16; ++k) {
+    const int i = wave + 4 * k;
+    if (i < jb && lane < jb) {
+      const bool up = i <= lane;
+      G[i * ld + lane] = up ? zconj(S[lane][i]) : make_double2(0.0, 0.0);
+      Rinv[i * ldi + lane] = up ? zconj(X[lane][i]) : make_double2(0.0, 0.0);
     }
   }
-#pragma unroll
-  for (int a = 0; a < E; ++a)
-#pragma unroll
-    for (int b = 0; b < E; ++b) {
-      const int i = ti + S * a, j = tj + S * b;
-      if (i < jb && j < jb) Rinv[i * ldi + j] = (i <= j) ? v[a][b] : make_double2(0.0, 0.0);
-    }
 }
 
-template <int S>
-__global__ __launch_bounds__(S * S) void k_chol_inv(z64 *__restrict__ G, int64_t ld, int jb,
-                                                    int col0, int32_t *__restrict__ flag,
-                                                    z64 *__restrict__ Rinv, int64_t ldi) {
-  chol_inv_body<S>(G, ld, jb, col0, flag, Rinv, ldi);
+__global__ __launch_bounds__(256) void k_chol_inv(z64 *__restrict__ G, int64_t ld, int jb, int col0,
+                                                  int32_t *__restrict__ flag,
+                                                  z64 *__restrict__ Rinv, int64_t ldi) {
+  chol_inv_body(G, ld, jb, col0, flag, Rinv, ldi);
 }
 
 // The same over a group: matrix b = blockIdx.x of g, its diagonal block at
 // (J0, J0) (skipped when J0 is past its order); the inverse of the factor to
 // Dinv + b * dstride + (J0 / 64) * 4096 (leading dimension 64), a breakdown
 // to flag[b * flag_stride].
-template <int S>
-__global__ __launch_bounds__(S * S) void k_chol_inv_grp(const GrpMat *__restrict__ g, int64_t J0,
-                                                        int32_t *__restrict__ flag,
-                                                        int flag_stride, z64 *__restrict__ Dinv,
-                                                        int64_t dstride) {
+__global__ __launch_bounds__(256) void k_chol_inv_grp(const GrpMat *__restrict__ g, int64_t J0,
+                                                      int32_t *__restrict__ flag, int flag_stride,
+                                                      z64 *__restrict__ Dinv, int64_t dstride) {
   const GrpMat e = g[blockIdx.x];
   if (J0 >= e.n) return;
   const int jb = static_cast<int>(e.n - J0 < 64 ? e.n - J0 : 64);
-  chol_inv_body<S>(static_cast<z64 *>(e.base) + J0 * e.ld + J0, e.ld, jb, static_cast<int>(J0),
-                   flag + blockIdx.x * flag_stride, Dinv + blockIdx.x * dstride + (J0 / 64) * 4096,
-                   64);
+  chol_inv_body(static_cast<z64 *>(e.base) + J0 * e.ld + J0, e.ld, jb, static_cast<int>(J0),
+                flag + blockIdx.x * flag_stride, Dinv + blockIdx.x * dstride + (J0 / 64) * 4096, 64);
 }
 
 // Strict lower triangle of a t x t matrix set to zero; optionally the whole matrix.
@@ -839,7 +841,7 @@ void add_diag_shift(hipStream_t s, z64 *G, int64_t t, double shift_rel) {
 
 void chol_inv_block(hipStream_t s, z64 *G, int64_t ld, int jb, int col0, int32_t *flag, z64 *Rinv,
                     int64_t ldi) {
-  hipLaunchKernelGGL((k_chol_inv<32>), dim3(1), dim3(1024), 0, s, G, ld, jb, col0, flag, Rinv, ldi);
+  hipLaunchKernelGGL((k_chol_inv), dim3(1), dim3(256), 0, s, G, ld, jb, col0, flag, Rinv, ldi);
 }
 
 void zero_lower(hipStream_t s, z64 *X, int64_t t, bool all) {
@@ -867,7 +869,7 @@ void add_shift_grp(hipStream_t s, const GrpMat *g, int count, const double *shif
 void chol_inv_grp(hipStream_t s, const GrpMat *g, int count, int64_t J0, int32_t *flag,
                   int flag_stride, z64 *Dinv, int64_t dstride) {
   if (count <= 0) return;
-  hipLaunchKernelGGL((k_chol_inv_grp<32>), dim3(count), dim3(1024), 0, s, g, J0, flag, flag_stride,
+  hipLaunchKernelGGL((k_chol_inv_grp), dim3(count), dim3(256), 0, s, g, J0, flag, flag_stride,
                      Dinv, dstride);
 }
 

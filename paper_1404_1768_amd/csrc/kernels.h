@@ -134,16 +134,16 @@ void panel_update(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch
 int panel_update_max_width();
 
 // Inverses of the diagonal blocks of the unit-lower L (lower=true) or of the
-// upper U (lower=false) factor: block I covers rows/cols [I*nb, min(n,(I+1)*nb)).
-// out[b][I] is an nb x nb row-major block (ld nb).  Blocks [blk0, blk1).
+// upper U (lower=false) factor: block I covers rows/cols [64 I, min(n, 64 (I+1))).
+// out[b][I] is a 64 x 64 row-major block (ld 64, zero padded).  Blocks [blk0, blk1).
 template <typename T>
 void diag_block_inverse(hipStream_t s, const T *M, int64_t ld, int64_t stride, int32_t batch,
-                        int64_t n, int nb, int64_t blk0, int64_t blk1, bool lower, T *out,
+                        int64_t n, int64_t blk0, int64_t blk1, bool lower, T *out,
                         int64_t out_stride, const GrpMat *grp = nullptr, int nodes = 1);
 
 // Inverted 128-row diagonal blocks (row-major 128 x 128, istride2 apart per
-// matrix) built from the inverted 64-row blocks of diag_block_inverse (nb = 64,
-// istride apart) and the factor's off-diagonal 64 x 64 blocks.
+// matrix) built from the inverted 64-row blocks of diag_block_inverse (istride
+// apart) and the factor's off-diagonal 64 x 64 blocks.
 template <typename T>
 void inverse_pairs(hipStream_t s, const T *M, int64_t ld, int64_t stride, int32_t batch, int64_t n,
                    const T *inv64, int64_t istride, T *inv128, int64_t istride2, bool lower);
