@@ -87,58 +87,65 @@ constexpr int kIB = 64;
 // third panel cost more than the wider update saves).
 template <typename T> constexpr int kGroup = sizeof(T) == 16 ? 3 : 2;
 
-// X <- L^{-1} X for the unit-lower L = M[r0:r1, r0:r1] (r0 a multiple of kIB)
-// and X = rows [r0, r1) of the block with columns starting at Xc (leading
-// dimension ldx, batch stride sX): recursive halving, leaves are in-place MFMA
-// products with the inverted kIB x kIB diagonal blocks.
-//   lb: rows of the inverted diagonal blocks (64, or 128 with leaf products on
-//   128-row tiles, which keep the in-place product within one workgroup).
+// X <- L^{-1} X for the unit-lower L = M[r0:r1, r0:r1] (r0 a multiple of lb)
+// and X = rows [r0, r1) of the block with columns starting at X (leading
+// dimension ldx, batch stride sX): recursive halving down to leaves, products
+// with the inverted lb x lb diagonal blocks.
+//   lb: rows of the inverted diagonal blocks (64 or 128).
+//   out: where the solution goes (leading dimension ldo, batch stride sO); X's
+//   rows are then overwritten with what the leaves multiply.  A leaf that does not
+//   write over its operand runs on many workgroups per column block (16
+//   complex128 matrices, 40 columns: 39 us a 128-row leaf in place, 7 us out
+//   of place).  out = X: in place, one workgroup per column block (lb = 64).
 template <typename T>
 void trsm_lower_rec(hipStream_t s, const T *M, int64_t ld, int64_t stride, int32_t batch,
                     const T *Linv, int64_t istride, int64_t r0, int64_t r1, T *X, int64_t ldx,
-                    int64_t sX, int64_t ncols, int ta, int lb = kIB) {
+                    int64_t sX, T *out, int64_t ldo, int64_t sO, int64_t ncols, int ta, int lb) {
   if (r1 - r0 <= lb) {
     gemm_t<T>(s, ta, r1 - r0, ncols, r1 - r0, zc(1.0), Linv + (r0 / lb) * lb * lb, lb, istride,
-              X + r0 * ldx, ldx, sX, zc(0.0), X + r0 * ldx, ldx, sX, batch, nullptr, 0,
-              lb > 64 ? feast::GEMM_TALL : feast::GEMM_SQUARE);
+              X + r0 * ldx, ldx, sX, zc(0.0), out + r0 * ldo, ldo, sO, batch);
     return;
   }
   const int64_t half = ((r1 - r0 + 2 * lb - 1) / (2 * lb)) * lb;
   const int64_t mid = r0 + half;
-  trsm_lower_rec<T>(s, M, ld, stride, batch, Linv, istride, r0, mid, X, ldx, sX, ncols, ta, lb);
+  trsm_lower_rec<T>(s, M, ld, stride, batch, Linv, istride, r0, mid, X, ldx, sX, out, ldo, sO,
+                    ncols, ta, lb);
   if (ta == 0)  // X[mid:r1] -= L[mid:r1, r0:mid] X[r0:mid]
     gemm_t<T>(s, 0, r1 - mid, ncols, mid - r0, zc(-1.0), M + mid * ld + r0, ld, stride,
-              X + r0 * ldx, ldx, sX, zc(1.0), X + mid * ldx, ldx, sX, batch, nullptr, 0,
+              out + r0 * ldo, ldo, sO, zc(1.0), X + mid * ldx, ldx, sX, batch, nullptr, 0,
               kSolveCfg<T>);
   else  // lower factor given as (U^*): rows [mid, r1) of U^* are columns of U rows [r0, mid)
     gemm_t<T>(s, 2, r1 - mid, ncols, mid - r0, zc(-1.0), M + r0 * ld + mid, ld, stride,
-              X + r0 * ldx, ldx, sX, zc(1.0), X + mid * ldx, ldx, sX, batch);
-  trsm_lower_rec<T>(s, M, ld, stride, batch, Linv, istride, mid, r1, X, ldx, sX, ncols, ta, lb);
+              out + r0 * ldo, ldo, sO, zc(1.0), X + mid * ldx, ldx, sX, batch);
+  trsm_lower_rec<T>(s, M, ld, stride, batch, Linv, istride, mid, r1, X, ldx, sX, out, ldo, sO,
+                    ncols, ta, lb);
 }
 
-// X <- U^{-1} X for the upper U = M[r0:r1, r0:r1] (ta = 0), or X <- L^{-*} X
-// with L^* unit upper (ta = 2, Linv holding the inverted blocks of L).
+// out <- U^{-1} X for the upper U = M[r0:r1, r0:r1] (ta = 0), or out <- L^{-*} X
+// with L^* unit upper (ta = 2, Inv holding the inverted blocks of L); X is
+// overwritten as in trsm_lower_rec.
 template <typename T>
 void trsm_upper_rec(hipStream_t s, const T *M, int64_t ld, int64_t stride, int32_t batch,
                     const T *Inv, int64_t istride, int64_t r0, int64_t r1, T *X, int64_t ldx,
-                    int64_t sX, int64_t ncols, int ta, int lb = kIB) {
+                    int64_t sX, T *out, int64_t ldo, int64_t sO, int64_t ncols, int ta, int lb) {
   if (r1 - r0 <= lb) {
     gemm_t<T>(s, ta, r1 - r0, ncols, r1 - r0, zc(1.0), Inv + (r0 / lb) * lb * lb, lb, istride,
-              X + r0 * ldx, ldx, sX, zc(0.0), X + r0 * ldx, ldx, sX, batch, nullptr, 0,
-              lb > 64 ? feast::GEMM_TALL : feast::GEMM_SQUARE);
+              X + r0 * ldx, ldx, sX, zc(0.0), out + r0 * ldo, ldo, sO, batch);
     return;
   }
   const int64_t half = ((r1 - r0 + 2 * lb - 1) / (2 * lb)) * lb;
   const int64_t mid = r0 + half;
-  trsm_upper_rec<T>(s, M, ld, stride, batch, Inv, istride, mid, r1, X, ldx, sX, ncols, ta, lb);
+  trsm_upper_rec<T>(s, M, ld, stride, batch, Inv, istride, mid, r1, X, ldx, sX, out, ldo, sO,
+                    ncols, ta, lb);
   if (ta == 0)  // X[r0:mid] -= U[r0:mid, mid:r1] X[mid:r1]
     gemm_t<T>(s, 0, mid - r0, ncols, r1 - mid, zc(-1.0), M + r0 * ld + mid, ld, stride,
-              X + mid * ldx, ldx, sX, zc(1.0), X + r0 * ldx, ldx, sX, batch, nullptr, 0,
+              out + mid * ldo, ldo, sO, zc(1.0), X + r0 * ldx, ldx, sX, batch, nullptr, 0,
               kSolveCfg<T>);
   else  // rows [r0, mid) of L^* are columns of L rows [mid, r1)
     gemm_t<T>(s, 2, mid - r0, ncols, r1 - mid, zc(-1.0), M + mid * ld + r0, ld, stride,
-              X + mid * ldx, ldx, sX, zc(1.0), X + r0 * ldx, ldx, sX, batch);
-  trsm_upper_rec<T>(s, M, ld, stride, batch, Inv, istride, r0, mid, X, ldx, sX, ncols, ta, lb);
+              out + mid * ldo, ldo, sO, zc(1.0), X + r0 * ldx, ldx, sX, batch);
+  trsm_upper_rec<T>(s, M, ld, stride, batch, Inv, istride, r0, mid, X, ldx, sX, out, ldo, sO,
+                    ncols, ta, lb);
 }
 
 // Streams and events of the look-ahead factorisation.
@@ -201,7 +208,8 @@ void lu_batched(const LuStreams &st, T *M, int64_t ld, int64_t stride, int32_t b
                                  (k1 + kIB - 1) / kIB, true, Linv, istride);
     if (rest <= 0) break;
     // U12 = L11^{-1} A12
-    trsm_lower_rec<T>(s, M, ld, stride, batch, Linv, istride, k0, k1, M + k1, ld, stride, rest, 0);
+    trsm_lower_rec<T>(s, M, ld, stride, batch, Linv, istride, k0, k1, M + k1, ld, stride, M + k1, ld,
+                      stride, rest, 0, kIB);
     const int kb1 = static_cast<int>(std::min<int64_t>(nb, rest));
     if (ahead && rest > kb1 && rest <= st.ahead_rows) {
       // look-ahead: update the next panel's columns (whole chip), then factor
@@ -237,7 +245,7 @@ void lu_batched(const LuStreams &st, T *M, int64_t ld, int64_t stride, int32_t b
                                      (ke + kIB - 1) / kIB, true, Linv, istride);
         timed_gemm(nb, n - ke, ks - k0, M + ks * ld + k0, M + k0 * ld + ke, M + ks * ld + ke);
         trsm_lower_rec<T>(s, M, ld, stride, batch, Linv, istride, ks, ke, M + ke, ld, stride,
-                          n - ke, 0);
+                          M + ke, ld, stride, n - ke, 0, kIB);
         kg = ke;
       }
       timed_gemm(n - kg, n - kg, kg - k0, M + kg * ld + k0, M + k0 * ld + kg, M + kg * ld + kg);
@@ -257,25 +265,26 @@ void lu_batched(const LuStreams &st, T *M, int64_t ld, int64_t stride, int32_t b
 // leading dimension ldy, node stride sY):
 //   trans = 0: Y <- U^{-1} L^{-1} Y   (after the row permutation)
 //   trans = 2: Y <- L^{-*} U^{-*} Y   (before the inverse permutation)
+// S: scratch of Y's shape (leading dimension ldsc, node stride sS): the first
+// solve goes from Y to S, the second back.
 template <typename T>
 void trsolve(hipStream_t s, const T *F, int64_t ld, int64_t fstride, int32_t batch, int64_t n,
              const T *Linv, const T *Uinv, int64_t istride, T *Y, int64_t m, int64_t ldy,
-             int64_t sY, int trans, int lb = kIB) {
-  if (trans == 0) {
-    trsm_lower_rec<T>(s, F, ld, fstride, batch, Linv, istride, 0, n, Y, ldy, sY, m, 0, lb);
-    trsm_upper_rec<T>(s, F, ld, fstride, batch, Uinv, istride, 0, n, Y, ldy, sY, m, 0, lb);
-  } else {
-    trsm_lower_rec<T>(s, F, ld, fstride, batch, Uinv, istride, 0, n, Y, ldy, sY, m, 2, lb);
-    trsm_upper_rec<T>(s, F, ld, fstride, batch, Linv, istride, 0, n, Y, ldy, sY, m, 2, lb);
-  }
+             int64_t sY, T *S, int64_t ldsc, int64_t sS, int trans, int lb = kIB) {
+  const T *first = trans == 0 ? Linv : Uinv, *second = trans == 0 ? Uinv : Linv;
+  trsm_lower_rec<T>(s, F, ld, fstride, batch, first, istride, 0, n, Y, ldy, sY, S, ldsc, sS, m, trans,
+                    lb);
+  trsm_upper_rec<T>(s, F, ld, fstride, batch, second, istride, 0, n, S, ldsc, sS, Y, ldy, sY, m,
+                    trans, lb);
 }
 
-// The plan's solves: leaves on its inverted 128 x 128 diagonal blocks.
+// The plan's solves: leaves on its inverted 128 x 128 diagonal blocks; S as
+// Y (same leading dimension and node stride).
 template <typename T>
-void plan_trsolve(feast_plan *p, hipStream_t s, T *Y, int64_t m, int64_t ldy, int64_t sY,
+void plan_trsolve(feast_plan *p, hipStream_t s, T *Y, T *S, int64_t m, int64_t ldy, int64_t sY,
                   int trans) {
   trsolve<T>(s, p->F.as<T>(), p->n, p->fstride(), p->N, p->n, p->Linv2.as<T>(), p->Uinv2.as<T>(),
-             p->istride2(), Y, m, ldy, sY, trans, 128);
+             p->istride2(), Y, m, ldy, sY, S, ldy, sY, trans, 128);
 }
 
 // ---------------------------------------------------------------------------
@@ -410,7 +419,8 @@ void solve_nodes_z(feast_plan *p, const z64 *R, int64_t ldr, int64_t cols) {
   ktimed(p, FEAST_K_GATHER, 16.0 * n * cols * (1 + p->N), [&]() {
     feast::gather_rows<z64>(p->s, R, ldr, 0, p->perm.as<int32_t>(), n, cols, p->N, Y, ldY, m);
   });
-  plan_trsolve<z64>(p, p->s, Y, cols, ldY, m, 0);
+  p->Y2.alloc(sizeof(z64) * n * ldY);
+  plan_trsolve<z64>(p, p->s, Y, p->Y2.as<z64>(), cols, ldY, m, 0);
 }
 
 // Mixed form: complex64 LU solves; FP64 residual r_j = R - (z_j B - A) Y_j of
@@ -444,7 +454,7 @@ void solve_nodes_mixed(feast_plan *p, const z64 *A, int64_t lda, const z64 *B, i
            [&]() { feast::gather_rows<z64>(s, R, ldr, 0, perm, n, m, N, T1, ldY, sY); });
     ktimed(p, FEAST_K_Z2C, 24.0 * n * ldY,
            [&]() { feast::z_to_c(s, T1, ldY, 0, n, ldY, 1, Yc, ldY, 0, rn, rcnt); });
-    plan_trsolve<c64>(p, s, Yc, m, ldY, sY, 0);
+    plan_trsolve<c64>(p, s, Yc, p->Yc2.as<c64>(), m, ldY, sY, 0);
     ktimed(p, FEAST_K_C2Z, 24.0 * n * ldY,
            [&]() { feast::c_to_z(s, Yc, ldY, 0, n, ldY, 1, Y, ldY, 0, rn, rcnt); });
   }
@@ -493,7 +503,7 @@ void solve_nodes_mixed(feast_plan *p, const z64 *A, int64_t lda, const z64 *B, i
            [&]() { feast::gather_rows<z64>(s, T1, ldY, sY, perm, n, m, N, T2, ldY, sY); });
     ktimed(p, FEAST_K_Z2C, 24.0 * n * ldY,
            [&]() { feast::z_to_c(s, T2, ldY, 0, n, ldY, 1, Yc, ldY, 0, rn, rcnt); });
-    plan_trsolve<c64>(p, s, Yc, m, ldY, sY, 0);
+    plan_trsolve<c64>(p, s, Yc, p->Yc2.as<c64>(), m, ldY, sY, 0);
     if (sweep == 0) {
       // the first correction relative to the solution it corrects: about the
       // forward error of the complex64 solves, u32 cond(z_j B - A)
@@ -646,6 +656,7 @@ void ensure_workspace(feast_plan *p, bool with_nodes) {
     p->T1.alloc(zs * n * m * N);
     p->T2.alloc(zs * n * m * N);
     p->Yc.alloc(sizeof(c64) * n * m * N);
+    p->Yc2.alloc(sizeof(c64) * n * m * N);
   }
 }
 
@@ -883,7 +894,7 @@ int feast_plan_destroy(feast_plan *p) {
   for (hipEvent_t e : {p->ev_fork, p->ev_join})
     if (e) (void)hipEventDestroy(e);
   for (DevBuf *b : {&p->dz, &p->dw, &p->dwc, &p->adj, &p->adj_piv, &p->adj_info, &p->adj_inv, &p->F, &p->piv, &p->perm, &p->info, &p->Linv, &p->Uinv, &p->Linv2, &p->Uinv2, &p->cirr_w, &p->R,
-                    &p->Y, &p->T1, &p->T2, &p->Yc, &p->W, &p->G, &p->splitws, &p->splitws2, &p->part, &p->nrm,
+                    &p->Y, &p->Y2, &p->T1, &p->T2, &p->Yc, &p->Yc2, &p->W, &p->G, &p->splitws, &p->splitws2, &p->part, &p->nrm,
                     &p->flag, &p->small, &p->fp, &p->rn})
     b->release();
   delete p;
@@ -1747,7 +1758,7 @@ int feast_left_eigvecs(feast_plan *p, const feast_z *dA, int64_t lda, const feas
       // W = sum_j conj(w_j) (z_j B - A)^{-*} G with the cached factors:
       // (z_j B - A)^* = U^* L^* P, so solve with U^*, then L^*, then undo P
       feast::bcast_cols(s, G, sc, n, sc, N, Y, ldw);
-      plan_trsolve<z64>(p, s, Y, sc, ldw, sc, 2);
+      plan_trsolve<z64>(p, s, Y, Adj, sc, ldw, sc, 2);
       feast::scatter_rows<z64>(s, Y, ldw, sc, p->perm.as<int32_t>(), n, sc, N, Adj, ldw, sc);
       feast::weighted_sum(s, Adj, ldw, sc, p->dwc.as<z64>(), N, n, sc, W, sc);
     }
@@ -1767,7 +1778,7 @@ int feast_left_eigvecs(feast_plan *p, const feast_z *dA, int64_t lda, const feas
     feast::perm_from_ipiv(s, piv, perm, sc, 1);
     feast::identity(s, S, sc);
     feast::gather_rows<z64>(s, S, sc, 0, perm, sc, sc, 1, Z, sc, 0);
-    trsolve<z64>(s, T, sc, 0, 1, sc, Li, Ui, nb64 * 64 * 64, Z, sc, sc, 0, 0);
+    trsolve<z64>(s, T, sc, 0, 1, sc, Li, Ui, nb64 * 64 * 64, Z, sc, sc, 0, S, sc, 0, 0);
     gemm_t<z64>(s, 0, n, sc, sc, zc(1.0), W, sc, 0, Z, sc, 0, zc(0.0), reinterpret_cast<z64 *>(dY),
                 ldy, 0, 1);
     int32_t hinfo = 0;
@@ -1910,13 +1921,15 @@ void zgetrs_enqueue(hipStream_t s, int64_t n, int64_t nrhs, int32_t batch, const
   feast::perm_from_ipiv(s, dPiv, w.perm, n, batch);
   if (trans == 0) {
     feast::gather_rows<z64>(s, Xz, ldx, strideX, w.perm, n, nrhs, batch, w.T, nrhs, n * nrhs);
-    trsolve<z64>(s, F, ldm, strideM, batch, n, w.Li, w.Ui, ist, w.T, nrhs, nrhs, n * nrhs, 0);
+    trsolve<z64>(s, F, ldm, strideM, batch, n, w.Li, w.Ui, ist, w.T, nrhs, nrhs, n * nrhs, Xz, ldx,
+                 strideX, 0);
     for (int32_t i = 0; i < batch; ++i)
       feast::copy_block_z(s, w.T + i * n * nrhs, nrhs, n, nrhs, Xz + i * strideX, ldx);
   } else {
     for (int32_t i = 0; i < batch; ++i)
       feast::copy_block_z(s, Xz + i * strideX, ldx, n, nrhs, w.T + i * n * nrhs, nrhs);
-    trsolve<z64>(s, F, ldm, strideM, batch, n, w.Li, w.Ui, ist, w.T, nrhs, nrhs, n * nrhs, 2);
+    trsolve<z64>(s, F, ldm, strideM, batch, n, w.Li, w.Ui, ist, w.T, nrhs, nrhs, n * nrhs, Xz, ldx,
+                 strideX, 2);
     feast::scatter_rows<z64>(s, w.T, nrhs, n * nrhs, w.perm, n, nrhs, batch, Xz, ldx, strideX);
   }
 }

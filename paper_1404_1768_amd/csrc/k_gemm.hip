@@ -770,32 +770,32 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const GemmArgs<T> d) {
   *C = v;
 }
 
-template <typename T, int BM, int BN, int BK = 16>
-void launch_cfg(hipStream_t s, const GemmArgs<T> &d, int ta, bool update = false) {
-  const int64_t tiles = ((d.M + BM - 1) / BM) * ((d.N + BN - 1) / BN);
+template <typename T>
+void launch_tiles(hipStream_t s, const GemmArgs<T> &d, int ta, int cfg) {
+  const int BM = cfg == GEMM_UPDATE_TALL ? 128 : 64;
+  const int64_t tiles = ((d.M + BM - 1) / BM) * ((d.N + 63) / 64);
   const int64_t total = tiles * d.batch * d.splits;
   const int64_t padded = (total + 7) / 8 * 8;
   const dim3 grid(static_cast<unsigned>(padded));
   // C -= op(A) B is recognised from alpha = -1, beta = 1 without split-K
   const bool sub = d.splits == 1 && d.alpha.x == -1.0 && d.alpha.y == 0.0 && d.beta.x == 1.0 &&
                    d.beta.y == 0.0;
-  if (ta == 0) {
-    // (BK = 8: two workgroups per compute unit in FP64, four in complex64; the
-    // 128-row tiles take this instance for every C -= A B, which at BK = 16
-    // would spill in complex64)
-    if (sub && (update || BM > 64))
-      hipLaunchKernelGGL((k_gemm<T, BM, BN, 0, true, 8, true>), grid, dim3(256), 0, s, d, padded);
-    else if (sub) {
-      if constexpr (BM == 64)
-        hipLaunchKernelGGL((k_gemm<T, BM, BN, 0, true, BK>), grid, dim3(256), 0, s, d, padded);
-    }
+  if (ta == 0 && sub) {
+    // (BK = 8: two workgroups per compute unit in FP64, four in complex64)
+    if (cfg == GEMM_UPDATE_TALL)
+      hipLaunchKernelGGL((k_gemm<T, 128, 64, 0, true, 8, true>), grid, dim3(256), 0, s, d, padded);
+    else if (cfg == GEMM_UPDATE)
+      hipLaunchKernelGGL((k_gemm<T, 64, 64, 0, true, 8, true>), grid, dim3(256), 0, s, d, padded);
+    else if (cfg == GEMM_SOLVE)
+      hipLaunchKernelGGL((k_gemm_solve<T>), grid, dim3(256), 0, s, d, padded);
     else
-      hipLaunchKernelGGL((k_gemm<T, BM, BN, 0, false, BK>), grid, dim3(256), 0, s, d, padded);
+      hipLaunchKernelGGL((k_gemm<T, 64, 64, 0, true, 16>), grid, dim3(256), 0, s, d, padded);
+  } else if (ta == 0) {
+    hipLaunchKernelGGL((k_gemm<T, 64, 64, 0, false, 16>), grid, dim3(256), 0, s, d, padded);
+  } else if (sub) {
+    hipLaunchKernelGGL((k_gemm<T, 64, 64, 2, true, 16>), grid, dim3(256), 0, s, d, padded);
   } else {
-    if (sub)
-      hipLaunchKernelGGL((k_gemm<T, BM, BN, 2, true, BK>), grid, dim3(256), 0, s, d, padded);
-    else
-      hipLaunchKernelGGL((k_gemm<T, BM, BN, 2, false, BK>), grid, dim3(256), 0, s, d, padded);
+    hipLaunchKernelGGL((k_gemm<T, 64, 64, 2, false, 16>), grid, dim3(256), 0, s, d, padded);
   }
 }
 
@@ -817,15 +817,15 @@ template <typename T> void launch_splitk_reduce(hipStream_t s, const GemmArgs<T>
                      s, d);
 }
 
-// complex128 products of at most kSmallTiles 64 x 64 output tiles (no more than
-// compute units: each unit would run one 64 x 64 workgroup at most) take
-// k_gemm_ks; above, the 64 x 64 tiles read less per flop and are as fast or
+// Products of at most kSmallTiles 64 x 64 output tiles (no more than compute
+// units: each unit would run one 64 x 64 workgroup at most) take k_gemm_ks; above, the 64 x 64 tiles read less per flop and are as fast or
 // faster (512 tiles, K = 128: 42 us against 46; 1024 tiles, K = 40: 42 against
 // 58).  In-place products (C is A or B) need one workgroup per column block and
 // keep the 64 x 64 tiles.  Sixteen wavefronts while that leaves units idle
 // (157 x 157 x 4001, 100 tiles: 41 us against 46 with eight); 32 x 16 tiles for
-// many tiles with a long sum (4000 x 160 x 4000: 349 us against 380), where the
-// operands' traffic counts.
+// many tiles, where the operands' traffic counts: eight wavefronts for a long sum
+// (4000 x 160 x 4000: 349 us against 380), four for a short one, so that all
+// workgroups fit at once (4000 x 160 x 160: 24 us against 26).
 constexpr int64_t kSmallTiles = 256;
 
 template <typename T>
@@ -845,6 +845,8 @@ void gemm_small(hipStream_t s, GemmArgs<T> d, int ta, int64_t work_elems) {
     launch_ks<T, 1, 1, 16>(s, d, ta);
   else if (t16 > 1024 && d.K >= 1024)
     launch_ks<T, 2, 1, 8>(s, d, ta);
+  else if (t16 > 1024)
+    launch_ks<T, 2, 1, 4>(s, d, ta);
   else
     launch_ks<T, 1, 1, 8>(s, d, ta);
   if (d.splits > 1) launch_splitk_reduce<T>(s, d);
@@ -861,12 +863,10 @@ void gemm_impl(hipStream_t s, GemmArgs<T> d, int ta, int cfg, int64_t work_elems
   d.kchunk = d.K > 0 ? d.K : 1;
   // (a 128 x 128 complex64 tile measured slower than 64 x 64 in the LU update,
   // and the FP64 one needs more than the 512 registers of a lane: not used)
-  const int BM = (cfg == GEMM_TALL || cfg == GEMM_UPDATE_TALL) ? 128 : 64;
-  if constexpr (sizeof(T) == 16)
-    if (BM == 64 && d.A != d.C && d.B != d.C &&
-        ((d.M + 63) / 64) * ((d.N + 63) / 64) * d.batch <= kSmallTiles)
-      return gemm_small<T>(s, d, ta, work_elems);
-  const int64_t tiles = ((d.M + BM - 1) / BM) * ((d.N + 63) / 64);
+  if (d.A != d.C && d.B != d.C && cfg != GEMM_UPDATE_TALL &&
+      ((d.M + 63) / 64) * ((d.N + 63) / 64) * d.batch <= kSmallTiles)
+    return gemm_small<T>(s, d, ta, work_elems);
+  const int64_t tiles = ((d.M + 63) / 64) * ((d.N + 63) / 64);
   // Split K when the output is too small to fill the chip (aiming at about
   // three workgroups per compute unit, each K chunk at least 64 long: the
   // Gram products of an n x m block, m <= 160, are otherwise a few long
@@ -881,18 +881,7 @@ void gemm_impl(hipStream_t s, GemmArgs<T> d, int ta, int cfg, int64_t work_elems
       d.splits = static_cast<int32_t>((d.K + d.kchunk - 1) / d.kchunk);
     }
   }
-  const bool sub = d.splits == 1 && d.alpha.x == -1.0 && d.alpha.y == 0.0 && d.beta.x == 1.0 &&
-                   d.beta.y == 0.0;
-  if (cfg == GEMM_SOLVE && ta == 0 && sub) {
-    const int64_t tiles2 = ((d.M + 63) / 64) * ((d.N + 63) / 64) * d.batch;
-    const int64_t padded = (tiles2 + 7) / 8 * 8;
-    hipLaunchKernelGGL((k_gemm_solve<T>), dim3(static_cast<unsigned>(padded)), dim3(256), 0, s, d,
-                       padded);
-  } else if (cfg == GEMM_TALL || cfg == GEMM_UPDATE_TALL) {
-    launch_cfg<T, 128, 64>(s, d, ta, cfg == GEMM_UPDATE_TALL);
-  } else {
-    launch_cfg<T, 64, 64>(s, d, ta, cfg == GEMM_UPDATE);
-  }
+  launch_tiles<T>(s, d, ta, ta == 0 ? cfg : static_cast<int>(GEMM_SQUARE));
   if (d.splits > 1) launch_splitk_reduce<T>(s, d);
 }
 

@@ -46,11 +46,11 @@ void zgemm_shift_residual(hipStream_t s, int64_t M, int64_t N, int64_t K, const 
 // kernel names of their own (the LU trailing update); GEMM_SOLVE: C -= A B
 // (no transpose) on the update's 64 x 64 tile under a third name (the
 // triangular solves), other products as GEMM_SQUARE.
-enum { GEMM_SQUARE = 0, GEMM_TALL = 1, GEMM_UPDATE = 3, GEMM_UPDATE_TALL = 4, GEMM_SOLVE = 5 };
+enum { GEMM_SQUARE = 0, GEMM_UPDATE = 3, GEMM_UPDATE_TALL = 4, GEMM_SOLVE = 5 };
 
 // C_b = alpha op(A_b) B_b + beta C_b; transA 0: A is M x K; 2: A stored K x M, op = ^*.
 // `work` (optional, work_elems entries) enables split-K for small outputs.
-// GEMM_TALL uses 128-row tiles (needed for in-place products with M <= 128).
+// In-place products (C is B) need M <= 64: one workgroup per column block.
 void zgemm(hipStream_t s, int transA, int64_t M, int64_t N, int64_t K, z64 alpha, const z64 *A,
            int64_t lda, int64_t sA, const z64 *B, int64_t ldb, int64_t sB, z64 beta, z64 *C,
            int64_t ldc, int64_t sC, int32_t batch, z64 *work = nullptr, int64_t work_elems = 0,

@@ -51,3 +51,27 @@ def test_orthonormalisation_at_the_block_edges(m):
     assert np.linalg.norm(low) < 5 * np.sqrt(n) * m * U * np.linalg.norm(Bt)
     assert np.all(np.diag(Bt).real > 0)
     assert np.allclose(Bt.conj().T @ Bt, BQ.conj().T @ BQ, rtol=0, atol=1e-12 * m)
+
+
+@pytest.mark.parametrize("n,nrhs", [(64, 3), (65, 17), (300, 20), (520, 130)])
+@pytest.mark.parametrize("trans", [0, 2])
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_solves_between_padded_blocks(n, nrhs, trans, noalloc):
+    # the right-hand sides' own rows serve as the solves' second block: nothing
+    # beside them (columns past nrhs, rows past n) may be read or written
+    rng = np.random.default_rng(n + nrhs)
+    M, R = crand(rng, 2, n, n), crand(rng, 2, n, nrhs)
+    tM = torch.from_numpy(M.copy()).to(DEV)
+    piv, info = fm.zgetrf_batched(tM)
+    box = torch.full((2, n + 2, nrhs + 3), complex(np.nan, np.nan), dtype=torch.complex128, device=DEV)
+    tX = box[:, :n, :nrhs]
+    tX.copy_(torch.from_numpy(R).to(DEV))
+    (fm.zgetrs_batched_noalloc if noalloc else fm.zgetrs_batched)(tM, piv, tX, trans=trans)
+    out = box.cpu().numpy()
+    assert np.all(np.isnan(out[:, n:].real)) and np.all(np.isnan(out[:, :, nrhs:].real))
+    for b in range(2):
+        X = out[b, :n, :nrhs]
+        Mb = M[b] if trans == 0 else M[b].conj().T
+        be = np.linalg.norm(Mb @ X - R[b]) / (np.linalg.norm(Mb) * np.linalg.norm(X) +
+                                              np.linalg.norm(R[b]))
+        assert be < 1e-15 * n + 1e-15, be
