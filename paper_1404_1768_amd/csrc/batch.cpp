@@ -314,22 +314,13 @@ GemmArgs<T> gargs(int64_t M, int64_t Nc, int64_t K, const T *A, int64_t lda, int
 // complex64 102.5 ms with one, 100.1 / 100.3 / 101.2 with two / three / four).
 template <typename T> constexpr int kBatchGroup = sizeof(T) == 16 ? 4 : 2;
 
-// Panel [c0, c0 + w) of the active matrices: halves down to register leaves,
-// each split joined by the fused triangular solve + rank update.
+// Columns [c0, c0 + w) of the active matrices, w <= 64, inside the panel
+// [pk0, pk0 + pkb).
 template <typename T>
 void panel_grp(feast_batch *b, T *F, int nmat, int64_t c0, int w, int64_t pk0, int pkb) {
-  const GrpMat *g = b->grp.as<GrpMat>();
-  int32_t *piv = b->piv.as<int32_t>(), *info = b->info.as<int32_t>();
-  const int ib = feast::leaf_max_width<T>(b->nmax - c0);
-  if (w <= ib) {
-    if (!feast::leaf_lu<T>(b->gs, F, 0, 0, nmat, b->nmax, c0, w, pk0, pkb, piv, info, g, b->N))
-      throw HipError{hipErrorInvalidValue, "leaf_lu"};
-    return;
-  }
-  const int w1 = w / 2, w2 = w - w1;
-  panel_grp<T>(b, F, nmat, c0, w1, pk0, pkb);
-  feast::panel_update<T>(b->gs, F, 0, 0, nmat, b->nmax, c0, w1, w2, g, b->N);
-  panel_grp<T>(b, F, nmat, c0 + w1, w2, pk0, pkb);
+  if (!feast::panel_cols<T>(b->gs, F, 0, 0, nmat, b->nmax, c0, w, pk0, pkb, b->piv.as<int32_t>(),
+                            b->info.as<int32_t>(), b->grp.as<GrpMat>(), b->N))
+    throw HipError{hipErrorInvalidValue, "panel_cols"};
 }
 
 // Blocked right-looking LU of every shifted matrix of every pencil in lockstep,

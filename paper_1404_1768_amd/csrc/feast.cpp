@@ -35,34 +35,34 @@ namespace {
 
 // ---------------------------------------------------------------------------
 // Blocked right-looking LU of `batch` matrices (row-major, partial pivoting).
-// Panels of width nb are factored recursively (left half, small TRSM, GEMM
-// update of the right half, right half) down to register-resident leaves;
+// A panel of width nb is factored 64 columns at a time (feast::panel_cols: leaves
+// and their updates); the two halves of a 128-column panel are joined by the
+// product with the first half's inverted diagonal block and an MFMA update;
 // then the panel's swaps reach the columns outside it, U12 = L11^{-1} A12 is
-// an in-place MFMA product with the inverted diagonal block, and the trailing
+// an in-place MFMA product with the inverted diagonal blocks, and the trailing
 // update A22 -= L21 U12 is one batched MFMA GEMM over all matrices.
 // ---------------------------------------------------------------------------
+
+// Panel [c0, c0 + w), c0 a multiple of 64, w <= 128, and the inverses of L's
+// diagonal blocks in it.
 template <typename T>
-void panel_rec(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch, int64_t n,
-               int64_t c0, int w, int64_t pk0, int pkb, int32_t *ipiv, int32_t *info) {
-  const int ib = feast::leaf_max_width<T>(n - c0);
-  if (w <= ib) {
-    if (!feast::leaf_lu<T>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ipiv, info))
-      throw HipError{hipErrorInvalidValue, "leaf_lu"};
-    return;
+void panel(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch, int64_t n, int64_t c0,
+           int w, int32_t *ipiv, int32_t *info, T *Linv, int64_t istride) {
+  for (int h = 0; h < w; h += 64) {
+    const int wh = std::min(64, w - h);
+    const int64_t ch = c0 + h;
+    if (h > 0) {  // (the exchanges so far have reached these columns)
+      T *X = M + c0 * ld + ch;
+      gemm_t<T>(s, 0, 64, wh, 64, zc(1.0), Linv + c0 / 64 * 4096, 64, istride, X, ld, stride, zc(0.0),
+                X, ld, stride, batch);
+      gemm_t<T>(s, 0, n - ch, wh, 64, zc(-1.0), M + ch * ld + c0, ld, stride, X, ld, stride, zc(1.0),
+                M + ch * ld + ch, ld, stride, batch);
+    }
+    if (!feast::panel_cols<T>(s, M, ld, stride, batch, n, ch, wh, c0, w, ipiv, info))
+      throw HipError{hipErrorInvalidValue, "panel_cols"};
+    feast::diag_block_inverse<T>(s, M, ld, stride, batch, n, ch / 64, ch / 64 + 1, true, Linv,
+                                 istride);
   }
-  const int w1 = w / 2, w2 = w - w1;
-  panel_rec<T>(s, M, ld, stride, batch, n, c0, w1, pk0, pkb, ipiv, info);
-  if (w2 <= feast::panel_update_max_width()) {
-    feast::panel_update<T>(s, M, ld, stride, batch, n, c0, w1, w2);
-    panel_rec<T>(s, M, ld, stride, batch, n, c0 + w1, w2, pk0, pkb, ipiv, info);
-    return;
-  }
-  feast::trsm_small<T>(s, M, ld, stride, batch, c0, w1, w2);
-  if (c0 + w1 < n)
-    gemm_t<T>(s, 0, n - c0 - w1, w2, w1, zc(-1.0), M + (c0 + w1) * ld + c0, ld, stride,
-              M + c0 * ld + c0 + w1, ld, stride, zc(1.0), M + (c0 + w1) * ld + c0 + w1, ld, stride,
-              batch);
-  panel_rec<T>(s, M, ld, stride, batch, n, c0 + w1, w2, pk0, pkb, ipiv, info);
 }
 
 struct LuProf {
@@ -197,15 +197,13 @@ void lu_batched(const LuStreams &st, T *M, int64_t ld, int64_t stride, int32_t b
     }
   };
   // first panel
-  panel_rec<T>(s, M, ld, stride, batch, n, 0, static_cast<int>(std::min<int64_t>(nb, n)), 0,
-               static_cast<int>(std::min<int64_t>(nb, n)), ipiv, info);
+  panel<T>(s, M, ld, stride, batch, n, 0, static_cast<int>(std::min<int64_t>(nb, n)), ipiv, info,
+           Linv, istride);
   for (int64_t k0 = 0; k0 < n; k0 += nb) {
     const int kb = static_cast<int>(std::min<int64_t>(nb, n - k0));
     const int64_t k1 = k0 + kb, rest = n - k1;
     // the panel [k0, k1) is factored (on `s`, or on the side stream joined below)
     feast::laswp_outside<T>(s, M, ld, stride, batch, n, k0, kb, k0, k1, ipiv);
-    feast::diag_block_inverse<T>(s, M, ld, stride, batch, n, k0 / kIB,
-                                 (k1 + kIB - 1) / kIB, true, Linv, istride);
     if (rest <= 0) break;
     // U12 = L11^{-1} A12
     trsm_lower_rec<T>(s, M, ld, stride, batch, Linv, istride, k0, k1, M + k1, ld, stride, M + k1, ld,
@@ -220,7 +218,7 @@ void lu_batched(const LuStreams &st, T *M, int64_t ld, int64_t stride, int32_t b
       timed_gemm(rest, kb1, kb, M + k1 * ld + k0, M + k0 * ld + k1, M + k1 * ld + k1);
       HIPCHK(hipEventRecord(st.cols_ready, s));
       HIPCHK(hipStreamWaitEvent(st.side, st.cols_ready, 0));
-      panel_rec<T>(st.side, M, ld, stride, batch, n, k1, kb1, k1, kb1, ipiv, info);
+      panel<T>(st.side, M, ld, stride, batch, n, k1, kb1, ipiv, info, Linv, istride);
       HIPCHK(hipEventRecord(st.panel_done, st.side));
       timed_gemm(rest, rest - kb1, kb, M + k1 * ld + k0, M + k0 * ld + k1 + kb1,
                  M + k1 * ld + k1 + kb1, st.upd_wgs);
@@ -239,10 +237,8 @@ void lu_batched(const LuStreams &st, T *M, int64_t ld, int64_t stride, int32_t b
         const int64_t ks = kg, ke = kg + nb;
         timed_gemm(n - ks, static_cast<int>(nb), ks - k0, M + ks * ld + k0, M + k0 * ld + ks,
                    M + ks * ld + ks);
-        panel_rec<T>(s, M, ld, stride, batch, n, ks, nb, ks, nb, ipiv, info);
+        panel<T>(s, M, ld, stride, batch, n, ks, nb, ipiv, info, Linv, istride);
         feast::laswp_outside<T>(s, M, ld, stride, batch, n, ks, nb, ks, ke, ipiv);
-        feast::diag_block_inverse<T>(s, M, ld, stride, batch, n, ks / kIB,
-                                     (ke + kIB - 1) / kIB, true, Linv, istride);
         timed_gemm(nb, n - ke, ks - k0, M + ks * ld + k0, M + k0 * ld + ke, M + ks * ld + ke);
         trsm_lower_rec<T>(s, M, ld, stride, batch, Linv, istride, ks, ke, M + ke, ld, stride,
                           M + ke, ld, stride, n - ke, 0, kIB);
@@ -250,11 +246,11 @@ void lu_batched(const LuStreams &st, T *M, int64_t ld, int64_t stride, int32_t b
       }
       timed_gemm(n - kg, n - kg, kg - k0, M + kg * ld + k0, M + k0 * ld + kg, M + kg * ld + kg);
       const int kbn = static_cast<int>(std::min<int64_t>(nb, n - kg));
-      panel_rec<T>(s, M, ld, stride, batch, n, kg, kbn, kg, kbn, ipiv, info);
+      panel<T>(s, M, ld, stride, batch, n, kg, kbn, ipiv, info, Linv, istride);
       k0 = kg - nb;  // (the loop's step moves on to the panel at kg)
     } else {
       timed_gemm(rest, rest, kb, M + k1 * ld + k0, M + k0 * ld + k1, M + k1 * ld + k1);
-      panel_rec<T>(s, M, ld, stride, batch, n, k1, kb1, k1, kb1, ipiv, info);
+      panel<T>(s, M, ld, stride, batch, n, k1, kb1, ipiv, info, Linv, istride);
     }
   }
   const int64_t nblk = (n + kIB - 1) / kIB;

@@ -174,7 +174,7 @@ template <typename T> __device__ inline T recip_scaled(T a) {
 template <typename T, int NT, int RPT, int IB>
 __global__ __launch_bounds__(NT) void k_leaf(T *__restrict__ Mall, int64_t ld_in, int64_t stride,
                                              int64_t n_in, int64_t c0, int w, int64_t pk0,
-                                             int pkb, int32_t *__restrict__ ipiv_all,
+                                             int pkb, int ue, int32_t *__restrict__ ipiv_all,
                                              int32_t *__restrict__ info_all,
                                              const GrpMat *__restrict__ grp, int nodes) {
   using Tr = cplx_traits<T>;
@@ -197,6 +197,7 @@ __global__ __launch_bounds__(NT) void k_leaf(T *__restrict__ Mall, int64_t ld_in
   __shared__ T s_post[2][16][IB];
   __shared__ T s_crow[2][IB];
   __shared__ int s_pivs[IB];
+  __shared__ T s_l[IB][IB];   // the leaf's rows (L11)
   int info_local = 0;
   // rows of this thread relative to c0: tid + NT q (32-bit: rows < 2^31)
   const int nrel = static_cast<int>(n - c0);
@@ -337,7 +338,10 @@ __global__ __launch_bounds__(NT) void k_leaf(T *__restrict__ Mall, int64_t ld_in
     }
   }
 
-  __syncthreads();  // s_pivs
+  if (ue > 0 && tid < IB)
+#pragma unroll
+    for (int c = 0; c < IB; ++c) s_l[tid][c] = a[0][c];
+  __syncthreads();  // s_pivs, s_l
   if (tid < w) ipiv[c0 + tid] = s_pivs[tid];
   // The leaf's swaps (c0 + c <-> s_pivs[c], in order) applied to the other
   // columns of the panel as one gather.  Destinations: the w leaf rows and
@@ -359,7 +363,7 @@ __global__ __launch_bounds__(NT) void k_leaf(T *__restrict__ Mall, int64_t ld_in
   int dst[H];  // destination row of slot h (uniform), -1: none
 #pragma unroll
   for (int h = 0; h < H; ++h) {
-    const int k = 2 * NT / 256 * h + (wave >> 1);
+    const int k = NT / 128 * h + (wave >> 1);
     v[h] = czero<T>();
     dst[h] = -1;
     if (k < 2 * w) {
@@ -387,7 +391,7 @@ __global__ __launch_bounds__(NT) void k_leaf(T *__restrict__ Mall, int64_t ld_in
             if (src == top) src = pv_[c];
             else if (src == pv_[c]) src = top;
           }
-        if (src != key) {
+        if (src != key || (ue > 0 && k < w)) {
           dst[h] = key;
           if (pin) v[h] = M[static_cast<int64_t>(src) * ld + pcol];
         }
@@ -409,19 +413,63 @@ __global__ __launch_bounds__(NT) void k_leaf(T *__restrict__ Mall, int64_t ld_in
       }
       wave_lds_order();
     }
+  // the leaf's exchanged rows over the panel's columns, through the LDS of the
+  // wavefronts that fetched them: row k's columns are with wavefronts
+  // 2 (k mod NT / 128) and the next one, 64 each
+  constexpr int RW = NT / 128;
+  auto su = [&](int k, int col) -> T & {
+    return (&stg_all[2 * (k % RW) + (col >> 6)][0][0])[(k / RW) * 64 + (col & 63)];
+  };
+  if (ue > 0)
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      const int k = RW * h + (wave >> 1);
+      if (k < w) {
+        su(k, tid & 127) = v[h];
+        dst[h] = -1;  // (stored below)
+      }
+    }
   __syncthreads();  // every source of the exchanges has been read
 #pragma unroll
   for (int h = 0; h < H; ++h)
     if (dst[h] >= 0 && pin) M[static_cast<int64_t>(dst[h]) * ld + pcol] = v[h];
+  // the leaf's rows: U12 = L11^{-1} A12 in the columns up to ue, one column per
+  // thread (the others only exchanged)
+  if (ue > 0 && tid < 128 && pin) {
+    T x[IB];
+#pragma unroll
+    for (int k = 0; k < IB; ++k) x[k] = k < w ? su(k, tid) : czero<T>();
+    if (pcol >= c0 + w && pcol < c0 + w + ue)
+#pragma unroll
+      for (int k = 0; k < IB; ++k)
+#pragma unroll
+        for (int r = k + 1; r < IB; ++r)
+          if (r < w) x[r] = ffms(x[r], s_l[r][k], x[k]);
+#pragma unroll
+    for (int k = 0; k < IB; ++k)
+      if (k < w) M[(c0 + k) * ld + pcol] = x[k];
+  }
   if (tid == 0 && info_local != 0 && info_all[b] == 0) info_all[b] = info_local;
 }
 
+// A panel's exchanges (rows r0 + i <-> ipiv[r0 + i], i < kb <= 128, in order) on
+// the columns outside it, [0, clo) and [chi, n), as one gather: the exchanges
+// reach at most the kb panel rows and kb rows below, and every destination's
+// source is found by walking them backwards (all destinations at once, in LDS).
+// A workgroup moves 512-byte pieces of those rows, every piece read before any is
+// written.  One exchange after the other, each column waited for 128 memory round
+// trips: 58 us a 128-column panel of 16 complex128 matrices of order 1000, 22 us
+// so (124 us for 32 complex64 ones of order 4000, 95 to 107 so, 5 TB/s).
 template <typename T>
 __global__ __launch_bounds__(256) void k_laswp_outside(T *__restrict__ Mall, int64_t ld_in,
                                                        int64_t stride, int64_t n_in, int64_t r0,
                                                        int kb, int64_t clo, int64_t chi,
                                                        const int32_t *__restrict__ ipiv_all,
                                                        const GrpMat *__restrict__ grp, int nodes) {
+  constexpr int CT = 512 / sizeof(T), G = 256 / CT;  // columns of a piece, rows at a time
+  __shared__ int2 s_x[128];  // the exchanges that move rows: panel row, its partner
+  __shared__ int s_dst[256], s_src[256];
+  __shared__ int s_cnt[4];
   const int b = blockIdx.y;
   const MatRef<T> mr = mat_of<T>(grp, nodes, Mall, ld_in, stride, n_in, b);
   T *M = mr.M;
@@ -429,157 +477,133 @@ __global__ __launch_bounds__(256) void k_laswp_outside(T *__restrict__ Mall, int
   // (grouped: a panel wider than what is left of a smaller matrix is clipped
   // to its last row and column; a matrix already factored has nothing to swap)
   const int kbe = static_cast<int>(r0 + kb <= n ? kb : n - r0);
-  if (kbe <= 0) return;
-  const int64_t chie = chi < n ? chi : n;
-  const int32_t *ipiv = ipiv_all + b * n_in;
-  const int64_t t = blockIdx.x * 256ll + threadIdx.x;
-  const int64_t ncols = clo + (n - chie);
-  if (t >= ncols) return;
-  const int64_t col = (t < clo) ? t : chie + (t - clo);
-  for (int i = 0; i < kbe; ++i) {
-    const int64_t r = r0 + i, p = ipiv[r];
-    if (p != r) {
-      const T x = M[r * ld + col];
-      M[r * ld + col] = M[p * ld + col];
-      M[p * ld + col] = x;
-    }
-  }
-}
-
-// X = L11^{-1} X with L11 unit lower (w1 x w1), X (w1 x w2), w1, w2 <= 64, both
-// inside the matrix; one workgroup of 256 threads per matrix, X in registers
-// (the layout of k_diag_inv), forward substitution with one barrier per row.
-template <typename T>
-__global__ __launch_bounds__(256) void k_trsm_small(T *__restrict__ Mall, int64_t ld,
-                                                    int64_t stride, int64_t c0, int w1, int w2) {
-  using Tr = cplx_traits<T>;
-  __shared__ T sL[64][65];
-  __shared__ T rowb[2][4][64];
-  T *M = Mall + blockIdx.x * stride;
-  const int tid = threadIdx.x, ti = tid >> 4, tj = tid & 15;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  for (int e = tid; e < 64 * 64; e += 256) {
-    const int i = e >> 6, j = e & 63;
-    sL[i][j] = (i < w1 && j < w1) ? M[(c0 + i) * ld + c0 + j] : czero<T>();
-  }
-  T x[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int i = ti + 16 * a, j = tj + 16 * c;
-      x[a][c] = (i < w1 && j < w2) ? M[(c0 + i) * ld + c0 + w1 + j] : czero<T>();
-    }
-  for (int i = 0; i + 1 < w1; ++i) {
-    if (ti == (i & 15))  // the owners of row i publish it (all four row blocks)
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) rowb[i & 1][a][tj + 16 * c] = x[a][c];
+  const int64_t chie = chi < n ? chi : n, ncols = clo + (n - chie);
+  if (kbe <= 0 || static_cast<int64_t>(blockIdx.x) * CT >= ncols) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // position of this thread among those with `on`, and their number
+  auto rank_of = [&](bool on, int &count) {
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(on);
+    if (lane == 0) s_cnt[wave] = __builtin_popcountll(mask);
     __syncthreads();
-    T la[4], xb[4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a) la[a] = sL[ti + 16 * a][i];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) xb[c] = rowb[i & 1][i >> 4][tj + 16 * c];
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      if (16 * a + 4 * wv + 3 <= i) continue;
-      const T l = (ti + 16 * a > i) ? la[a] : czero<T>();  // rows r > i only
-#pragma unroll
-      for (int c = 0; c < 4; ++c) x[a][c] = Tr::fms(x[a][c], l, xb[c]);
-    }
+    int at = __builtin_popcountll(mask & ((1ull << lane) - 1));
+    for (int w = 0; w < wave; ++w) at += s_cnt[w];
+    count = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
+    __syncthreads();
+    return at;
+  };
+  const int p = tid < kbe ? ipiv_all[b * n_in + r0 + tid] - static_cast<int>(r0) : tid;
+  int nx, cnt;
+  const int xat = rank_of(tid < kbe && p != tid, nx);
+  if (nx == 0) return;
+  if (tid < kbe && p != tid) s_x[xat] = make_int2(tid, p);
+  __syncthreads();
+  // destination (relative to r0): panel row tid, or the partner of exchange
+  // tid - 128 if it lies below the panel and no earlier exchange names it
+  int key = -1;
+  if (tid < 128) key = tid < kbe ? tid : -1;
+  else if (tid - 128 < nx && s_x[tid - 128].y >= kbe) key = s_x[tid - 128].y;
+  int src = key, first = 0;  // first: the lowest exchange that names key
+#pragma unroll 4
+  for (int i = nx - 1; i >= 0; --i) {
+    const int2 x = s_x[i];
+    first = x.y == key ? i : first;
+    src = src == x.x ? x.y : (src == x.y ? x.x : src);
   }
+  const bool moved = key >= 0 && src != key && (tid < 128 || first == tid - 128);
+  const int at = rank_of(moved, cnt);
+  if (moved) {
+    s_dst[at] = key;
+    s_src[at] = src;
+  }
+  __syncthreads();
+  const int g = tid / CT;
+  for (int64_t c0 = static_cast<int64_t>(blockIdx.x) * CT; c0 < ncols;
+       c0 += static_cast<int64_t>(gridDim.x) * CT) {
+    const int64_t t = c0 + tid % CT;
+    const bool in = t < ncols;
+    T *C = M + r0 * ld + (!in ? 0 : t < clo ? t : chie + (t - clo));
+    T v[CT];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int i = ti + 16 * a, j = tj + 16 * c;
-      if (i >= 1 && i < w1 && j < w2) M[(c0 + i) * ld + c0 + w1 + j] = x[a][c];
+    for (int e = 0; e < CT; ++e) {
+      v[e] = czero<T>();
+      if (in && G * e + g < cnt) v[e] = C[s_src[G * e + g] * ld];
     }
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): every piece has arrived
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < CT; ++e)
+      if (in && G * e + g < cnt) C[s_dst[G * e + g] * ld] = v[e];
+  }
 }
 
-// One recursion step of the panel factorisation for w1, w2 <= 32:
+// Joins of the panel factorisation:
 //   X = L11^{-1} X      for X = M[c0:c0+w1, c0+w1:c0+w1+w2], L11 unit lower (w1 x w1),
-//   C -= L21 X          for C = M[c0+w1:n, c0+w1:c0+w1+w2], L21 = M[c0+w1:n, c0:c0+w1].
-// The update is a rank-w1 product with w1 <= 32: it is bound by the traffic of
-// C, so it runs on the VALU.
+//   C -= L21 X          for C = M[c0+w1:n, c0+w1:c0+w1+w2], L21 = M[c0+w1:n, c0:c0+w1],
+// w1 <= 32, in two launches: the small solve once per matrix (k_panel_solve, w2
+// <= 32; a leaf that has solved its own rows needs none), then the update by every
+// 64-row chunk and 32-column block (k_panel_rank, reading the solved X).  (In one
+// launch every chunk would repeat the solve.)  The update is a product with
+// w1 <= 32: bound by the traffic of C, so it runs on the VALU.
 constexpr int kPU = 32;
-// The small triangular solve of one matrix by one workgroup: L11 and X staged
-// in LDS, forward substitution with eight lanes per column sharing each inner
-// product, rows 1.. of the solved X stored back.
-template <typename T>
-__device__ void panel_solve_body(T *__restrict__ M, int64_t ld, int64_t c0, int w1, int w2,
-                                 T (*sL)[kPU + 1], T (*sX)[kPU + 1]) {
-  using Tr = cplx_traits<T>;
-  const int tid = threadIdx.x;
-  for (int e = tid; e < w1 * w1; e += 256) {
-    const int i = e / w1, k = e % w1;
-    sL[i][k] = M[(c0 + i) * ld + c0 + k];
-  }
-  for (int e = tid; e < w1 * w2; e += 256) {
-    const int i = e / w2, j = e % w2;
-    sX[i][j] = M[(c0 + i) * ld + c0 + w1 + j];
-  }
-  __syncthreads();
-  {
-    // forward substitution: column j = tid / 8, lanes q = tid % 8 split the sum
-    const int j = tid >> 3, q = tid & 7;
-    for (int i = 1; i < w1; ++i) {
-      T part = Tr::make(0.0, 0.0);
-      if (j < w2)
-        for (int k = q; k < i; k += 8) part = Tr::fms(part, sL[i][k], sX[k][j]);
-#pragma unroll
-      for (int off = 1; off < 8; off <<= 1) {
-        part.x += __shfl_xor(part.x, off);
-        part.y += __shfl_xor(part.y, off);
-      }
-      if (q == 0 && j < w2) {
-        T x = sX[i][j];
-        x.x += part.x;
-        x.y += part.y;
-        sX[i][j] = x;
-      }
-      // the eight lanes of a column are in one wavefront: order its LDS accesses
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    }
-  }
-  __syncthreads();
-  for (int e = tid; e < w1 * w2; e += 256) {
-    const int i = e / w2, j = e % w2;
-    if (i > 0) M[(c0 + i) * ld + c0 + w1 + j] = sX[i][j];
-  }
-}
-
-// The panel update in two launches: the small triangular solve once per
-// matrix (k_panel_solve: X = L11^{-1} X written back), then the rank-w1 update
-// of the rows below by every 64-row chunk (k_panel_rank, reading the solved X).
-// (Fusing both into one launch makes every chunk repeat the solve, a chain of
-// up to 31 dependent LDS steps that then dominates the launch: measured slower.)
+// One workgroup per matrix: L11's inverse by halves (tri64.h), then the product
+// on the matrix cores, one 16 x 16 tile per wavefront.  (32 x 32, 16 complex128
+// matrices: 13 us a launch by substitution, 9 so.)
 template <typename T>
 __global__ __launch_bounds__(256) void k_panel_solve(T *__restrict__ Mall, int64_t ld_in,
                                                      int64_t stride, int64_t n_in, int64_t c0,
                                                      int w1, int w2,
                                                      const GrpMat *__restrict__ grp, int nodes) {
-  __shared__ T sL[64][kPU + 1];
-  __shared__ T sX[kPU][kPU + 1];
+  __shared__ T sL[kPU][kTP];
+  __shared__ T sX[kPU][kTP];
   const MatRef<T> mr = mat_of<T>(grp, nodes, Mall, ld_in, stride, n_in, blockIdx.x);
   if (c0 + w1 + w2 > mr.n) return;
-  panel_solve_body<T>(mr.M, mr.ld, c0, w1, w2, sL, sX);
+  const int64_t ld = mr.ld;
+  T *D = mr.M + c0 * (ld + 1);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  T v[4], x[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int i = (tid >> 5) + 8 * k, j = tid & 31;
+    v[k] = (i < w1 && j < w1) ? D[i * ld + j] : czero<T>();
+    x[k] = (i < w1 && j < w2) ? D[i * ld + w1 + j] : czero<T>();
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    sL[(tid >> 5) + 8 * k][tid & 31] = v[k];
+    sX[(tid >> 5) + 8 * k][tid & 31] = x[k];
+  }
+  __syncthreads();
+  if (wave < 2) wave_tri16(sL, 16 * wave, true, lane);
+  __syncthreads();
+  tri_join<T, 16, 32>(sL, lane, wave);
+  const int ti = 16 * (wave >> 1), tj = 16 * (wave & 1);
+  Tile16<T> t;
+  t.template mac<false>(sL, ti, 0, sX, 0, tj, (ti + 16) / 4, lane);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int i = ti + mfma_ops<T>::out_row(lane, r), j = tj + (lane & 15);
+    T o;
+    o.x = t.re[r];
+    o.y = t.im[r];
+    if (i < w1 && j < w2) D[i * ld + w1 + j] = o;
+  }
 }
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_panel_rank(T *__restrict__ Mall, int64_t ld_in,
                                                     int64_t stride, int64_t n_in, int64_t c0,
-                                                    int w1, int w2,
+                                                    int w1, int w2all,
                                                     const GrpMat *__restrict__ grp, int nodes) {
   using Tr = cplx_traits<T>;
   __shared__ T sL[64][kPU + 1];
   __shared__ T sX[kPU][kPU + 1];
   const MatRef<T> mr = mat_of<T>(grp, nodes, Mall, ld_in, stride, n_in, blockIdx.y);
-  T *M = mr.M;
   const int64_t ld = mr.ld, n = mr.n;
-  if (c0 + w1 + w2 > n) return;
+  if (c0 + w1 + w2all > n) return;
+  T *M = mr.M + kPU * static_cast<int64_t>(blockIdx.z);  // (column block: M's columns past w1)
+  const int w2 = w2all - kPU * static_cast<int>(blockIdx.z) < kPU ? w2all - kPU * static_cast<int>(blockIdx.z) : kPU;
+  const T *L = mr.M;
   const int64_t r0 = c0 + w1 + static_cast<int64_t>(blockIdx.x) * 64;
   if (r0 >= n) return;  // (a chunk beyond a smaller matrix of a grouped launch)
   const int rows = static_cast<int>((n - r0 < 64) ? n - r0 : 64);
@@ -590,7 +614,7 @@ __global__ __launch_bounds__(256) void k_panel_rank(T *__restrict__ Mall, int64_
   }
   for (int e = tid; e < rows * w1; e += 256) {
     const int i = e / w1, k = e % w1;
-    sL[i][k] = M[(r0 + i) * ld + c0 + k];
+    sL[i][k] = L[(r0 + i) * ld + c0 + k];
   }
   const int ti = tid >> 4, tj = tid & 15;
   T acc[4][2];
@@ -611,7 +635,7 @@ __global__ __launch_bounds__(256) void k_panel_rank(T *__restrict__ Mall, int64_
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
-      for (int b = 0; b < 2; ++b) acc[a][b] = Tr::fms(acc[a][b], l[a], x[b]);
+      for (int b = 0; b < 2; ++b) acc[a][b] = ffms(acc[a][b], l[a], x[b]);
   }
 #pragma unroll
   for (int a = 0; a < 4; ++a)
@@ -866,10 +890,10 @@ __global__ void k_fill_i32(int32_t *p, int64_t count, int32_t v) {
 
 template <typename T, int RPT, int IB, int NT = 1024>
 void launch_leaf(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch, int64_t n,
-                 int64_t c0, int w, int64_t pk0, int pkb, int32_t *ipiv, int32_t *info,
+                 int64_t c0, int w, int64_t pk0, int pkb, int ue, int32_t *ipiv, int32_t *info,
                  const GrpMat *grp, int nodes) {
   hipLaunchKernelGGL((k_leaf<T, NT, RPT, IB>), dim3(batch), dim3(NT), 0, s, M, ld, stride, n, c0, w,
-                     pk0, pkb, ipiv, info, grp, nodes);
+                     pk0, pkb, ue, ipiv, info, grp, nodes);
 }
 
 }  // namespace
@@ -890,7 +914,7 @@ template <> int leaf_max_width<c64>(int64_t rows) {
 
 template <>
 bool leaf_lu<z64>(hipStream_t s, z64 *M, int64_t ld, int64_t stride, int32_t batch, int64_t n,
-                  int64_t c0, int w, int64_t pk0, int pkb, int32_t *ipiv, int32_t *info,
+                  int64_t c0, int w, int64_t pk0, int pkb, int ue, int32_t *ipiv, int32_t *info,
                   const GrpMat *grp, int nodes) {
   const int64_t rows = n - c0;
   if (w < 1 || w > leaf_max_width<z64>(rows) || pkb > 128) return false;
@@ -899,38 +923,38 @@ bool leaf_lu<z64>(hipStream_t s, z64 *M, int64_t ld, int64_t stride, int32_t bat
   // against 19.8 with 256 and 20.4 with 1024 threads, 2000 rows 24.6 against 25.6
   // with 1024)
   if (rows <= 256)
-    launch_leaf<z64, 1, 8, 256>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ipiv, info, grp, nodes);
+    launch_leaf<z64, 1, 8, 256>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ue, ipiv, info, grp, nodes);
   else if (rows <= 512)
-    launch_leaf<z64, 1, 8, 512>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ipiv, info, grp, nodes);
+    launch_leaf<z64, 1, 8, 512>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ue, ipiv, info, grp, nodes);
   else if (rows <= 1024)
-    launch_leaf<z64, 2, 8, 512>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ipiv, info, grp, nodes);
+    launch_leaf<z64, 2, 8, 512>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ue, ipiv, info, grp, nodes);
   else if (rows <= 2048)
-    launch_leaf<z64, 4, 8, 512>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ipiv, info, grp, nodes);
+    launch_leaf<z64, 4, 8, 512>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ue, ipiv, info, grp, nodes);
   else if (rows <= 4096)
-    launch_leaf<z64, 4, 4>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ipiv, info, grp, nodes);
+    launch_leaf<z64, 4, 4>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ue, ipiv, info, grp, nodes);
   else if (rows <= 8192)
-    launch_leaf<z64, 8, 2>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ipiv, info, grp, nodes);
+    launch_leaf<z64, 8, 2>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ue, ipiv, info, grp, nodes);
   else
-    launch_leaf<z64, 16, 1>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ipiv, info, grp, nodes);
+    launch_leaf<z64, 16, 1>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ue, ipiv, info, grp, nodes);
   return true;
 }
 
 template <>
 bool leaf_lu<c64>(hipStream_t s, c64 *M, int64_t ld, int64_t stride, int32_t batch, int64_t n,
-                  int64_t c0, int w, int64_t pk0, int pkb, int32_t *ipiv, int32_t *info,
+                  int64_t c0, int w, int64_t pk0, int pkb, int ue, int32_t *ipiv, int32_t *info,
                   const GrpMat *grp, int nodes) {
   const int64_t rows = n - c0;
   if (w < 1 || w > leaf_max_width<c64>(rows) || pkb > 128) return false;
   if (rows <= 1024)
-    launch_leaf<c64, 1, 8>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ipiv, info, grp, nodes);
+    launch_leaf<c64, 1, 8>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ue, ipiv, info, grp, nodes);
   else if (rows <= 2048)
-    launch_leaf<c64, 2, 8>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ipiv, info, grp, nodes);
+    launch_leaf<c64, 2, 8>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ue, ipiv, info, grp, nodes);
   else if (rows <= 4096)
-    launch_leaf<c64, 4, 8>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ipiv, info, grp, nodes);
+    launch_leaf<c64, 4, 8>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ue, ipiv, info, grp, nodes);
   else if (rows <= 8192)
-    launch_leaf<c64, 8, 4>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ipiv, info, grp, nodes);
+    launch_leaf<c64, 8, 4>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ue, ipiv, info, grp, nodes);
   else
-    launch_leaf<c64, 16, 2>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ipiv, info, grp, nodes);
+    launch_leaf<c64, 16, 2>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ue, ipiv, info, grp, nodes);
   return true;
 }
 
@@ -941,22 +965,17 @@ void laswp_outside(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batc
   // (n: the largest order of a grouped launch; every matrix has at most this many columns)
   const int64_t ncols = clo + (n > chi ? n - chi : 0);
   if (ncols <= 0 || kb <= 0) return;
-  hipLaunchKernelGGL((k_laswp_outside<T>), dim3(static_cast<unsigned>((ncols + 255) / 256), batch),
+  // one piece a workgroup while the chip has room for all, else several: finding
+  // the sources costs a workgroup about as much as a piece
+  constexpr int64_t ct = 512 / sizeof(T);
+  const int64_t pieces = std::min<int64_t>((ncols + ct - 1) / ct, std::max<int64_t>(1, 1024 / batch));
+  hipLaunchKernelGGL((k_laswp_outside<T>), dim3(static_cast<unsigned>(pieces), batch),
                      dim3(256), 0, s, M, ld, stride, n, r0, kb, clo, chi, ipiv, grp, nodes);
 }
 template void laswp_outside<z64>(hipStream_t, z64 *, int64_t, int64_t, int32_t, int64_t, int64_t,
                                  int, int64_t, int64_t, const int32_t *, const GrpMat *, int);
 template void laswp_outside<c64>(hipStream_t, c64 *, int64_t, int64_t, int32_t, int64_t, int64_t,
                                  int, int64_t, int64_t, const int32_t *, const GrpMat *, int);
-
-template <typename T>
-void trsm_small(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch, int64_t c0,
-                int w1, int w2) {
-  if (w1 <= 1 || w2 <= 0) return;
-  hipLaunchKernelGGL((k_trsm_small<T>), dim3(batch), dim3(256), 0, s, M, ld, stride, c0, w1, w2);
-}
-template void trsm_small<z64>(hipStream_t, z64 *, int64_t, int64_t, int32_t, int64_t, int, int);
-template void trsm_small<c64>(hipStream_t, c64 *, int64_t, int64_t, int32_t, int64_t, int, int);
 
 template <> int lu_small_max_order<z64>() { return 64; }
 template <> int lu_small_max_order<c64>() { return 128; }
@@ -974,21 +993,61 @@ template void lu_small<z64>(hipStream_t, const GrpMat *, int, int, int64_t, int3
 template void lu_small<c64>(hipStream_t, const GrpMat *, int, int, int64_t, int32_t *, int32_t *);
 
 template <typename T>
+void panel_rank(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch, int64_t n,
+                int64_t c0, int w1, int w2, const GrpMat *grp, int nodes) {
+  const int64_t rows = n - c0 - w1;
+  if (w1 <= 0 || w2 <= 0 || w1 > kPU || batch <= 0 || rows <= 0) return;
+  hipLaunchKernelGGL((k_panel_rank<T>),
+                     dim3(static_cast<unsigned>((rows + 63) / 64), batch, (w2 + kPU - 1) / kPU),
+                     dim3(256), 0, s, M, ld, stride, n, c0, w1, w2, grp, nodes);
+}
+template <typename T>
 void panel_update(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch, int64_t n,
                   int64_t c0, int w1, int w2, const GrpMat *grp, int nodes) {
   if (w1 <= 0 || w2 <= 0 || w1 > kPU || w2 > kPU || batch <= 0) return;
-  const int64_t rows = n - c0 - w1;
   hipLaunchKernelGGL((k_panel_solve<T>), dim3(batch), dim3(256), 0, s, M, ld, stride, n, c0, w1, w2,
                      grp, nodes);
-  if (rows > 0)
-    hipLaunchKernelGGL((k_panel_rank<T>), dim3(static_cast<unsigned>((rows + 63) / 64), batch),
-                       dim3(256), 0, s, M, ld, stride, n, c0, w1, w2, grp, nodes);
+  panel_rank<T>(s, M, ld, stride, batch, n, c0, w1, w2, grp, nodes);
 }
-template void panel_update<z64>(hipStream_t, z64 *, int64_t, int64_t, int32_t, int64_t, int64_t,
-                                int, int, const GrpMat *, int);
-template void panel_update<c64>(hipStream_t, c64 *, int64_t, int64_t, int32_t, int64_t, int64_t,
-                                int, int, const GrpMat *, int);
 int panel_update_max_width() { return kPU; }
+
+// Columns [c0, c0 + w), w <= 64, of each matrix: leaves of eight columns, each
+// of which solves its own rows over the rest of a block of `bw` columns and is
+// followed by the update of that block's rows below (eight columns deep);
+// blocks of 32 are joined by panel_update.  A block of 64 saves that join's two
+// launches (about 18 us) and passes over the block's rows 28 times eight columns
+// instead of 17: it is taken while a pass over all matrices' rows moves less
+// than 8 MB.  Above 8-column leaves' row limit: recursion down to the leaves.
+template <typename T>
+bool panel_cols(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch, int64_t n,
+                int64_t c0, int w, int64_t pk0, int pkb, int32_t *ipiv, int32_t *info,
+                const GrpMat *grp, int nodes) {
+  const int ib = leaf_max_width<T>(n - c0);
+  if (w <= ib) return leaf_lu<T>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, 0, ipiv, info, grp, nodes);
+  if (ib < 8) {
+    const int w1 = w / 2, w2 = w - w1;
+    if (w > 2 * kPU || !panel_cols<T>(s, M, ld, stride, batch, n, c0, w1, pk0, pkb, ipiv, info, grp, nodes))
+      return false;
+    panel_update<T>(s, M, ld, stride, batch, n, c0, w1, w2, grp, nodes);
+    return panel_cols<T>(s, M, ld, stride, batch, n, c0 + w1, w2, pk0, pkb, ipiv, info, grp, nodes);
+  }
+  const int bw = batch * (n - c0) * static_cast<int64_t>(sizeof(T)) <= (512 << 10) ? 64 : kPU;
+  for (int b0 = 0; b0 < w; b0 += bw) {
+    const int be = b0 + bw < w ? b0 + bw : w;
+    for (int l0 = b0; l0 < be; l0 += 8) {
+      const int lw = be - l0 < 8 ? be - l0 : 8, rest = be - l0 - lw;
+      if (!leaf_lu<T>(s, M, ld, stride, batch, n, c0 + l0, lw, pk0, pkb, rest, ipiv, info, grp, nodes))
+        return false;
+      panel_rank<T>(s, M, ld, stride, batch, n, c0 + l0, lw, rest, grp, nodes);
+    }
+    if (be < w) panel_update<T>(s, M, ld, stride, batch, n, c0 + b0, be - b0, w - be, grp, nodes);
+  }
+  return true;
+}
+template bool panel_cols<z64>(hipStream_t, z64 *, int64_t, int64_t, int32_t, int64_t, int64_t, int,
+                              int64_t, int, int32_t *, int32_t *, const GrpMat *, int);
+template bool panel_cols<c64>(hipStream_t, c64 *, int64_t, int64_t, int32_t, int64_t, int64_t, int,
+                              int64_t, int, int32_t *, int32_t *, const GrpMat *, int);
 
 template <typename T>
 void diag_block_inverse(hipStream_t s, const T *M, int64_t ld, int64_t stride, int32_t batch,

@@ -95,11 +95,17 @@ void gemm_group(hipStream_t s, int ta, bool sub, const GemmArgs<T> *dtab, int co
 // launch.
 
 // Factor columns [c0, c0+w) (rows [c0, n)) of each matrix with partial pivoting,
-// swapping rows over the panel columns [pk0, pk0+pkb) as well.  Returns false
-// if w is larger than the register-resident leaf supports for n - c0 rows.
+// w <= 64, swapping rows over the panel columns [pk0, pk0+pkb), pkb <= 128, as
+// well.  Returns false if w is larger than that.
+template <typename T>
+bool panel_cols(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch, int64_t n,
+                int64_t c0, int w, int64_t pk0, int pkb, int32_t *ipiv, int32_t *info,
+                const GrpMat *grp = nullptr, int nodes = 1);
+// Its leaves: w at most leaf_max_width (false otherwise); the rows [c0, c0+w) of
+// the next ue columns are solved with the leaf's unit-lower block.
 template <typename T>
 bool leaf_lu(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch, int64_t n,
-             int64_t c0, int w, int64_t pk0, int pkb, int32_t *ipiv, int32_t *info,
+             int64_t c0, int w, int64_t pk0, int pkb, int ue, int32_t *ipiv, int32_t *info,
              const GrpMat *grp = nullptr, int nodes = 1);
 // Largest leaf width for `rows` remaining rows.
 template <typename T> int leaf_max_width(int64_t rows);
@@ -119,18 +125,17 @@ void laswp_outside(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batc
                    int64_t r0, int kb, int64_t clo, int64_t chi, const int32_t *ipiv,
                    const GrpMat *grp = nullptr, int nodes = 1);
 
-// X <- L11^{-1} X for the unit-lower L11 = M[c0:c0+w1, c0:c0+w1] and
-// X = M[c0:c0+w1, c0+w1:c0+w1+w2] (w1, w2 <= 64).
-template <typename T>
-void trsm_small(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch, int64_t c0,
-                int w1, int w2);
-
-// Both halves of one panel recursion step (w1, w2 <= panel_update_max_width()):
-// X = L11^{-1} X as in trsm_small (one workgroup per matrix), then
-// M[c0+w1:n, c0+w1:c0+w1+w2] -= M[c0+w1:n, c0:c0+w1] X (64-row chunks).
+// Joins of the panel (w1, w2 <= panel_update_max_width()):
+//   X = L11^{-1} X for the unit-lower L11 = M[c0:c0+w1, c0:c0+w1] and
+//   X = M[c0:c0+w1, c0+w1:c0+w1+w2] (one workgroup per matrix), then
+//   M[c0+w1:n, c0+w1:c0+w1+w2] -= M[c0+w1:n, c0:c0+w1] X (64-row chunks).
+// panel_rank: the second alone (any w2).
 template <typename T>
 void panel_update(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch, int64_t n,
                   int64_t c0, int w1, int w2, const GrpMat *grp = nullptr, int nodes = 1);
+template <typename T>
+void panel_rank(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch, int64_t n,
+                int64_t c0, int w1, int w2, const GrpMat *grp = nullptr, int nodes = 1);
 int panel_update_max_width();
 
 // Inverses of the diagonal blocks of the unit-lower L (lower=true) or of the

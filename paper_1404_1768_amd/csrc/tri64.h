@@ -117,10 +117,11 @@ template <typename T> __device__ void wave_tri16(T (*S)[kTP], int o, bool unit, 
 }
 
 // In place: [I1 0; C I2] -> [I1 0; -(I2 C) I1  I2] with diagonal blocks of H rows
-// already inverted, for the 64 / (2 H) blocks of S; 256 threads, barriers inside.
-template <typename T, int H> __device__ void tri_join(T (*S)[kTP], int lane, int wave) {
+// already inverted, for the R / (2 H) blocks of the R rows of S; 256 threads,
+// barriers inside.
+template <typename T, int H, int R = 64> __device__ void tri_join(T (*S)[kTP], int lane, int wave) {
   constexpr int HT = H / 16, TILES = HT * HT;  // tiles of a C block
-  const bool on = wave < TILES * (64 / (2 * H));
+  const bool on = wave < TILES * (R / (2 * H));
   const int o = 2 * H * (wave / TILES), ti = 16 * (wave % TILES / HT), tj = 16 * (wave % TILES % HT);
   Tile16<T> p;
   if (on)  // I2 C: columns k < ti + 16 of I2 only

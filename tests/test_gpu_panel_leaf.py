@@ -63,3 +63,25 @@ def test_zero_columns_are_reported_and_leave_the_rest_finite():
     F, piv, info = factor(M)
     assert list(info) == [1, 131]
     assert np.all(np.isfinite(F)) and int(piv[0, 0]) == 0
+
+
+@pytest.mark.parametrize("n,nb", [(40, 0), (129, 0), (300, 64), (700, 0)])
+@pytest.mark.parametrize("kind", ["none", "reverse", "cycle", "pairs"])
+def test_exchanges_follow_a_planted_permutation(n, nb, kind):
+    # rows of a diagonally dominant matrix in a known order: the pivots restore
+    # it, whether a panel has no exchange, one chain through all rows, or many
+    rng = np.random.default_rng(n)
+    D = 0.01 * (rng.normal(size=(n, n)) + 1j * rng.normal(size=(n, n))) / np.sqrt(n) + np.eye(n)
+    order = {"none": np.arange(n), "reverse": np.arange(n)[::-1],
+             "cycle": np.roll(np.arange(n), 1), "pairs": np.arange(n) ^ 1}[kind].copy()
+    if kind == "pairs" and n % 2:
+        order[-1] = n - 1
+    M = D[order]
+    tM = torch.from_numpy(M[None].copy()).to(DEV)
+    piv, info = fm.zgetrf_batched(tM, nb=nb)
+    F, piv = tM.cpu().numpy()[0], piv.cpu().numpy()[0]
+    rows = order.copy()
+    for i, p in enumerate(piv):
+        rows[[i, p]] = rows[[p, i]]
+    assert int(info[0]) == 0 and np.array_equal(rows, np.arange(n))
+    assert backward_error(M, F, piv) < 1e-14 * n
