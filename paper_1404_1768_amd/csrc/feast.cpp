@@ -548,8 +548,9 @@ int filter_rhs(feast_plan *p, const z64 *A, int64_t lda, const z64 *B, int64_t l
   return st;
 }
 
-// Cholesky G = R^* R of a t x t Hermitian matrix (upper triangle used, R
-// written over it) and X = R^{-1}, blocked by 64 columns: one kernel factors a
+// Cholesky G = R^* R of a t x t Hermitian matrix (upper triangle used, R's
+// written over it) and the upper triangle of X = R^{-1} (X's 64 x 64 blocks below
+// the diagonal ones are left alone), blocked by 64 columns: one kernel factors a
 // diagonal block and inverts it (the inverse goes to X's diagonal block), then
 // R_J,rest = R_JJ^{-*} G_J,rest and G_rest -= R_J,rest^* R_J,rest as MFMA GEMMs;
 // X's off-diagonal blocks follow by X12 = -X11 R12 X22, halving recursively.
@@ -578,17 +579,19 @@ void chol_inv_blocked(feast_plan *p, z64 *G, int64_t t, double shift_rel, int32_
     gemm_t<z64>(s, 2, rest, rest, jb, zc(-1.0), GJ + jb, t, 0, GJ + jb, t, 0, zc(1.0),
                 G + (J0 + jb) * t + J0 + jb, t, 0, 1);
   }
-  if (t > 64) {
-    feast::zero_lower(s, G, t, false);
-    feast::zero_lower(s, X, t, false);
-    inv_upper_rec(s, G, t, X, T, 0, t);
-  }
+  if (t > 64) inv_upper_rec(s, G, t, X, T, 0, t);
 }
 
-// Shifted Cholesky QR3 (three Cholesky QR passes, the first on X^*X + s I with
-// s = 11 (n m + m (m+1)) u ||X||_F^2): an FP64 orthonormalisation that stays
+// Shifted Cholesky QR (up to three Cholesky QR passes, the first on X^*X + s I
+// with s = 11 (n m + m (m+1)) u ||X||_F^2): an FP64 orthonormalisation that stays
 // stable for condition numbers up to about 1/u, built from the Gram GEMM,
 // a blocked t x t Cholesky, a blocked triangular inverse and one more GEMM per pass.
+// A pass leaves the columns orthonormal to about u kappa^2, kappa the condition
+// number of what it is given.  The second pass's Gram matrix tells kappa: within
+// kNearOrthonormal of the identity (kappa^2 < 1.23) the second pass is as good as a
+// third would be, and the third is skipped (every block of condition number up to
+// about 1e4, the shift's reach).
+constexpr double kNearOrthonormal = 0.1;  // ||X^* X - I||_F
 }  // namespace
 
 // Helpers shared with the batched driver (declared in plan.h).
@@ -666,16 +669,29 @@ void orth(feast_plan *p, z64 *X, int64_t ldx, int flag_slot, int64_t cols) {
   hipStream_t s = p->s;
   z64 *G = p->gblk(feast_plan::G_GRAM);
   z64 *Ri = p->gblk(feast_plan::G_RINV), *T = p->gblk(feast_plan::G_T);
-  z64 *Wt = p->wblk(feast_plan::W_ORTH);
   int32_t *flag = p->flag.as<int32_t>() + flag_slot;
   const double shift_rel = 11.0 * (static_cast<double>(n) * m + static_cast<double>(m) * (m + 1)) * kU64;
+  feast::zero_lower(s, Ri, m, false);
+  // X and a work block in turn
+  z64 *src = X, *dst = p->wblk(feast_plan::W_ORTH);
+  int64_t lds = ldx, ldd = m;
   for (int pass = 0; pass < 3; ++pass) {
-    gemm_t<z64>(s, 2, m, m, n, zc(1.0), X, ldx, 0, X, ldx, 0, zc(0.0), G, m, 0, 1,
+    gemm_t<z64>(s, 2, m, m, n, zc(1.0), src, lds, 0, src, lds, 0, zc(0.0), G, m, 0, 1,
                 p->splitws.as<z64>(), splitws_elems(p));
+    if (pass == 1) {  // (read below, once the rest of the pass is enqueued)
+      feast::dev_identity(s, G, m, p->hdev);
+      HIPCHK(hipEventRecord(p->ev_orth, s));
+    }
     chol_inv_blocked(p, G, m, pass == 0 ? shift_rel : 0.0, flag + pass, Ri, T);
-    gemm_t<z64>(s, 0, n, m, m, zc(1.0), X, ldx, 0, Ri, m, 0, zc(0.0), Wt, m, 0, 1);
-    feast::copy_block_z(s, Wt, m, n, m, X, ldx);
+    gemm_t<z64>(s, 0, n, m, m, zc(1.0), src, lds, 0, Ri, m, 0, zc(0.0), dst, ldd, 0, 1);
+    std::swap(src, dst);
+    std::swap(lds, ldd);
+    if (pass == 1) {
+      HIPCHK(hipEventSynchronize(p->ev_orth));
+      if (p->hrn[3] <= kNearOrthonormal * kNearOrthonormal) break;  // (a NaN goes on)
+    }
   }
+  if (src != X) feast::copy_block_z(s, src, lds, n, m, X, ldx);
 }
 
 // Algorithm 5's QR steps and reduced pencil: U -> U_1, A U_1, B U_1, U_2, At, Bt (device m x m).
@@ -855,6 +871,9 @@ int feast_plan_create(feast_plan **plan, int64_t n, int64_t m, const feast_conto
     HIPCHK(hipMemcpy(p->dwc.p, wc.data(), sizeof(z64) * p->N, hipMemcpyHostToDevice));
     ensure_workspace(p);
     HIPCHK(hipHostMalloc(reinterpret_cast<void **>(&p->hrn), 4 * sizeof(double), hipHostMallocDefault));
+    void *hdev = nullptr;
+    HIPCHK(hipHostGetDevicePointer(&hdev, p->hrn + 3, 0));
+    p->hdev = static_cast<double *>(hdev);
     HIPCHK(hipStreamCreateWithFlags(&p->aux, hipStreamNonBlocking));
     HIPCHK(hipStreamCreateWithFlags(&p->side, hipStreamNonBlocking));
     int dev = 0;
@@ -864,6 +883,7 @@ int feast_plan_create(feast_plan **plan, int64_t n, int64_t m, const feast_conto
     HIPCHK(hipEventCreateWithFlags(&p->ev_panel, hipEventDisableTiming));
     HIPCHK(hipEventCreateWithFlags(&p->ev_fork, hipEventDisableTiming));
     HIPCHK(hipEventCreateWithFlags(&p->ev_join, hipEventDisableTiming));
+    HIPCHK(hipEventCreateWithFlags(&p->ev_orth, hipEventDisableTiming));
     return FEAST_OK;
   });
   if (rc != FEAST_OK) {
@@ -887,7 +907,7 @@ int feast_plan_destroy(feast_plan *p) {
     }
   if (p->ev_cols) (void)hipEventDestroy(p->ev_cols);
   if (p->ev_panel) (void)hipEventDestroy(p->ev_panel);
-  for (hipEvent_t e : {p->ev_fork, p->ev_join})
+  for (hipEvent_t e : {p->ev_fork, p->ev_join, p->ev_orth})
     if (e) (void)hipEventDestroy(e);
   for (DevBuf *b : {&p->dz, &p->dw, &p->dwc, &p->adj, &p->adj_piv, &p->adj_info, &p->adj_inv, &p->F, &p->piv, &p->perm, &p->info, &p->Linv, &p->Uinv, &p->Linv2, &p->Uinv2, &p->cirr_w, &p->R,
                     &p->Y, &p->Y2, &p->T1, &p->T2, &p->Yc, &p->Yc2, &p->W, &p->G, &p->splitws, &p->splitws2, &p->part, &p->nrm,

@@ -477,6 +477,25 @@ __global__ __launch_bounds__(256) void k_chol_inv_grp(const GrpMat *__restrict__
                 flag + blockIdx.x * flag_stride, Dinv + blockIdx.x * dstride + (J0 / 64) * 4096, 64);
 }
 
+// out[0] = ||G - I||_F^2 (one workgroup; t <= a few hundred).
+__global__ __launch_bounds__(1024) void k_dev_identity(const z64 *__restrict__ G, int64_t t,
+                                                       double *__restrict__ out) {
+  __shared__ double red[1024];
+  double v = 0.0;
+  for (int64_t e = threadIdx.x; e < t * t; e += 1024) {
+    const z64 g = G[e];
+    const double x = e / t == e % t ? g.x - 1.0 : g.x;
+    v = fma(x, x, fma(g.y, g.y, v));
+  }
+  red[threadIdx.x] = v;
+  __syncthreads();
+  for (int o = 512; o > 0; o >>= 1) {
+    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) out[0] = red[0];
+}
+
 // Strict lower triangle of a t x t matrix set to zero; optionally the whole matrix.
 __global__ __launch_bounds__(256) void k_zero_lower(z64 *__restrict__ X, int64_t t, int all) {
   const int64_t e = blockIdx.x * 256ll + threadIdx.x;
@@ -844,6 +863,9 @@ void chol_inv_block(hipStream_t s, z64 *G, int64_t ld, int jb, int col0, int32_t
   hipLaunchKernelGGL((k_chol_inv), dim3(1), dim3(256), 0, s, G, ld, jb, col0, flag, Rinv, ldi);
 }
 
+void dev_identity(hipStream_t s, const z64 *G, int64_t t, double *out) {
+  hipLaunchKernelGGL(k_dev_identity, dim3(1), dim3(1024), 0, s, G, t, out);
+}
 void zero_lower(hipStream_t s, z64 *X, int64_t t, bool all) {
   hipLaunchKernelGGL(k_zero_lower, dim3(static_cast<unsigned>((t * t + 255) / 256)), dim3(256), 0,
                      s, X, t, all ? 1 : 0);

@@ -269,6 +269,9 @@ void add_diag_shift(hipStream_t s, z64 *G, int64_t t, double shift_rel);
 void chol_inv_block(hipStream_t s, z64 *G, int64_t ld, int jb, int col0, int32_t *flag, z64 *Rinv,
                     int64_t ldi);
 void zero_lower(hipStream_t s, z64 *X, int64_t t, bool all);
+// out[0] = ||G - I||_F^2 of a t x t matrix (out: a device address, of page-locked
+// host memory if the caller wants it there).
+void dev_identity(hipStream_t s, const z64 *G, int64_t t, double *out);
 
 // Gather columns idx[0..k) of the n x t block X into Y (n x k) and normalise each
 // to unit 2-norm with its largest-modulus entry real positive.

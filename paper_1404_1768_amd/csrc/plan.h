@@ -97,7 +97,10 @@ struct feast_plan {
   DevBuf R, Y, T1, T2, Yc, W, G, splitws, splitws2, part, nrm, flag, small;
   DevBuf rn;  // mixed form: ||R||_F^2 at rn[0] (scale of the complex64 solves), ||d_1||^2 and
               // ||Y_0||^2 of the first correction at rn[1], rn[2]; partials from rn[8]
-  double *hrn = nullptr;   // page-locked copy of rn[0..3) (read after the stream is idle)
+  double *hrn = nullptr;   // page-locked copy of rn[0..3) (read after the stream is idle);
+                           // [3]: ||X^* X - I||_F^2 of an orthonormalisation's second pass
+  double *hdev = nullptr;  // device address of hrn[3]
+  hipEvent_t ev_orth = nullptr;
   bool rho_pending = false;  // hrn holds a filter's first-correction norms not yet read
   DevBuf adj, adj_piv, adj_info, adj_inv;  // adjoint solves (allocated on first use)
   // sparse pencil of the running feast_solve_csr call: the union pattern of A
@@ -179,7 +182,8 @@ void gemm_t<c64>(hipStream_t s, int ta, int64_t M, int64_t N, int64_t K, z64 alp
 void ensure_workspace(feast_plan *p, bool with_nodes = true);
 int64_t splitws_elems(const feast_plan *p);
 
-// Shifted CholeskyQR3 of the n x m block X in place (flags at flag_slot..+2).
+// Shifted Cholesky QR of the n x m block X in place (flags at flag_slot..+2; waits
+// for its second Gram matrix).
 void orth(feast_plan *p, z64 *X, int64_t ldx, int flag_slot, int64_t cols = -1);
 // Algorithm 5's QR steps and reduced pencil on the device: U -> U_1, A U_1, B U_1, U_2, At, Bt.
 void project_device(feast_plan *p, const z64 *A, int64_t lda, const z64 *B, int64_t ldb, z64 *U,
