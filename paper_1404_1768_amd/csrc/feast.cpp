@@ -529,7 +529,8 @@ int filter_rhs(feast_plan *p, const z64 *A, int64_t lda, const z64 *B, int64_t l
     p->last_sweeps = 0;
     if (p->sp.on)
       feast::band_solve(p->s, p->sp.Lf.as<z64>(), p->sp.Uf.as<z64>(), p->sp.Dinv.as<z64>(),
-                        p->sp.piv.as<int32_t>(), p->N, p->n, p->sp.kl, p->sp.ku, R, ldr, cols,
+                        p->sp.piv.as<int32_t>(), p->sp.midlu.as<z64>(), p->sp.midperm.as<int32_t>(),
+                        p->N, feast::BandSplit::of(p->n, p->sp.kl, p->sp.ku), R, ldr, cols,
                         p->Y.as<z64>(), p->ldY(), p->m);
     else
       solve_nodes_z(p, R, ldr, cols);
@@ -912,6 +913,10 @@ int feast_plan_destroy(feast_plan *p) {
   for (DevBuf *b : {&p->dz, &p->dw, &p->dwc, &p->adj, &p->adj_piv, &p->adj_info, &p->adj_inv, &p->F, &p->piv, &p->perm, &p->info, &p->Linv, &p->Uinv, &p->Linv2, &p->Uinv2, &p->cirr_w, &p->R,
                     &p->Y, &p->Y2, &p->T1, &p->T2, &p->Yc, &p->Yc2, &p->W, &p->G, &p->splitws, &p->splitws2, &p->part, &p->nrm,
                     &p->flag, &p->small, &p->fp, &p->rn})
+    b->release();
+  for (DevBuf *b : {&p->sp.rp, &p->sp.ci, &p->sp.va, &p->sp.vb, &p->sp.map, &p->sp.perm, &p->sp.Lf,
+                    &p->sp.Uf, &p->sp.Dinv, &p->sp.piv, &p->sp.info, &p->sp.mid, &p->sp.midlu,
+                    &p->sp.midperm, &p->sp.V, &p->sp.X})
     b->release();
   delete p;
   return FEAST_OK;
@@ -1521,28 +1526,36 @@ int prepare_sparse(feast_plan *p, const feast_csr *A, const feast_csr *B) {
   }
   const int N = p->N;
   const int64_t WC = kl + ku + 1;
-  sp.Lf.alloc(sizeof(z64) * N * n * std::max<int64_t>(kl, 1));
-  sp.Uf.alloc(sizeof(z64) * N * n * WC);
-  sp.Dinv.alloc(sizeof(z64) * N * n);
-  sp.piv.alloc(sizeof(int32_t) * N * n);
-  sp.info.alloc(sizeof(int32_t) * N);
+  const feast::BandSplit bs = feast::BandSplit::of(n, sp.kl, sp.ku);
+  const int64_t vrows = 2 * static_cast<int64_t>(N) * bs.stride();  // rows of both sides of all nodes
+  sp.Lf.alloc(sizeof(z64) * vrows * std::max(bs.lmax(), 1));
+  sp.Uf.alloc(sizeof(z64) * vrows * WC);
+  sp.Dinv.alloc(sizeof(z64) * vrows);
+  sp.piv.alloc(sizeof(int32_t) * vrows);
+  sp.mid.alloc(sizeof(z64) * 4096 * N);
+  sp.midlu.alloc(sizeof(z64) * 2 * 4096 * N);
+  sp.midperm.alloc(sizeof(int32_t) * 64 * N);
+  sp.info.alloc(sizeof(int32_t) * 3 * N);
   sp.V.alloc(sizeof(z64) * n * p->m);
   sp.X.alloc(sizeof(z64) * n * p->m);
+  feast::fill_i32(s, sp.info.as<int32_t>(), 3 * N, 0);
   feast::band_lu(s, sp.rp.as<int32_t>(), sp.ci.as<int32_t>(), sp.va.as<z64>(), sp.vb.as<z64>(),
-                 p->dz.as<z64>(), N, n, sp.kl, sp.ku, sp.Lf.as<z64>(), sp.Uf.as<z64>(),
-                 sp.Dinv.as<z64>(), sp.piv.as<int32_t>(), sp.info.as<int32_t>());
-  std::vector<int32_t> hinfo(N);
-  HIPCHK(hipMemcpyAsync(hinfo.data(), sp.info.p, sizeof(int32_t) * N, hipMemcpyDeviceToHost, s));
+                 p->dz.as<z64>(), N, bs, sp.Lf.as<z64>(), sp.Uf.as<z64>(), sp.Dinv.as<z64>(),
+                 sp.piv.as<int32_t>(), sp.mid.as<z64>(), sp.midlu.as<z64>(),
+                 sp.midperm.as<int32_t>(), sp.info.as<int32_t>());
+  std::vector<int32_t> hinfo(3 * N);
+  HIPCHK(hipMemcpyAsync(hinfo.data(), sp.info.p, sizeof(int32_t) * 3 * N, hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
   HIPCHK(hipGetLastError());
   for (int j = 0; j < N; ++j)
-    if (hinfo[j] != 0) {
-      char buf[200];
-      std::snprintf(buf, sizeof buf, "exact zero pivot in the band LU at node %d (z = %.17g%+.17gi), column %d",
-                    j, p->hz[j].real(), p->hz[j].imag(), hinfo[j] - 1);
-      p->err = buf;
-      return FEAST_SINGULAR;
-    }
+    for (const int bad : {hinfo[2 * j], hinfo[2 * j + 1], hinfo[2 * N + j]})
+      if (bad != 0) {
+        char buf[200];
+        std::snprintf(buf, sizeof buf, "exact zero pivot in the band LU at node %d (z = %.17g%+.17gi), column %d",
+                      j, p->hz[j].real(), p->hz[j].imag(), bad - 1);
+        p->err = buf;
+        return FEAST_SINGULAR;
+      }
   return FEAST_OK;
 }
 

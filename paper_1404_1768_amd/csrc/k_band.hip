@@ -14,8 +14,18 @@
 // entries.  The multipliers of column k are kept in the order of the
 // exchanges, so the forward solve applies exchange k and then column k's
 // multipliers, k = 0, 1, ...
+//
+// A node is factored and solved from both ends at once (BandSplit, kernels.h):
+// the top side eliminates columns 0 .. c - 1, the bottom side, the same kernels on
+// the matrix in reverse order (kl and ku change places), the last c' ones, and the
+// s = n - c - c' = kl + ku columns between them, whose rows are what the two
+// windows hold in the end, make a dense s x s system (k_band_mid).  The kernels
+// are one wavefront's walk along the rows, so two of half the length halve their
+// time: n = 4800, kl = ku = 22, 16 nodes, 40 columns: LU 8.4 -> 4.5 ms, one
+// filter's solves 3.2 -> 1.7.
 #include "common.h"
 #include "kernels.h"
+#include "tri64.h"
 
 namespace feast {
 
@@ -132,12 +142,16 @@ __global__ __launch_bounds__(256) void k_band_lu(const int32_t *__restrict__ rp,
                                                  const int32_t *__restrict__ ci,
                                                  const z64 *__restrict__ va,
                                                  const z64 *__restrict__ vb,
-                                                 const z64 *__restrict__ zn, int64_t n, int kl,
-                                                 int ku, z64 *__restrict__ Lf,
-                                                 z64 *__restrict__ Uf, z64 *__restrict__ Dinv,
-                                                 int32_t *__restrict__ piv,
+                                                 const z64 *__restrict__ zn, const BandSplit sp,
+                                                 z64 *__restrict__ Lf, z64 *__restrict__ Uf,
+                                                 z64 *__restrict__ Dinv, int32_t *__restrict__ piv,
+                                                 z64 *__restrict__ mid,
                                                  int32_t *__restrict__ info) {
-  const int KR = kl + 1, WC = kl + ku + 1;
+  const bool rev = blockIdx.y != 0;
+  // this side's matrix: n rows (of N0 in all), nc columns to eliminate
+  const int64_t N0 = sp.n, n = sp.rows(rev), nc = sp.cols(rev);
+  const int kl = sp.lower(rev);
+  const int KR = kl + 1, WC = sp.kl + sp.ku + 1;
   // one block, so that the per-column arrays sit at the low LDS addresses
   // (immediate offsets) whatever the allocator's order
   struct Lds {
@@ -157,21 +171,24 @@ __global__ __launch_bounds__(256) void k_band_lu(const int32_t *__restrict__ rp,
   auto &s_info = sm.info;
   z64 *SR = sm.SR[0];
   const int j = blockIdx.x;
+  const int64_t v = 2 * static_cast<int64_t>(j) + blockIdx.y;  // this side of node j
   const int tid = threadIdx.x, lane = tid & 63;
   const z64 z = zn[j];
-  z64 *L = Lf + static_cast<int64_t>(j) * n * kl;
-  z64 *U = Uf + static_cast<int64_t>(j) * n * WC;
-  z64 *Di = Dinv + static_cast<int64_t>(j) * n;
-  int32_t *pv = piv + static_cast<int64_t>(j) * n;
+  z64 *L = Lf + v * sp.stride() * sp.lmax();
+  z64 *U = Uf + v * sp.stride() * WC;
+  z64 *Di = Dinv + v * sp.stride();
+  int32_t *pv = piv + v * sp.stride();
 
-  // stage rows r0 .. r0 + cnt - 1 (all < n) into SR (row q at SR[q WC + c - (r0 + q - kl)])
+  // stage rows r0 .. r0 + cnt - 1 (all < n) into SR (row q at SR[q WC + c - (r0 + q - kl)]);
+  // the bottom side's row r and column c are the matrix's N0 - 1 - r and N0 - 1 - c
   auto stage = [&](int64_t r0, int cnt) {
     for (int e = tid; e < cnt * WC; e += 256) SR[e] = zmake(0.0, 0.0);
-    if (tid <= cnt) srp[tid] = rp[r0 + tid];
+    const int64_t ra = rev ? N0 - r0 - cnt : r0;
+    if (tid <= cnt) srp[tid] = rp[ra + tid];
     __syncthreads();
     const int e0 = srp[0], e1 = srp[cnt];
     // (at most kBandCH rows of at most 64 entries: 8 per thread, loaded 4 at a time)
-    for (int h = 0; h < 2; ++h) {
+    for (int h = 0; h < 2 && e0 < e1; ++h) {
       int32_t c4[4];
       z64 a4[4], b4[4];
 #pragma unroll
@@ -188,8 +205,10 @@ __global__ __launch_bounds__(256) void k_band_lu(const int32_t *__restrict__ rp,
         if (e < e1) {
           int row = 0;  // the chunk row holding entry e
           while (row + 1 < cnt && srp[row + 1] <= e) ++row;
+          if (rev) row = cnt - 1 - row;
+          const int64_t c = rev ? N0 - 1 - c4[q] : c4[q];
           const z64 b = b4[q], a = a4[q];
-          SR[row * WC + c4[q] - (r0 + row - kl)] =
+          SR[row * WC + c - (r0 + row - kl)] =
               zmake(z.x * b.x - z.y * b.y - a.x, z.x * b.y + z.y * b.x - a.y);
         }
       }
@@ -207,10 +226,10 @@ __global__ __launch_bounds__(256) void k_band_lu(const int32_t *__restrict__ rp,
     if (row >= cnt) return;
     z64 *dst = sm.SR[b] + row * WC;
     for (int c = sub; c < WC; c += 6) dst[c] = zmake(0.0, 0.0);
-    const int64_t r = r0 + row;
-    const int64_t base = r - kl;  // the column of slot 0
+    const int64_t r = rev ? N0 - 1 - (r0 + row) : r0 + row;
+    const int64_t base = r0 + row - kl;  // the column of slot 0
     for (int e = rp[r], e1 = rp[r + 1]; e < e1; ++e) {
-      const int c = static_cast<int>(ci[e] - base);
+      const int c = static_cast<int>((rev ? N0 - 1 - ci[e] : ci[e]) - base);
       if (c % 6 == sub) {
         const z64 bv = vb[e], av = va[e];
         dst[c] = zmake(z.x * bv.x - z.y * bv.y - av.x, z.x * bv.y + z.y * bv.x - av.y);
@@ -219,7 +238,7 @@ __global__ __launch_bounds__(256) void k_band_lu(const int32_t *__restrict__ rp,
   };
   // the rows entering during the chunk of columns k0 .. k0 + kBandCH - 1
   auto chunk_rows = [&](int64_t k0, int64_t *r0) {
-    const int ch = static_cast<int>(n - k0 < kBandCH ? n - k0 : kBandCH);
+    const int ch = static_cast<int>(nc - k0 < kBandCH ? nc - k0 : kBandCH);
     *r0 = k0 + KR;
     return *r0 < n ? static_cast<int>(n - *r0 < ch ? n - *r0 : ch) : 0;
   };
@@ -249,14 +268,14 @@ __global__ __launch_bounds__(256) void k_band_lu(const int32_t *__restrict__ rp,
     stage_bg(0, r0, cnt);
   }
   int ck = 0;  // slot of column k
-  for (int64_t k0 = 0, c = 0; k0 < n; k0 += kBandCH, ++c) {
-    const int ch = static_cast<int>(n - k0 < kBandCH ? n - k0 : kBandCH);
+  for (int64_t k0 = 0, c = 0; k0 < nc; k0 += kBandCH, ++c) {
+    const int ch = static_cast<int>(nc - k0 < kBandCH ? nc - k0 : kBandCH);
     int64_t r0;
     const int cnt = chunk_rows(k0, &r0);  // incoming rows of this chunk's columns
     const z64 *SRc = sm.SR[c & 1];
     __syncthreads();  // this chunk's rows are staged; the other buffer is free
     if (tid >= 64) {  // the next chunk's rows, while wave 0 factors this one's
-      if (k0 + kBandCH < n) {
+      if (k0 + kBandCH < nc) {
         int64_t r0n;
         const int cntn = chunk_rows(k0 + kBandCH, &r0n);
         stage_bg(static_cast<int>((c + 1) & 1), r0n, cntn);
@@ -295,7 +314,7 @@ __global__ __launch_bounds__(256) void k_band_lu(const int32_t *__restrict__ rp,
         if (lane == 0) {
           pv[k] = static_cast<int32_t>(k + p);
           Di[k] = inv;
-          if (zero && s_info == 0) s_info = static_cast<int>(k) + 1;
+          if (zero && s_info == 0) s_info = static_cast<int>(rev ? N0 - 1 - k : k) + 1;
         }
         // every owner is a lane of this wavefront: a wavefront barrier makes
         // the multipliers visible
@@ -317,7 +336,7 @@ __global__ __launch_bounds__(256) void k_band_lu(const int32_t *__restrict__ rp,
                 w[i] = w[0];
               }
           }
-          U[k * WC + jo] = (k + jo < n) ? rpv : zmake(0.0, 0.0);
+          U[k * WC + jo] = (rev || k + jo < N0) ? rpv : zmake(0.0, 0.0);
           // the incoming row k + KR at this slot's next column (k + jo, or
           // k + WC for the slot of column k): staged index WC - 1 or jo - 1
           const z64 nv = (kk < cnt) ? SRc[kk * WC + (jo == 0 ? WC - 1 : jo - 1)] : zmake(0.0, 0.0);
@@ -365,8 +384,124 @@ __global__ __launch_bounds__(256) void k_band_lu(const int32_t *__restrict__ rp,
       if (++ck == WC) ck = 0;
     }
   }
+  // the window's kl rows over the s columns between the sides
+  if (sp.two && tid < WC) {
+    int jo = tid - ck;
+    if (jo < 0) jo += WC;
+    const int s = sp.kl + sp.ku;
+    z64 *Mj = mid + j * 4096ll;
+    if (jo < s)
+#pragma unroll
+      for (int i = 0; i < W; ++i)
+        if (i < kl) Mj[rev ? (s - 1 - i) * 64 + (s - 1 - jo) : i * 64 + jo] = w[i];
+  }
   __syncthreads();
-  if (tid == 0) info[j] = s_info;
+  if (tid == 0) info[v] = s_info;
+}
+
+// The dense s x s system between the two sides of node j = blockIdx.x (rows 64
+// apart in mid): LU with partial pivoting in LDS, one barrier-separated rank-1
+// update per column, then the inverses of both factors by halves (tri64.h):
+// lu[0] = L^{-1}, lu[1] = U^{-1} (64 x 64, identity past s), perm[i] the row of
+// mid that the pivoting put in place i; info: 1 + the first column without a
+// pivot, counted from the first of all (c0), or 0.
+__global__ __launch_bounds__(256) void k_band_mid(const z64 *__restrict__ mid, int s, int64_t c0,
+                                                  z64 *__restrict__ lu, int32_t *__restrict__ perm,
+                                                  int32_t *__restrict__ info) {
+  __shared__ z64 S[64][kTP];
+  __shared__ z64 X[64][kTP];
+  __shared__ int s_p[64];
+  __shared__ int s_piv;
+  __shared__ z64 s_inv;
+  const int j = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const z64 *Mj = mid + j * 4096ll;
+  for (int i = wave; i < 64; i += 4)
+    S[i][lane] = (i < s && lane < s) ? Mj[i * 64 + lane] : zmake(i == lane ? 1.0 : 0.0, 0.0);
+  if (tid < 64) s_p[tid] = tid;
+  int bad = 0;
+  __syncthreads();
+  for (int k = 0; k < s; ++k) {
+    if (wave == 0) {
+      const z64 v = S[lane][k];
+      const double a1 = zabs1(v);
+      double key = lane >= k && lane < s ? (a1 == a1 ? a1 : -1.0) : -2.0;
+      int idx = lane >= k && lane < s ? lane : 1 << 30;
+      wave_argmax(key, idx);
+      const int p = __builtin_amdgcn_readfirstlane(idx < s ? idx : k);
+      const bool zero = !(lane_at(key, 0) > 0.0);
+      if (zero && bad == 0) bad = k + 1;
+      const z64 inv = zero ? zmake(0.0, 0.0) : band_recip(lane_at(v.x, p), lane_at(v.y, p));
+      if (lane == 0) {
+        s_piv = p;
+        s_inv = inv;
+      }
+    }
+    __syncthreads();
+    const int p = s_piv;
+    if (p != k && tid < 64) {
+      const z64 x = S[k][tid];
+      S[k][tid] = S[p][tid];
+      S[p][tid] = x;
+      if (tid == 0) {
+        const int q = s_p[k];
+        s_p[k] = s_p[p];
+        s_p[p] = q;
+      }
+    }
+    __syncthreads();
+    if (tid > k && tid < s) S[tid][k] = zmul(S[tid][k], s_inv);
+    __syncthreads();
+    for (int i = k + 1 + wave; i < s; i += 4)
+      if (lane > k && lane < s) S[i][lane] = band_fms(S[i][lane], S[i][k], S[k][lane]);
+    __syncthreads();
+  }
+  for (int h = 0; h < 2; ++h) {  // L, then U (as the lower matrix it is in reverse order)
+    const int rv = h == 0 ? 0 : 63;
+    for (int i = wave; i < 64; i += 4) X[i][lane] = S[i ^ rv][lane ^ rv];
+    __syncthreads();
+    tri64_inverse(X, h == 0, lane, wave);
+    z64 *o = lu + (2ll * j + h) * 4096;
+    for (int i = wave; i < 64; i += 4) {
+      const bool in = h == 0 ? lane <= i : lane >= i;
+      o[i * 64 + lane] = in ? X[i ^ rv][lane ^ rv] : zmake(0.0, 0.0);
+    }
+    __syncthreads();
+  }
+  if (tid < 64) perm[j * 64 + tid] = s_p[tid];
+  if (tid == 0) info[j] = bad ? static_cast<int>(c0) + bad : 0;
+}
+
+// Rows c0 .. c0 + s - 1 of the node blocks: x = U^{-1} (L^{-1} P x), 32 columns a
+// workgroup, each wavefront a strip of 16 rows on the matrix cores.
+__global__ __launch_bounds__(256) void k_band_midsolve(const z64 *__restrict__ lu,
+                                                       const int32_t *__restrict__ perm, int s,
+                                                       int64_t c0, int64_t m, z64 *__restrict__ Y,
+                                                       int64_t ldy, int64_t sY) {
+  __shared__ z64 A[64][kTP];
+  __shared__ z64 X[64][kTP];
+  const int j = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t col = static_cast<int64_t>(blockIdx.y) * 32 + (tid & 31);
+  z64 *Yj = Y + j * sY + c0 * ldy;
+  for (int i = tid >> 5; i < 64; i += 8) {
+    const int p = perm[j * 64 + i];
+    X[i][tid & 31] = (i < s && col < m) ? Yj[p * ldy + col] : zmake(0.0, 0.0);
+  }
+  for (int h = 0; h < 2; ++h) {
+    const z64 *f = lu + (2ll * j + h) * 4096;
+    for (int i = wave; i < 64; i += 4) A[i][lane] = f[i * 64 + lane];
+    __syncthreads();
+    Tile16<z64> t[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) t[q].mac<false>(A, 16 * wave, 0, X, 0, 16 * q, 16, lane);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) t[q].put(X, 16 * wave, 16 * q, lane, 1.0);
+    __syncthreads();
+  }
+  for (int i = tid >> 5; i < s; i += 8)
+    if (col < m) Yj[i * ldy + col] = X[i][tid & 31];
 }
 
 // The node solves Y_j = M_j^{-1} R with M_j's band factors (node j =
@@ -499,10 +634,10 @@ __device__ inline z64 band_fwd_row(z64 (&w)[N], const z64 *f, int p, z64 nv, int
 
 template <int WF>
 __global__ __launch_bounds__(128) void k_band_fwd(const z64 *__restrict__ Lf,
-                                                  const int32_t *__restrict__ piv, int64_t n,
-                                                  int kl, const z64 *__restrict__ R, int64_t ldr,
-                                                  int64_t m, z64 *__restrict__ Y, int64_t ldy,
-                                                  int64_t sY) {
+                                                  const int32_t *__restrict__ piv,
+                                                  const BandSplit sp, const z64 *__restrict__ R,
+                                                  int64_t ldr, int64_t m, z64 *__restrict__ Y,
+                                                  int64_t ldy, int64_t sY) {
   constexpr int UF = kBandU, H = WF / 2;
   static_assert(WF % 2 == 0, "two halves of the window");
   // two chunks' staging (wave 1 fills one while wave 0 solves from the other)
@@ -515,12 +650,22 @@ __global__ __launch_bounds__(128) void k_band_fwd(const z64 *__restrict__ Lf,
   // idle lanes (col >= m, in the last block only) duplicate column m - 1 of
   // their own wavefront, so they may store: same values, same instruction
   const int64_t cc = act ? col : m - 1;
-  const z64 *L = Lf + static_cast<int64_t>(j) * n * kl;
-  const int32_t *pv = piv + static_cast<int64_t>(j) * n;
+  const bool rev = blockIdx.z != 0;
+  const int64_t n = sp.rows(rev), nc = sp.cols(rev);  // (as in k_band_lu)
+  const int kl = sp.lower(rev);
+  const int64_t v = 2 * static_cast<int64_t>(j) + blockIdx.z;
+  const z64 *L = Lf + v * sp.stride() * sp.lmax();
+  const int32_t *pv = piv + v * sp.stride();
   z64 *Yj = Y + static_cast<int64_t>(j) * sY;
+  if (rev) {  // rows in reverse order
+    R += (sp.n - 1) * ldr;
+    ldr = -ldr;
+    Yj += (sp.n - 1) * ldy;
+    ldy = -ldy;
+  }
   // wave 1: the chunk of rows k0 .. k0 + kBandCH - 1 into buffer b
   auto stage = [&](int b, int64_t k0) {
-    const int ch = static_cast<int>(n - k0 < kBandCH ? n - k0 : kBandCH);
+    const int ch = static_cast<int>(nc - k0 < kBandCH ? nc - k0 : kBandCH);
     BandStage::padded<WF>(fac[b], L + k0 * kl, kl, -1, 1, kl + 1, ch, lane);
     if (lane < ch) s_piv[b][lane] = pv[k0 + lane] - static_cast<int32_t>(k0 + lane);
     BandStage::rows(rows[b], R, ldr, k0 + WF, ch, n, cc, lane);
@@ -532,12 +677,12 @@ __global__ __launch_bounds__(128) void k_band_fwd(const z64 *__restrict__ Lf,
     w[i] = (i < H && row < n) ? R[row * ldr + cc] : zmake(0.0, 0.0);
   }
   if (wv == 1) stage(0, 0);
-  for (int64_t k0 = 0, c = 0; k0 < n; k0 += kBandCH, ++c) {
-    const int ch = static_cast<int>(n - k0 < kBandCH ? n - k0 : kBandCH);
+  for (int64_t k0 = 0, c = 0; k0 < nc; k0 += kBandCH, ++c) {
+    const int ch = static_cast<int>(nc - k0 < kBandCH ? nc - k0 : kBandCH);
     const int b = static_cast<int>(c & 1);
     __syncthreads();  // this chunk is staged; the other buffer is free
     if (wv == 1) {
-      if (k0 + kBandCH < n) stage(b ^ 1, k0 + kBandCH);
+      if (k0 + kBandCH < nc) stage(b ^ 1, k0 + kBandCH);
       continue;
     }
     for (int kb = 0; kb < ch; kb += UF) {
@@ -559,6 +704,16 @@ __global__ __launch_bounds__(128) void k_band_fwd(const z64 *__restrict__ Lf,
   }
       FEAST_FWD_STEP(0) FEAST_FWD_STEP(1) FEAST_FWD_STEP(2) FEAST_FWD_STEP(3)
 #undef FEAST_FWD_STEP
+      if (n > nc && k0 + ch >= nc && kb + UF >= ch) {
+        // the side's last row is done, nb <= UF rows into the block: the window's
+        // kl rows go on to the system between the sides
+#pragma unroll
+        for (int e = 1; e <= UF; ++e)
+          if (nb == e)
+#pragma unroll
+            for (int i = 0; i < H; ++i)
+              if (half * H + i < kl) Yj[(nc + half * H + i) * ldy + cc] = w[e + i];
+      }
 #pragma unroll
       for (int i = 0; i < H; ++i) w[i] = w[i + UF];
     }
@@ -583,12 +738,15 @@ __device__ inline double quarter_prev(double v, int qt) {
 
 template <int WB>
 __global__ __launch_bounds__(128) void k_band_bwd(const z64 *__restrict__ Uf,
-                                                  const z64 *__restrict__ Dinv, int64_t n, int kl,
-                                                  int ku, int64_t m, z64 *__restrict__ Y,
-                                                  int64_t ldy, int64_t sY) {
+                                                  const z64 *__restrict__ Dinv,
+                                                  const BandSplit sp, int64_t m,
+                                                  z64 *__restrict__ Y, int64_t ldy, int64_t sY) {
   constexpr int UB = kBandU, Q = WB / 4;
   static_assert(WB % 4 == 0 && Q >= UB, "a quarter's block rows come from the quarter before");
-  const int WC = kl + ku + 1, WU = kl + ku;
+  const int WC = sp.kl + sp.ku + 1, WU = sp.kl + sp.ku;
+  const bool rev = blockIdx.z != 0;
+  const int64_t n = sp.cols(rev);  // this side's rows
+  const int64_t v = 2 * static_cast<int64_t>(blockIdx.x) + blockIdx.z;
   // two chunks' staging (wave 1 fills one while wave 0 solves from the other)
   __shared__ z64 fac[2][kBandCH * WB];  // rows of U past the diagonal (WU each, zero-padded)
   __shared__ z64 rows[2][kBandCH][64];  // the forward results of those rows (all quarters)
@@ -597,13 +755,17 @@ __global__ __launch_bounds__(128) void k_band_bwd(const z64 *__restrict__ Uf,
   const int64_t col = static_cast<int64_t>(blockIdx.y) * 16 + (lane & 15);
   const bool act = col < m;
   const int64_t cc = act ? col : m - 1;
-  const z64 *U = Uf + static_cast<int64_t>(j) * n * WC;
-  const z64 *Di = Dinv + static_cast<int64_t>(j) * n;
+  const z64 *U = Uf + v * sp.stride() * WC;
+  const z64 *Di = Dinv + v * sp.stride();
   z64 *Yj = Y + static_cast<int64_t>(j) * sY;
+  if (rev) {  // rows in reverse order
+    Yj += (sp.n - 1) * ldy;
+    ldy = -ldy;
+  }
   // Lanes l, l + 16, l + 32, l + 48 share column l: quarter q sums the terms
   // t = qQ + 1 .. (q + 1)Q of row k.  Step r of a block (rows descending):
-  // b[UB - 1 - r + t] = solved row k + qQ + t, t = 1 .. Q; rows past n - 1
-  // stay zero (and U's entries there are stored zero).
+  // b[UB - 1 - r + t] = solved row k + qQ + t, t = 1 .. Q; rows past the
+  // matrix's last one stay zero (and U's entries there are stored zero).
   // wave 1: the chunk of rows k1 - kBandCH .. k1 - 1 (from 0) into buffer bf;
   // its rows of Y hold forward results until wave 0 reaches them
   auto stage = [&](int bf, int64_t k1) {
@@ -616,6 +778,10 @@ __global__ __launch_bounds__(128) void k_band_bwd(const z64 *__restrict__ Uf,
   z64 b[Q + UB];
 #pragma unroll
   for (int i = 0; i < Q + UB; ++i) b[i] = zmake(0.0, 0.0);
+  if (sp.two)  // the solved rows between the sides are the first window
+#pragma unroll
+    for (int i = 0; i < Q; ++i)
+      if (qt * Q + i < WU) b[UB + i] = Yj[(n + qt * Q + i) * ldy + cc];
   if (wv == 1) stage(0, n);
   for (int64_t k1 = n, c = 0; k1 > 0; k1 -= kBandCH, ++c) {
     const int ch = static_cast<int>(k1 < kBandCH ? k1 : kBandCH);
@@ -726,25 +892,32 @@ int band_class(int w) { return w <= 16 ? 16 : w <= 24 ? 24 : w <= 32 ? 32 : w <=
 // (kl + ku <= 63: kl + 1 <= 64 rows in the registers of a column owner, and at
 // most 64 owners, all in the first wavefront)
 void band_lu(hipStream_t s, const int32_t *rp, const int32_t *ci, const z64 *va, const z64 *vb,
-             const z64 *z, int32_t N, int64_t n, int kl, int ku, z64 *Lf, z64 *Uf, z64 *Dinv,
-             int32_t *piv, int32_t *info) {
-  if (N <= 0 || n <= 0) return;
-  FEAST_BAND_DISPATCH(band_class(kl + 1), k_band_lu, dim3(N), dim3(256), 0, s, rp, ci, va, vb, z,
-                      n, kl, ku, Lf, Uf, Dinv, piv, info)
+             const z64 *z, int32_t N, const BandSplit &sp, z64 *Lf, z64 *Uf, z64 *Dinv,
+             int32_t *piv, z64 *mid, z64 *midlu, int32_t *midperm, int32_t *info) {
+  if (N <= 0 || sp.n <= 0) return;
+  FEAST_BAND_DISPATCH(band_class(sp.lmax() + 1), k_band_lu, dim3(N, sp.two ? 2 : 1), dim3(256), 0, s,
+                      rp, ci, va, vb, z, sp, Lf, Uf, Dinv, piv, mid, info)
+  if (sp.two)
+    hipLaunchKernelGGL(k_band_mid, dim3(N), dim3(256), 0, s, mid, sp.kl + sp.ku, sp.c, midlu, midperm,
+                       info + 2 * N);
 }
 
 void band_solve(hipStream_t s, const z64 *Lf, const z64 *Uf, const z64 *Dinv, const int32_t *piv,
-                int32_t N, int64_t n, int kl, int ku, const z64 *R, int64_t ldr, int64_t m,
-                z64 *Y, int64_t ldy, int64_t sY) {
-  if (N <= 0 || n <= 0 || m <= 0) return;
+                const z64 *midlu, const int32_t *midperm, int32_t N, const BandSplit &sp,
+                const z64 *R, int64_t ldr, int64_t m, z64 *Y, int64_t ldy, int64_t sY) {
+  if (N <= 0 || sp.n <= 0 || m <= 0) return;
   // forward: 32 columns per wavefront (two lanes each); backward: 16 (four)
-  const dim3 gf(N, static_cast<unsigned>((m + 31) / 32));
-  const dim3 gb(N, static_cast<unsigned>((m + 15) / 16));
+  const unsigned sides = sp.two ? 2 : 1;
+  const dim3 gf(N, static_cast<unsigned>((m + 31) / 32), sides);
+  const dim3 gb(N, static_cast<unsigned>((m + 15) / 16), sides);
   // (a second wavefront per block stages the next chunk)
-  FEAST_BAND_DISPATCH(band_class(kl + 1), k_band_fwd, gf, dim3(128), 0, s, Lf, piv, n, kl, R,
+  FEAST_BAND_DISPATCH(band_class(sp.lmax() + 1), k_band_fwd, gf, dim3(128), 0, s, Lf, piv, sp, R,
                       ldr, m, Y, ldy, sY)
-  FEAST_BAND_DISPATCH(band_class(kl + ku), k_band_bwd, gb, dim3(128), 0, s, Uf, Dinv, n, kl, ku,
-                      m, Y, ldy, sY)
+  if (sp.two && sp.kl + sp.ku > 0)
+    hipLaunchKernelGGL(k_band_midsolve, dim3(N, static_cast<unsigned>((m + 31) / 32)), dim3(256), 0,
+                       s, midlu, midperm, sp.kl + sp.ku, sp.c, m, Y, ldy, sY);
+  FEAST_BAND_DISPATCH(band_class(sp.kl + sp.ku), k_band_bwd, gb, dim3(128), 0, s, Uf, Dinv, sp, m, Y,
+                      ldy, sY)
 }
 
 void csr_spmm(hipStream_t s, const int32_t *rp, const int32_t *ci, const z64 *va, const z64 *vb,

@@ -290,19 +290,46 @@ void identity(hipStream_t s, z64 *X, int64_t t);
 // Sparse pencils in band form (k_band.hip).  A and B are values va, vb on one
 // CSR pattern (rp, ci) whose entries lie within kl subdiagonals and ku
 // superdiagonals; M_j = z_j B - A.
-// Band LU with partial pivoting of every node (one workgroup each): Lf holds
-// node j's multipliers of column k at (j n + k) kl + i - 1 (rows k + i), Uf
-// its row k of U at (j n + k)(kl + ku + 1) + t (column k + t), Dinv the
-// reciprocal of U's diagonal entry k at j n + k, piv the row exchanged with k,
-// info the first zero-pivot column + 1 (0: none).
+// How a node's n columns are eliminated: from both ends (two): the first c ones
+// from the top, the last n - c - (kl + ku) ones from the bottom in reverse order
+// (side 1, where kl and ku change places), and a dense system of the kl + ku
+// columns between them; or all from the top.  rows: the rows a side works on (those
+// it eliminates and the ones its window holds at the end); arrays of factors hold
+// side sd of node j at v = 2 j + sd, stride() rows apart.
+struct BandSplit {
+  int64_t n, c;
+  int kl, ku;
+  bool two;
+  // The two sides take half the time of one (a walk of n / 2 rows each); a
+  // matrix that is little more than its windows is left to the top side.
+  __host__ static BandSplit of(int64_t n, int kl, int ku) {
+    const bool two = n >= 4 * static_cast<int64_t>(kl + ku) + 64;
+    return BandSplit{n, two ? (n - kl - ku) / 2 : n, kl, ku, two};
+  }
+  __host__ __device__ int64_t cols(bool side) const { return side ? n - kl - ku - c : c; }
+  __host__ __device__ int64_t rows(bool side) const {
+    return two ? cols(side) + lower(side) : n;
+  }
+  __host__ __device__ int lower(bool side) const { return side ? ku : kl; }
+  __host__ __device__ int lmax() const { return kl > ku ? kl : ku; }
+  __host__ __device__ int64_t stride() const { return two ? n - kl - ku - c : n; }
+};
+// Band LU with partial pivoting of every node and side (one workgroup each): Lf
+// holds the multipliers of side v's column k at v stride lmax + k lower + i - 1
+// (rows k + i), Uf its row k of U at (v stride + k)(kl + ku + 1) + t (column
+// k + t), Dinv the reciprocal of U's diagonal entry k at v stride + k, piv the row
+// exchanged with k.  mid (64 x 64 per node): the system between the sides; midlu
+// its inverted factors (two 64 x 64 blocks per node), midperm (64 per node) its
+// row order.  info[v], and info[2 N + j] for the systems between: the
+// first zero-pivot column + 1 (0: none).
 void band_lu(hipStream_t s, const int32_t *rp, const int32_t *ci, const z64 *va, const z64 *vb,
-             const z64 *z, int32_t N, int64_t n, int kl, int ku, z64 *Lf, z64 *Uf, z64 *Dinv,
-             int32_t *piv, int32_t *info);
+             const z64 *z, int32_t N, const BandSplit &sp, z64 *Lf, z64 *Uf, z64 *Dinv,
+             int32_t *piv, z64 *mid, z64 *midlu, int32_t *midperm, int32_t *info);
 // Y_j = M_j^{-1} R (R: n x m, ldr; node j's solution at Y + j sY, leading
 // dimension ldy) with the band factors above.
 void band_solve(hipStream_t s, const z64 *Lf, const z64 *Uf, const z64 *Dinv, const int32_t *piv,
-                int32_t N, int64_t n, int kl, int ku, const z64 *R, int64_t ldr, int64_t m,
-                z64 *Y, int64_t ldy, int64_t sY);
+                const z64 *midlu, const int32_t *midperm, int32_t N, const BandSplit &sp,
+                const z64 *R, int64_t ldr, int64_t m, z64 *Y, int64_t ldy, int64_t sY);
 // YA = A X, YB = B X on the shared pattern (a null output is skipped).
 void csr_spmm(hipStream_t s, const int32_t *rp, const int32_t *ci, const z64 *va, const z64 *vb,
               int64_t n, const z64 *X, int64_t ldx, int64_t m, z64 *YA, int64_t ldya, z64 *YB,

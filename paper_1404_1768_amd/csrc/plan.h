@@ -112,6 +112,7 @@ struct feast_plan {
     int64_t nnz = 0;
     DevBuf rp, ci, va, vb, map, perm;
     DevBuf Lf, Uf, Dinv, piv, info;
+    DevBuf mid, midlu, midperm;  // the systems between the two sides of the nodes
     DevBuf V, X;  // start block and eigenvector block in the new order
     // the patterns the device ordering (rp, ci, map, perm, kl, ku) was made
     // for: a later call with the same patterns reuses it
