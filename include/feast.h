@@ -95,7 +95,7 @@ typedef struct {
                           ahead_cus compute units free for it; 0: panels and updates in
                           sequence (default 0: at n = 4000 the overlap gains 1-2 % of the
                           factorisation, the persistent update being slower per flop) */
-  int32_t update_tile; /* LU trailing-update tile: 0 = 64 x 64, 1 = 128 x 64 (default 0) */
+  int32_t update_tile; /* LU trailing-update tile: 0 = 64 x 32, 1 = 128 x 64 (default 0) */
   int32_t batch_update; /* batched form's trailing-update loop: 0 = from the tuned table
                            (with nb = 0 for the panel width too), 1 = four real products per
                            complex step, 2 = three products, operand-pipelined, 3 = four

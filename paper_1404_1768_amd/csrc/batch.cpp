@@ -252,7 +252,8 @@ void ggemm(feast_batch *b, Tables &tab, int ta, bool sub, std::vector<GemmArgs<T
   if (e.empty()) return;
   if (variant < 0)
     variant = (sub && ta == 0 && sizeof(T) == 16) ? feast::GROUP_UPDATE_M3 : feast::GROUP_PLAIN;
-  const int64_t tiles = feast::gemm_group_tiles<T>(e.data(), static_cast<int>(e.size()));
+  const feast::GroupTiles tiles =
+      feast::gemm_group_tiles<T>(e.data(), static_cast<int>(e.size()), ta);
   const GemmArgs<T> *d = tab.put(e);
   if (!tab.record)
     feast::gemm_group<T>(b->gs, ta, sub, d, static_cast<int>(e.size()), tiles, variant);
@@ -987,7 +988,8 @@ void leave(feast_batch *b) {
 // which may still read the table's previous contents).
 void grouped_on(Tables &t, hipStream_t st, std::vector<GemmArgs<z64>> &e) {
   if (e.empty()) return;
-  const int64_t tiles = feast::gemm_group_tiles<z64>(e.data(), static_cast<int>(e.size()));
+  const feast::GroupTiles tiles =
+      feast::gemm_group_tiles<z64>(e.data(), static_cast<int>(e.size()), 0);
   t.host.clear();
   t.off.clear();
   t.cnt.clear();

@@ -4,18 +4,14 @@
 //
 // FP64 (z64): every complex 16x16x4 tile product is four real
 // v_mfma_f64_16x16x4_f64 products (Cr += Ar Br - Ai Bi, Ci += Ar Bi + Ai Br),
-// i.e. 8 real flops per complex multiply-add, the count the roofline uses.
+// i.e. 8 real flops per complex multiply-add, the count the roofline uses, or
+// three in the three-product form.
 // FP32 (c64): the same structure on v_mfma_f32_16x16x4_f32.
 //
-// Tiles: BM x BN outputs per 256-thread workgroup (4 waves in a 2x2 grid, each
-// wave owning a (BM/2) x (BN/2) block of 16x16 MFMA tiles), K in steps of 16
-// complex.  Operands are staged through LDS as separate real/imaginary planes
-// stored k-major, so that each MFMA operand fragment is 16 consecutive LDS
-// words per k row; the next K step is prefetched into registers while the
-// current one is multiplied (two LDS buffers, one barrier per step).
-//
-// A launch covers batch x splits x tiles workgroups mapped XCD-contiguously.
+// Large outputs are cut into the tiles of gemm_tile.h, small ones go to k_gemm_ks
+// below.  A launch covers batch x splits x tiles workgroups mapped XCD-contiguously.
 #include "common.h"
+#include "gemm_tile.h"
 #include "kernels.h"
 #include "mfma.h"
 
@@ -23,490 +19,62 @@ namespace feast {
 
 namespace {
 
-template <typename T> __device__ inline T ld_cplx(const T *p) { return *p; }
-
-// SUB = true computes C -= op(A) B exactly: the accumulators start from C (loaded
-// before the K loop, so its latency overlaps the first operand loads) and the
-// MFMAs use -A; the epilogue is then a plain store.  SUB = false is the general
-// C = alpha op(A) B + beta C with the C read in the epilogue.
-// One output tile: `lin` indexes the tiles x batch x splits of problem d.
-//
-// SHF (with SUB, TA = 0): the A operand is shift[b] A2 - A, formed from the two
-// staged tiles in registers before they are written to LDS, and the
-// accumulators start from C0 rather than C (C = C0 - (shift A2 - A) B).
-//
-// NG > 1: the workgroup is NG groups of 256 threads, each with LDS planes of
-// its own, working on NG tiles at once.  A group's four wavefronts meet at a
-// barrier of their own (an LDS counter, gcount, that each wavefront raises by
-// one per barrier and waits on until it reaches *gphase), so the groups do
-// not run in lockstep: while one waits for its operands another computes.
-// A group with no tile of its own passes own = false with any valid lin: it
-// stages operands but issues no MFMAs or stores.
-constexpr int kFoldK = 128;  // three-product form: K steps between folds of T1 (power of 2)
-
-template <typename T, int BM, int BN, int TA, bool SUB, int BK, bool M3, bool SHF = false,
-          bool PIPE = true, int NG = 1>
-__device__ __forceinline__ void gemm_tile(const GemmArgs<T> &d, int64_t lin, bool own = true,
-                                          uint32_t *gcount = nullptr, uint32_t *gphase = nullptr) {
-  static_assert(!SHF || (SUB && TA == 0), "shifted operand: C0 - (s A2 - A) B only");
-  using Ops = mfma_ops<T>;
-  using real = typename Ops::real;
-  using acc_t = typename Ops::acc_t;
-  static_assert(BK == 8 || BK == 16, "BK");
-  constexpr int WM = BM / 2, WN = BN / 2;
-  constexpr int FM = WM / 16, FN = WN / 16;
-  // LDS row pitch (32 banks of 4 bytes).  FP64 planes: a read of 16
-  // consecutive doubles covers the 32 banks; an odd pitch keeps the 16 rows of
-  // an A store apart.  complex64 planes: pitch BM + 2 (reads of rows k and k+1
-  // then share banks 2-way; an XOR swizzle removing that measured no faster
-  // and costs registers).
-  constexpr bool F32 = sizeof(real) == 4;
-  constexpr int PA = F32 ? BM + 2 : BM + 1, PB = F32 ? BN + 2 : BN + 1;
-  constexpr int NA = BM * BK / 256, NB = BN * BK / 256;
-  __shared__ real gAr[NG][2][BK][PA], gAi[NG][2][BK][PA], gBr[NG][2][BK][PB], gBi[NG][2][BK][PB];
-  // (NG > 1 runs in a loop over tiles: the thread index passes through an
-  // empty asm statement so that the addresses derived from it are formed
-  // again in each round instead of being held in registers across the loop)
-  int tx = static_cast<int>(threadIdx.x);
-  if constexpr (NG > 1) asm volatile("" : "+v"(tx));
-  const int gsel = NG > 1 ? __builtin_amdgcn_readfirstlane(tx >> 8) : 0;  // wave-uniform
-  auto &sAr = gAr[gsel];
-  auto &sAi = gAi[gsel];
-  auto &sBr = gBr[gsel];
-  auto &sBi = gBi[gsel];
-  // M3: the three-multiplication complex product
-  //   T1 = (Ar + Ai) Br,  P = -Ai (Br + Bi),  Q = Ar (Bi - Br),
-  //   Re(AB) = T1 + P,    Im(AB) = T1 + Q
-  // (3 real MFMAs per complex step instead of 4; its normwise rounding bound is
-  // about twice the usual one).
-  // The operand sums are formed once, when a tile is staged in LDS: plane
-  // sAs = Ar + Ai, sBs = Br + Bi, and sBi holds Bi - Br.
-  __shared__ real gAs[NG][2][M3 ? BK : 1][M3 ? PA : 1], gBs[NG][2][M3 ? BK : 1][M3 ? PB : 1];
-  auto &sAs = gAs[gsel];
-  auto &sBs = gBs[gsel];
-
-  const int64_t tm = (d.M + BM - 1) / BM, tn = (d.N + BN - 1) / BN;
-  const int64_t tiles = tm * tn;
-  const int64_t total = tiles * d.batch * d.splits;
-  if (lin >= total) return;
-  const int64_t tile = lin % tiles;
-  lin /= tiles;
-  const int64_t bidx = lin % d.batch;
-  const int64_t split = lin / d.batch;
-  // tiles in groups of up to 8 tile rows, column by column inside a group:
-  // consecutive workgroups share the A row panels of the group (kept in L2)
-  // and read each B column panel once per group instead of once per tile row
-  constexpr int64_t G = 8;
-  const int64_t grp = tile / (G * tn);
-  const int64_t gr0 = grp * G;
-  const int64_t grows = (tm - gr0 < G) ? tm - gr0 : G;
-  const int64_t gt = tile - grp * G * tn;
-  const int64_t m0 = (gr0 + gt % grows) * BM, n0 = (gt / grows) * BN;
-  const int64_t kbeg = split * d.kchunk;
-  const int64_t kend = (kbeg + d.kchunk < d.K) ? kbeg + d.kchunk : d.K;
-
-  const T *A = d.A + bidx * d.sA;
-  const T *B = d.B + bidx * d.sB;
-  const T *A2 = SHF ? d.A2 + bidx * d.sA : nullptr;
-  real zr = 0, zi = 0;
-  if constexpr (SHF) {
-    zr = static_cast<real>(d.shift[bidx].x);
-    zi = static_cast<real>(d.shift[bidx].y);
-  }
-
-  const int tid = NG > 1 ? (tx & 255) : tx;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  // barrier of the threads that share this tile's LDS planes
-  auto tile_sync = [&]() {
-    if constexpr (NG == 1) {
-      __syncthreads();
-    } else {
-      *gphase += 4;
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-      if (lane == 0) __hip_atomic_fetch_add(gcount, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      while (__hip_atomic_load(gcount, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < *gphase)
-        __builtin_amdgcn_s_sleep(1);
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    }
-  };
-  // a wavefront whose whole output block lies outside C (ragged last tile)
-  // stages operands and meets the barriers but issues no MFMAs
-  const bool live = own && (m0 + wm * WM < d.M) && (n0 + wn * WN < d.N);
-
-  T ra[NA], rb[NB];
-  T ra2[SHF ? NA : 1];
-
-  auto gload = [&](int64_t k0) {
-    if (TA == 0) {
-      // A is M x K row-major: BK lanes read one row's BK consecutive elements
-      const int kk = tid % BK, rr = tid / BK;
-#pragma unroll
-      for (int i = 0; i < NA; ++i) {
-        const int64_t r = m0 + rr + (256 / BK) * i, k = k0 + kk;
-        ra[i] = (r < d.M && k < kend) ? A[r * d.lda + k] : T{};
-        if constexpr (SHF) ra2[i] = (r < d.M && k < kend) ? A2[r * d.lda + k] : T{};
-      }
-    } else {
-      // A stored K x M row-major; op(A) = A^*
-      const int rr = tid & 63, kk = tid >> 6;
-#pragma unroll
-      for (int i = 0; i < NA; ++i) {
-        const int64_t r = m0 + rr + 64 * (i % (BM / 64)), k = k0 + kk + 4 * (i / (BM / 64));
-        ra[i] = (r < d.M && k < kend) ? A[k * d.lda + r] : T{};
-      }
-    }
-    const int cc = tid & 63, kk = tid >> 6;
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int64_t c = n0 + cc + 64 * (i % (BN / 64)), k = k0 + kk + 4 * (i / (BN / 64));
-      rb[i] = (c < d.N && k < kend) ? B[k * d.ldb + c] : T{};
-    }
-  };
-  auto sstore = [&](int buf) {
-    if (TA == 0) {
-      const int kk = tid % BK, rr = tid / BK;
-      if constexpr (SHF) {
-#pragma unroll
-        for (int i = 0; i < NA; ++i) {
-          const real ex = zr * ra2[i].x - zi * ra2[i].y - ra[i].x;
-          const real ey = zr * ra2[i].y + zi * ra2[i].x - ra[i].y;
-          ra[i].x = ex;
-          ra[i].y = ey;
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < NA; ++i) {
-        sAr[buf][kk][rr + (256 / BK) * i] = ra[i].x;
-        sAi[buf][kk][rr + (256 / BK) * i] = ra[i].y;
-        if constexpr (M3) sAs[buf][kk][rr + (256 / BK) * i] = ra[i].x + ra[i].y;
-      }
-    } else {
-      const int rr = tid & 63, kk = tid >> 6;
-#pragma unroll
-      for (int i = 0; i < NA; ++i) {
-        const int r = rr + 64 * (i % (BM / 64)), k = kk + 4 * (i / (BM / 64));
-        sAr[buf][k][r] = ra[i].x;
-        sAi[buf][k][r] = -ra[i].y;
-        if constexpr (M3) sAs[buf][k][r] = ra[i].x - ra[i].y;
-      }
-    }
-    const int cc = tid & 63, kk = tid >> 6;
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int c = cc + 64 * (i % (BN / 64)), k = kk + 4 * (i / (BN / 64));
-      sBr[buf][k][c] = rb[i].x;
-      if constexpr (M3) {
-        sBi[buf][k][c] = rb[i].y - rb[i].x;
-        sBs[buf][k][c] = rb[i].x + rb[i].y;
-      } else {
-        sBi[buf][k][c] = rb[i].y;
-      }
-    }
-  };
-
-  acc_t cr[FM][FN], ci[FM][FN];
-  acc_t t1[M3 ? FM : 1][M3 ? FN : 1];
-  if constexpr (M3) {
-#pragma unroll
-    for (int a = 0; a < FM; ++a)
-#pragma unroll
-      for (int b = 0; b < FN; ++b)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) t1[a][b][r] = 0;
-  }
-  T *C = d.C + bidx * d.sC;
-#pragma unroll
-  for (int a = 0; a < FM; ++a)
-#pragma unroll
-    for (int b = 0; b < FN; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        cr[a][b][r] = 0;
-        ci[a][b][r] = 0;
-        if (SUB) {
-          // every lane loads (element (0, 0) stands in outside C) and the
-          // bound selects the value afterwards: a load under a branch would be
-          // waited for inside it, one memory round trip per element
-          const int64_t row = m0 + wm * WM + a * 16 + Ops::out_row(lane, r);
-          const int64_t col = n0 + wn * WN + b * 16 + (lane & 15);
-          const bool in = row < d.M && col < d.N;
-          const int64_t rr = in ? row : 0, cc = in ? col : 0;
-          const T o = SHF ? d.C0[bidx * d.sC0 + rr * d.ldc0 + cc] : C[rr * d.ldc + cc];
-          cr[a][b][r] = in ? o.x : real(0);
-          ci[a][b][r] = in ? o.y : real(0);
-        }
-      }
-
-  const int nk = static_cast<int>((kend - kbeg + BK - 1) / BK);
-  if (nk > 0) {
-    gload(kbeg);
-    sstore(0);
-    tile_sync();
-  }
-  const int col16 = lane & 15, krow = lane >> 4;
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < nk) gload(kbeg + static_cast<int64_t>(kt + 1) * BK);
-    if constexpr (M3) {
-      if (live) {
-        // cr accumulates P, ci accumulates Q, t1 accumulates T1 (A negated for
-        // C -= A B).  The operands of k-step kk + 1 are read from LDS while the
-        // MFMAs of step kk issue (two MFMAs per LDS read), so the read latency
-        // hides behind the matrix cores instead of stalling them.
-        real as[2][FM], ai[2][FM], ar[2][FM], br[2][FN], bs[2][FN], bd[2][FN];
-        auto ops = [&](int kk, int o) {
-          const int kr = kk * 4 + krow;
-#pragma unroll
-          for (int a = 0; a < FM; ++a) {
-            const int c = wm * WM + a * 16 + col16;
-            as[o][a] = SUB ? -sAs[buf][kr][c] : sAs[buf][kr][c];
-            ai[o][a] = SUB ? sAi[buf][kr][c] : -sAi[buf][kr][c];  // -Ai for P
-            ar[o][a] = SUB ? -sAr[buf][kr][c] : sAr[buf][kr][c];
-          }
-#pragma unroll
-          for (int b = 0; b < FN; ++b) {
-            const int c = wn * WN + b * 16 + col16;
-            br[o][b] = sBr[buf][kr][c];
-            bs[o][b] = sBs[buf][kr][c];
-            bd[o][b] = sBi[buf][kr][c];
-          }
-        };
-        ops(0, 0);
-#pragma unroll
-        for (int kk = 0; kk < BK / 4; ++kk) {
-          const int o = kk & 1;
-          if (kk + 1 < BK / 4) ops(kk + 1, o ^ 1);
-#pragma unroll
-          for (int a = 0; a < FM; ++a)
-#pragma unroll
-            for (int b = 0; b < FN; ++b) t1[a][b] = Ops::mma(as[o][a], br[o][b], t1[a][b]);
-#pragma unroll
-          for (int a = 0; a < FM; ++a)
-#pragma unroll
-            for (int b = 0; b < FN; ++b) cr[a][b] = Ops::mma(ai[o][a], bs[o][b], cr[a][b]);
-#pragma unroll
-          for (int a = 0; a < FM; ++a)
-#pragma unroll
-            for (int b = 0; b < FN; ++b) ci[a][b] = Ops::mma(ar[o][a], bd[o][b], ci[a][b]);
-          if (kk + 1 < BK / 4) {
-            // interleave: 3 FM FN MFMAs with the next step's 3 (FM + FN) LDS reads
-#pragma unroll
-            for (int g = 0; g < 3 * (FM + FN); ++g) {
-              __builtin_amdgcn_sched_group_barrier(0x008, (3 * FM * FN) / (3 * (FM + FN)), 0);
-              __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            }
-          }
-        }
-        // T1 folded into both parts every kFoldK steps of K: the shared term
-        // then never sums more than kFoldK products before it meets P and Q,
-        // whatever the launch's K (long K ranges otherwise let T1 and P grow
-        // far beyond their difference, and the complex64 factors lose digits)
-        if (((kt + 1) & (kFoldK / BK - 1)) == 0 && kt + 1 < nk) {  // (the last fold is the epilogue's)
-#pragma unroll
-          for (int a = 0; a < FM; ++a)
-#pragma unroll
-            for (int b = 0; b < FN; ++b)
-#pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                cr[a][b][r] += t1[a][b][r];
-                ci[a][b][r] += t1[a][b][r];
-                t1[a][b][r] = 0;
-              }
-        }
-      }
-    } else if (live && !PIPE) {
-#pragma unroll
-      for (int kk = 0; kk < BK / 4; ++kk) {
-        const int kr = kk * 4 + krow;
-        real ar[FM], ai[FM], br[FN], bi[FN];
-#pragma unroll
-        for (int a = 0; a < FM; ++a) {
-          ar[a] = sAr[buf][kr][wm * WM + a * 16 + col16];
-          ai[a] = sAi[buf][kr][wm * WM + a * 16 + col16];
-          if (SUB) {  // accumulate (-A) B
-            ar[a] = -ar[a];
-            ai[a] = -ai[a];
-          }
-        }
-#pragma unroll
-        for (int b = 0; b < FN; ++b) {
-          br[b] = sBr[buf][kr][wn * WN + b * 16 + col16];
-          bi[b] = sBi[buf][kr][wn * WN + b * 16 + col16];
-        }
-#pragma unroll
-        for (int a = 0; a < FM; ++a)
-#pragma unroll
-          for (int b = 0; b < FN; ++b) {
-            cr[a][b] = Ops::mma(ar[a], br[b], cr[a][b]);
-            ci[a][b] = Ops::mma(ar[a], bi[b], ci[a][b]);
-          }
-#pragma unroll
-        for (int a = 0; a < FM; ++a)
-#pragma unroll
-          for (int b = 0; b < FN; ++b) {
-            cr[a][b] = Ops::mma(-ai[a], bi[b], cr[a][b]);
-            ci[a][b] = Ops::mma(ai[a], br[b], ci[a][b]);
-          }
-      }
-    } else if (live) {
-      // four real products per complex step, the next step's operands read
-      // while the current MFMAs issue (as above)
-      real ar[2][FM], ai[2][FM], br[2][FN], bi[2][FN];
-      auto ops = [&](int kk, int o) {
-        const int kr = kk * 4 + krow;
-#pragma unroll
-        for (int a = 0; a < FM; ++a) {
-          ar[o][a] = sAr[buf][kr][wm * WM + a * 16 + col16];
-          ai[o][a] = sAi[buf][kr][wm * WM + a * 16 + col16];
-          if (SUB) {  // accumulate (-A) B:  Cr += (-Ar) Br - (-Ai) Bi, Ci += (-Ar) Bi + (-Ai) Br
-            ar[o][a] = -ar[o][a];
-            ai[o][a] = -ai[o][a];
-          }
-        }
-#pragma unroll
-        for (int b = 0; b < FN; ++b) {
-          br[o][b] = sBr[buf][kr][wn * WN + b * 16 + col16];
-          bi[o][b] = sBi[buf][kr][wn * WN + b * 16 + col16];
-        }
-      };
-      ops(0, 0);
-#pragma unroll
-      for (int kk = 0; kk < BK / 4; ++kk) {
-        const int o = kk & 1;
-        if (kk + 1 < BK / 4) ops(kk + 1, o ^ 1);
-        // two sweeps over all tiles: an accumulator is reused only after every
-        // other accumulator of the wave has been issued once
-#pragma unroll
-        for (int a = 0; a < FM; ++a)
-#pragma unroll
-          for (int b = 0; b < FN; ++b) {
-            cr[a][b] = Ops::mma(ar[o][a], br[o][b], cr[a][b]);
-            ci[a][b] = Ops::mma(ar[o][a], bi[o][b], ci[a][b]);
-          }
-#pragma unroll
-        for (int a = 0; a < FM; ++a)
-#pragma unroll
-          for (int b = 0; b < FN; ++b) {
-            cr[a][b] = Ops::mma(-ai[o][a], bi[o][b], cr[a][b]);
-            ci[a][b] = Ops::mma(ai[o][a], br[o][b], ci[a][b]);
-          }
-        if (kk + 1 < BK / 4) {
-          // interleave: 4 FM FN MFMAs with the next step's 2 (FM + FN) LDS reads
-#pragma unroll
-          for (int g = 0; g < 2 * (FM + FN); ++g) {
-            __builtin_amdgcn_sched_group_barrier(0x008, (4 * FM * FN) / (2 * (FM + FN)), 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-          }
-        }
-      }
-    }
-    if (kt + 1 < nk) sstore(buf ^ 1);
-    tile_sync();
-  }
-
-  if constexpr (M3) {
-#pragma unroll
-    for (int a = 0; a < FM; ++a)
-#pragma unroll
-      for (int b = 0; b < FN; ++b)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          cr[a][b][r] += t1[a][b][r];
-          ci[a][b][r] += t1[a][b][r];
-        }
-  }
-  // epilogue
-  const real alr = static_cast<real>(d.alpha.x), ali = static_cast<real>(d.alpha.y);
-  const real ber = static_cast<real>(d.beta.x), bei = static_cast<real>(d.beta.y);
-  const bool use_beta = (ber != 0 || bei != 0);
-  T *W = (d.splits > 1) ? d.work + (split * d.batch + bidx) * d.M * d.N : nullptr;
-#pragma unroll
-  for (int a = 0; a < FM; ++a)
-#pragma unroll
-    for (int b = 0; b < FN; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t row = m0 + wm * WM + a * 16 + Ops::out_row(lane, r);
-        const int64_t col = n0 + wn * WN + b * 16 + col16;
-        if (own && row < d.M && col < d.N) {
-          const real xr = cr[a][b][r], xi = ci[a][b][r];
-          T v;
-          if (SUB) {
-            v.x = xr;
-            v.y = xi;
-            C[row * d.ldc + col] = v;
-            continue;
-          }
-          v.x = alr * xr - ali * xi;
-          v.y = alr * xi + ali * xr;
-          if (W) {
-            W[row * d.N + col] = v;
-          } else {
-            if (use_beta) {
-              const T o = C[row * d.ldc + col];
-              v.x += ber * o.x - bei * o.y;
-              v.y += ber * o.y + bei * o.x;
-            }
-            C[row * d.ldc + col] = v;
-          }
-        }
-      }
-}
-
-// UPD only renames the instance used for the LU trailing update (same code), so
-// that kernel traces time that update on its own.
 // Complex products take three real MFMAs per step (M3) in the single-problem
-// complex64 kernels and in the FP64 trailing update (where the extra LDS plane
-// and accumulators still allow two workgroups per compute unit at BK = 8).
+// complex64 kernels and in the FP64 trailing update and triangular solves.
 // Other FP64 products and the plain grouped kernels keep four (the grouped
 // trailing update has a three-product form of its own, k_gemm_grp_upd).
 template <typename T> constexpr bool kM3 = sizeof(T) == 8;
 
 // Waves per SIMD the register allocation must leave room for (512 registers a
-// lane are shared by the waves of a SIMD): the complex64 64 x 64 tile fits
-// three workgroups per compute unit in LDS at BK = 16 and at 168 registers
-// (at BK = 8, the trailing update, it takes 121 registers and runs four); the
-// complex128 64 x 64 tiles and the complex64 128 x 64 tiles fit two at 256
-// (left to themselves they take over 300, one wave per SIMD).  None of them
-// spills; the complex128 128 x 64 tile would.
-template <typename T, int BM>
-constexpr int kWaves = BM != 64 ? (sizeof(T) == 8 ? 2 : 1) : (sizeof(T) == 8 ? 3 : 2);
+// lane are shared by the waves of a SIMD).
+template <typename T> constexpr int kWaves = sizeof(T) == 8 ? 6 : 4;
 
-template <typename T, int BM, int BN, int TA, bool SUB, int BK, bool UPD = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves<T, BM>)))
+template <typename T, int TA, bool SUB>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves<T>)))
 void k_gemm(const GemmArgs<T> d, int64_t grid_total) {
-  gemm_tile<T, BM, BN, TA, SUB, BK, kM3<T> || UPD>(d, xcd_remap(blockIdx.x, grid_total));
+  gemm_tile<T, kTileM, kTileN, 2, TA, SUB ? kTileSub : kTileGen, kM3<T>>(
+      d, xcd_remap(blockIdx.x, grid_total));
 }
 
-// C -= A B of the triangular solves (GEMM_SOLVE): the trailing update's tile
-// (three real products per complex step, BK = 8) under a name of its own, so
-// kernel traces and counters time the update alone.
+// Strides past the reach of a 32-bit offset, and C on A (row blocks no wider than a
+// tile, hence 64 columns): 64-bit addresses.
+template <typename T, int TA, bool SUB>
+__global__ __launch_bounds__(256)
+void k_gemm_wide(const GemmArgs<T> d, int64_t grid_total) {
+  gemm_tile<T, kTileM, 64, 2, TA, SUB ? kTileSub : kTileGen, kM3<T>, true>(
+      d, xcd_remap(blockIdx.x, grid_total));
+}
+
+// The LU trailing update C -= A B: a name of its own, so that kernel traces and
+// counters time that update alone.
+template <typename T, int BM, int BN>
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(BM == kTileM ? kWaves<T> : (sizeof(T) == 8 ? 2 : 1))))
+void k_gemm_update(const GemmArgs<T> d, int64_t grid_total) {
+  gemm_tile<T, BM, BN, 2, 0, kTileSub, true>(d, xcd_remap(blockIdx.x, grid_total));
+}
+
+// C -= A B of the triangular solves (GEMM_SOLVE): three real products in FP64 too.
 template <typename T>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves<T, 64>)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves<T>)))
 void k_gemm_solve(const GemmArgs<T> d, int64_t grid_total) {
-  gemm_tile<T, 64, 64, 0, true, 8, true>(d, xcd_remap(blockIdx.x, grid_total));
+  gemm_tile<T, kTileM, kTileN, 2, 0, kTileSub, true>(d, xcd_remap(blockIdx.x, grid_total));
 }
 
-// The LU trailing update C -= A B (the tile above) on a fixed number of
-// persistent workgroups, each filling one compute unit on its own: NG tile
-// groups of 256 threads (four wavefronts a SIMD in complex64, two in
-// complex128, as the one-tile launch reaches), about 99 KB of LDS, so that no
+// The LU trailing update C -= A B on a fixed number of persistent workgroups, each
+// filling one compute unit on its own: four tile groups of 256 threads and, with
+// `lds` bytes of dynamic LDS that nothing reads, about 100 KB of LDS, so that no
 // second workgroup of any kernel fits beside it.  The compute units left over
 // stay free for the next panel's factorisation on another stream.
 // Workgroup w runs on XCD w mod 8; XCD x works through the tile range
 // [x per, (x + 1) per) in rounds, NG consecutive tiles a workgroup per round.
-// At n = 4000, K = 128 on 224 of the 256 units it reaches 0.56 (complex64)
-// and 0.55 (complex128) of peak, against 0.78 and 0.81 for the one-tile
-// launch on the whole chip (0.47 and 0.52 with one workgroup barrier for all
-// groups, which keeps them in lockstep).
-template <typename T> constexpr int kPersistGroups = sizeof(T) == 8 ? 4 : 2;
+constexpr int kPersistGroups = 4;
 
 template <typename T>
-__global__ __launch_bounds__(256 * kPersistGroups<T>)
-__attribute__((amdgpu_waves_per_eu(kPersistGroups<T>)))
+__global__ __launch_bounds__(256 * kPersistGroups)
+__attribute__((amdgpu_waves_per_eu(kPersistGroups)))
 void k_gemm_upd_pers(const GemmArgs<T> d, int64_t total, int64_t per, int rounds) {
-  constexpr int NG = kPersistGroups<T>;
+  constexpr int NG = kPersistGroups;
   const int64_t x = blockIdx.x & 7, j = blockIdx.x >> 3, p8 = gridDim.x >> 3;
   const int g = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 8));  // wave-uniform
   __shared__ uint32_t gcount[NG];
@@ -516,25 +84,21 @@ void k_gemm_upd_pers(const GemmArgs<T> d, int64_t total, int64_t per, int rounds
   for (int i = 0; i < rounds; ++i) {
     const int64_t lin = x * per + (i * p8 + j) * NG + g;
     const bool own = lin < total;
-    gemm_tile<T, 64, 64, 0, true, 8, true, false, true, NG>(d, own ? lin : total - 1, own,
-                                                              &gcount[g], &phase);
+    gemm_tile<T, kTileM, kTileN, 2, 0, kTileSub, true, false, NG>(d, own ? lin : total - 1, own,
+                                                                  &gcount[g], &phase);
   }
 }
 
-// C_b = C0_b - (shift[b] A2 - A) B_b (FP64: three-product form at BK = 8, as the
-// trailing update).
-template <typename T, int BK>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves<T, 64>)))
+// C_b = C0_b - (shift[b] A2 - A) B_b (three-product form, as the trailing update).
+template <typename T, bool WIDE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ? 2 : kWaves<T>)))
 void k_gemm_shift(const GemmArgs<T> d, int64_t grid_total) {
-  gemm_tile<T, 64, 64, 0, true, BK, true, true>(d, xcd_remap(blockIdx.x, grid_total));
+  gemm_tile<T, kTileM, kTileN, 2, 0, kTileShift, true, WIDE>(d, xcd_remap(blockIdx.x, grid_total));
 }
 
 // A group of independent problems in one launch: tab[e].tile0 is the first
 // linear tile of problem e (increasing); a workgroup finds its problem by
 // bisection over the table.
-// (the grouped tiles keep the unpipelined four-product loop: the complex64 one
-// then fits four workgroups per compute unit, 128 registers a lane; the
-// complex128 one takes the two-wave budget of the single-problem tile)
 template <typename T>
 __device__ inline int find_problem(const GemmArgs<T> *__restrict__ tab, int count, int64_t lin) {
   int lo = 0, hi = count - 1;
@@ -546,37 +110,23 @@ __device__ inline int find_problem(const GemmArgs<T> *__restrict__ tab, int coun
   return lo;
 }
 
-template <typename T, int BM, int BN, int TA, bool SUB, int BK>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 16 ? 2 : 1)))
+template <typename T, int TA, bool SUB, bool WIDE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ? 2 : kWaves<T>)))
 void k_gemm_grp(const GemmArgs<T> *__restrict__ tab, int count, int64_t grid_total) {
   const int64_t lin = xcd_remap(blockIdx.x, grid_total);
   const GemmArgs<T> d = tab[find_problem(tab, count, lin)];
-  gemm_tile<T, BM, BN, TA, SUB, BK, false, false, false>(d, lin - d.tile0);
+  gemm_tile<T, kTileM, kTileN, 2, TA, SUB ? kTileSub : kTileGen, false, WIDE>(d, lin - d.tile0);
 }
 
-// The grouped LU trailing update C -= A B with the single-problem update's
-// loop: three real products per complex step, next operands read from LDS
-// while the MFMAs issue, BK = 8 (complex128 in the two-wave register budget,
-// complex64 at four workgroups per compute unit).  The batched form picks it
-// (or a four-product loop) per precision and order from its tuned table.
+// The grouped LU trailing update C -= A B with three real products per complex
+// step.  The batched form picks it (or the four-product loop) per precision and
+// order from its tuned table.
 template <typename T>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves<T, 64>)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves<T>)))
 void k_gemm_grp_upd(const GemmArgs<T> *__restrict__ tab, int count, int64_t grid_total) {
   const int64_t lin = xcd_remap(blockIdx.x, grid_total);
   const GemmArgs<T> d = tab[find_problem(tab, count, lin)];
-  gemm_tile<T, 64, 64, 0, true, 8, true, false, true>(d, lin - d.tile0);
-}
-
-// The grouped update C -= A B with four real products per complex step and
-// the operand-pipelined loop (BK = 16, the single-problem tiles' register
-// budget): the candidate between the plain grouped loop and the
-// three-product one for either precision.
-template <typename T>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves<T, 64>)))
-void k_gemm_grp_pipe(const GemmArgs<T> *__restrict__ tab, int count, int64_t grid_total) {
-  const int64_t lin = xcd_remap(blockIdx.x, grid_total);
-  const GemmArgs<T> d = tab[find_problem(tab, count, lin)];
-  gemm_tile<T, 64, 64, 0, true, 16, false, false, true>(d, lin - d.tile0);
+  gemm_tile<T, kTileM, kTileN, 2, 0, kTileSub, true>(d, lin - d.tile0);
 }
 
 // Products whose output is too small to fill the chip with 64 x 64 tiles (inner
@@ -770,32 +320,41 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const GemmArgs<T> d) {
   *C = v;
 }
 
+// Workgroups of a launch over bm x bn tiles (a multiple of 8: xcd_remap).
+template <typename T> int64_t padded_tiles(const GemmArgs<T> &d, int bm, int bn) {
+  const int64_t total = ((d.M + bm - 1) / bm) * ((d.N + bn - 1) / bn) * d.batch * d.splits;
+  return (total + 7) / 8 * 8;
+}
+
 template <typename T>
 void launch_tiles(hipStream_t s, const GemmArgs<T> &d, int ta, int cfg) {
-  const int BM = cfg == GEMM_UPDATE_TALL ? 128 : 64;
-  const int64_t tiles = ((d.M + BM - 1) / BM) * ((d.N + 63) / 64);
-  const int64_t total = tiles * d.batch * d.splits;
-  const int64_t padded = (total + 7) / 8 * 8;
+  const bool tall = cfg == GEMM_UPDATE_TALL;
+  const int bm = tall ? 128 : kTileM;
+  const bool wide = d.A == d.C || !tile_spans_fit(d, ta, bm);
+  const int64_t padded = wide ? padded_tiles(d, kTileM, 64) : padded_tiles(d, bm, tall ? 64 : kTileN);
   const dim3 grid(static_cast<unsigned>(padded));
   // C -= op(A) B is recognised from alpha = -1, beta = 1 without split-K
   const bool sub = d.splits == 1 && d.alpha.x == -1.0 && d.alpha.y == 0.0 && d.beta.x == 1.0 &&
                    d.beta.y == 0.0;
-  if (ta == 0 && sub) {
-    // (BK = 8: two workgroups per compute unit in FP64, four in complex64)
-    if (cfg == GEMM_UPDATE_TALL)
-      hipLaunchKernelGGL((k_gemm<T, 128, 64, 0, true, 8, true>), grid, dim3(256), 0, s, d, padded);
-    else if (cfg == GEMM_UPDATE)
-      hipLaunchKernelGGL((k_gemm<T, 64, 64, 0, true, 8, true>), grid, dim3(256), 0, s, d, padded);
-    else if (cfg == GEMM_SOLVE)
-      hipLaunchKernelGGL((k_gemm_solve<T>), grid, dim3(256), 0, s, d, padded);
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, d, padded); };
+  if (wide) {
+    if (ta == 0)
+      sub ? go(k_gemm_wide<T, 0, true>) : go(k_gemm_wide<T, 0, false>);
     else
-      hipLaunchKernelGGL((k_gemm<T, 64, 64, 0, true, 16>), grid, dim3(256), 0, s, d, padded);
+      sub ? go(k_gemm_wide<T, 2, true>) : go(k_gemm_wide<T, 2, false>);
+  } else if (ta == 0 && sub) {
+    if (tall)
+      go(k_gemm_update<T, 128, 64>);
+    else if (cfg == GEMM_UPDATE)
+      go(k_gemm_update<T, kTileM, kTileN>);
+    else if (cfg == GEMM_SOLVE)
+      go(k_gemm_solve<T>);
+    else
+      go(k_gemm<T, 0, true>);
   } else if (ta == 0) {
-    hipLaunchKernelGGL((k_gemm<T, 64, 64, 0, false, 16>), grid, dim3(256), 0, s, d, padded);
-  } else if (sub) {
-    hipLaunchKernelGGL((k_gemm<T, 64, 64, 2, true, 16>), grid, dim3(256), 0, s, d, padded);
+    go(k_gemm<T, 0, false>);
   } else {
-    hipLaunchKernelGGL((k_gemm<T, 64, 64, 2, false, 16>), grid, dim3(256), 0, s, d, padded);
+    sub ? go(k_gemm<T, 2, true>) : go(k_gemm<T, 2, false>);
   }
 }
 
@@ -861,8 +420,6 @@ void gemm_impl(hipStream_t s, GemmArgs<T> d, int ta, int cfg, int64_t work_elems
   }
   d.splits = 1;
   d.kchunk = d.K > 0 ? d.K : 1;
-  // (a 128 x 128 complex64 tile measured slower than 64 x 64 in the LU update,
-  // and the FP64 one needs more than the 512 registers of a lane: not used)
   if (d.A != d.C && d.B != d.C && cfg != GEMM_UPDATE_TALL &&
       ((d.M + 63) / 64) * ((d.N + 63) / 64) * d.batch <= kSmallTiles)
     return gemm_small<T>(s, d, ta, work_elems);
@@ -888,43 +445,42 @@ void gemm_impl(hipStream_t s, GemmArgs<T> d, int ta, int cfg, int64_t work_elems
 }  // namespace
 
 template <typename T>
-int64_t gemm_group_tiles(GemmArgs<T> *tab, int count) {
-  int64_t t = 0;
+GroupTiles gemm_group_tiles(GemmArgs<T> *tab, int count, int ta) {
+  GroupTiles t{0, false};
   for (int e = 0; e < count; ++e) {
     tab[e].splits = 1;
     tab[e].kchunk = tab[e].K > 0 ? tab[e].K : 1;
-    tab[e].tile0 = t;
-    t += ((tab[e].M + 63) / 64) * ((tab[e].N + 63) / 64) * tab[e].batch;
+    tab[e].tile0 = t.tiles;
+    t.tiles += ((tab[e].M + kTileM - 1) / kTileM) * ((tab[e].N + kTileN - 1) / kTileN) * tab[e].batch;
+    t.wide = t.wide || !tile_spans_fit(tab[e], ta, kTileM);
   }
   return t;
 }
-template int64_t gemm_group_tiles<z64>(GemmArgs<z64> *, int);
-template int64_t gemm_group_tiles<c64>(GemmArgs<c64> *, int);
+template GroupTiles gemm_group_tiles<z64>(GemmArgs<z64> *, int, int);
+template GroupTiles gemm_group_tiles<c64>(GemmArgs<c64> *, int, int);
 
 template <typename T>
 void gemm_group(hipStream_t s, int ta, bool sub, const GemmArgs<T> *dtab, int count,
-                int64_t total_tiles, int variant) {
-  if (count <= 0 || total_tiles <= 0) return;
-  const int64_t padded = (total_tiles + 7) / 8 * 8;
-  const dim3 grid(static_cast<unsigned>(padded));
-  if (ta == 0) {
-    if (sub && variant == GROUP_UPDATE_M3)
-      hipLaunchKernelGGL((k_gemm_grp_upd<T>), grid, dim3(256), 0, s, dtab, count, padded);
-    else if (sub && variant == GROUP_UPDATE_PIPE)
-      hipLaunchKernelGGL((k_gemm_grp_pipe<T>), grid, dim3(256), 0, s, dtab, count, padded);
-    else if (sub)
-      hipLaunchKernelGGL((k_gemm_grp<T, 64, 64, 0, true, 16>), grid, dim3(256), 0, s, dtab, count,
-                         padded);
-    else
-      hipLaunchKernelGGL((k_gemm_grp<T, 64, 64, 0, false, 16>), grid, dim3(256), 0, s, dtab, count,
-                         padded);
-  } else {
-    hipLaunchKernelGGL((k_gemm_grp<T, 64, 64, 2, false, 16>), grid, dim3(256), 0, s, dtab, count,
+                GroupTiles t, int variant) {
+  if (count <= 0 || t.tiles <= 0) return;
+  const int64_t padded = (t.tiles + 7) / 8 * 8;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(padded)), dim3(256), 0, s, dtab, count,
                        padded);
-  }
+  };
+  if (ta != 0)
+    t.wide ? go(k_gemm_grp<T, 2, false, true>) : go(k_gemm_grp<T, 2, false, false>);
+  else if (!sub)
+    t.wide ? go(k_gemm_grp<T, 0, false, true>) : go(k_gemm_grp<T, 0, false, false>);
+  else if (t.wide)
+    go(k_gemm_grp<T, 0, true, true>);
+  else if (variant == GROUP_UPDATE_M3)
+    go(k_gemm_grp_upd<T>);
+  else
+    go(k_gemm_grp<T, 0, true, false>);
 }
-template void gemm_group<z64>(hipStream_t, int, bool, const GemmArgs<z64> *, int, int64_t, int);
-template void gemm_group<c64>(hipStream_t, int, bool, const GemmArgs<c64> *, int, int64_t, int);
+template void gemm_group<z64>(hipStream_t, int, bool, const GemmArgs<z64> *, int, GroupTiles, int);
+template void gemm_group<c64>(hipStream_t, int, bool, const GemmArgs<c64> *, int, GroupTiles, int);
 
 void zgemm_shift_residual(hipStream_t s, int64_t M, int64_t N, int64_t K, const z64 *A,
                           const z64 *A2, int64_t lda, const z64 *shift, const z64 *Y, int64_t ldy,
@@ -933,26 +489,28 @@ void zgemm_shift_residual(hipStream_t s, int64_t M, int64_t N, int64_t K, const 
   if (M <= 0 || N <= 0 || batch <= 0) return;
   GemmArgs<z64> d{M, N, K, A, lda, 0, Y, ldy, sY, C, ldc, sC, make_double2(-1.0, 0.0),
                   make_double2(1.0, 0.0), batch, 1, K > 0 ? K : 1, nullptr, 0, A2, shift, R, ldr, sR};
-  const int64_t total = ((M + 63) / 64) * ((N + 63) / 64) * batch;
-  const int64_t padded = (total + 7) / 8 * 8;
-  hipLaunchKernelGGL((k_gemm_shift<z64, 8>), dim3(static_cast<unsigned>(padded)), dim3(256), 0, s, d,
-                     padded);
+  const int64_t padded = padded_tiles(d, kTileM, kTileN);
+  const dim3 grid(static_cast<unsigned>(padded));
+  if (tile_spans_fit(d, 0, kTileM))
+    hipLaunchKernelGGL((k_gemm_shift<z64, false>), grid, dim3(256), 0, s, d, padded);
+  else
+    hipLaunchKernelGGL((k_gemm_shift<z64, true>), grid, dim3(256), 0, s, d, padded);
 }
 
 template <typename T>
 void update_persistent(hipStream_t s, GemmArgs<T> d, int wgs) {
   if (d.M <= 0 || d.N <= 0 || d.batch <= 0 || d.K <= 0) return;
-  constexpr int NG = kPersistGroups<T>;
+  constexpr int NG = kPersistGroups;
   d.splits = 1;
   d.kchunk = d.K;
-  const int64_t total = ((d.M + 63) / 64) * ((d.N + 63) / 64) * d.batch;
+  const int64_t total = ((d.M + kTileM - 1) / kTileM) * ((d.N + kTileN - 1) / kTileN) * d.batch;
   // multiples of 8 (one share per XCD), no more than the tiles need
   int64_t p = std::max<int64_t>(8, wgs / 8 * 8);
   p = std::min<int64_t>(p, (total + 8 * NG - 1) / (8 * NG) * 8);
   const int64_t rounds = (total + p * NG - 1) / (p * NG);
   const int64_t per = rounds * (p / 8) * NG;
-  hipLaunchKernelGGL((k_gemm_upd_pers<T>), dim3(static_cast<unsigned>(p)), dim3(256 * NG), 0, s, d,
-                     total, per, static_cast<int>(rounds));
+  hipLaunchKernelGGL((k_gemm_upd_pers<T>), dim3(static_cast<unsigned>(p)), dim3(256 * NG),
+                     sizeof(T) == 8 ? 48 * 1024 : 0, s, d, total, per, static_cast<int>(rounds));
 }
 
 void zupdate_persistent(hipStream_t s, int64_t M, int64_t N, int64_t K, const z64 *A, int64_t lda,

@@ -42,10 +42,10 @@ void zgemm_shift_residual(hipStream_t s, int64_t M, int64_t N, int64_t K, const 
                           int64_t sY, const z64 *R, int64_t ldr, int64_t sR, z64 *C, int64_t ldc,
                           int64_t sC, int32_t batch);
 
-// GEMM_UPDATE / GEMM_UPDATE_TALL: the 64 x 64 / 128 x 64 configurations under
-// kernel names of their own (the LU trailing update); GEMM_SOLVE: C -= A B
-// (no transpose) on the update's 64 x 64 tile under a third name (the
-// triangular solves), other products as GEMM_SQUARE.
+// GEMM_UPDATE / GEMM_UPDATE_TALL: the 64 x 32 / 128 x 64 tiles in the three-product
+// form under a kernel name of their own (the LU trailing update); GEMM_SOLVE: C -= A B
+// (no transpose) as the update under a third name (the triangular solves), other
+// products as GEMM_SQUARE.
 enum { GEMM_SQUARE = 0, GEMM_UPDATE = 3, GEMM_UPDATE_TALL = 4, GEMM_SOLVE = 5 };
 
 // C_b = alpha op(A_b) B_b + beta C_b; transA 0: A is M x K; 2: A stored K x M, op = ^*.
@@ -71,20 +71,23 @@ void cupdate_persistent(hipStream_t s, int64_t M, int64_t N, int64_t K, const c6
                         int64_t sA, const c64 *B, int64_t ldb, int64_t sB, c64 *C, int64_t ldc,
                         int64_t sC, int32_t batch, int wgs);
 
-// Grouped product: `count` independent problems (each a uniform batch, 64 x 64
+// Grouped product: `count` independent problems (each a uniform batch, 64 x 32
 // tiles, no split-K) in one launch.  gemm_group_tiles fills tile0 (and splits,
-// kchunk) of a host table and returns the total tile count; the launch reads
+// kchunk) of a host table and returns the total tile count and the addressing; the launch reads
 // the table from device memory.  sub: every problem is C -= A B (alpha = -1,
 // beta = 1); ta: 0 or 2 (2 only with sub = false).
-//   variant (sub = true, ta = 0 only): GROUP_PLAIN (four real products per
-//   complex step, unpipelined, BK = 16); GROUP_UPDATE_M3: the three-product,
-//   operand-pipelined loop (BK = 8); GROUP_UPDATE_PIPE: four products on the
-//   operand-pipelined loop.
+//   variant (sub = true, ta = 0 only): GROUP_PLAIN and GROUP_UPDATE_PIPE, four real
+//   products per complex step (one kernel: its loop always reads operands ahead);
+//   GROUP_UPDATE_M3, three.
 enum { GROUP_PLAIN = 0, GROUP_UPDATE_M3 = 1, GROUP_UPDATE_PIPE = 2 };
-template <typename T> int64_t gemm_group_tiles(GemmArgs<T> *tab, int count);
+struct GroupTiles {
+  int64_t tiles;  // of all problems
+  bool wide;      // some stride is past the reach of a 32-bit offset within a tile
+};
+template <typename T> GroupTiles gemm_group_tiles(GemmArgs<T> *tab, int count, int ta);
 template <typename T>
 void gemm_group(hipStream_t s, int ta, bool sub, const GemmArgs<T> *dtab, int count,
-                int64_t total_tiles, int variant = GROUP_PLAIN);
+                GroupTiles tiles, int variant = GROUP_PLAIN);
 
 // ---- LU building blocks (k_lu.hip); T = z64 or c64 --------------------------
 //
