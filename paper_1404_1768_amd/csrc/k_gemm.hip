@@ -27,12 +27,12 @@ template <typename T> constexpr bool kM3 = sizeof(T) == 8;
 
 // Waves per SIMD the register allocation must leave room for (512 registers a
 // lane are shared by the waves of a SIMD).
-template <typename T> constexpr int kWaves = sizeof(T) == 8 ? 6 : 4;
+template <typename T, int BN = kTileN> constexpr int kWaves = sizeof(T) == 8 && BN == kTileN ? 6 : 4;
 
-template <typename T, int TA, bool SUB>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves<T>)))
+template <typename T, int TA, bool SUB, int BN = kTileN>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves<T, BN>)))
 void k_gemm(const GemmArgs<T> d, int64_t grid_total) {
-  gemm_tile<T, kTileM, kTileN, 2, TA, SUB ? kTileSub : kTileGen, kM3<T>>(
+  gemm_tile<T, kTileM, BN, 2, TA, SUB ? kTileSub : kTileGen, kM3<T>>(
       d, xcd_remap(blockIdx.x, grid_total));
 }
 
@@ -49,7 +49,7 @@ void k_gemm_wide(const GemmArgs<T> d, int64_t grid_total) {
 // counters time that update alone.
 template <typename T, int BM, int BN>
 __global__ __launch_bounds__(256)
-__attribute__((amdgpu_waves_per_eu(BM == kTileM ? kWaves<T> : (sizeof(T) == 8 ? 2 : 1))))
+__attribute__((amdgpu_waves_per_eu(BM == kTileM ? kWaves<T, BN> : (sizeof(T) == 8 ? 2 : 1))))
 void k_gemm_update(const GemmArgs<T> d, int64_t grid_total) {
   gemm_tile<T, BM, BN, 2, 0, kTileSub, true>(d, xcd_remap(blockIdx.x, grid_total));
 }
@@ -326,16 +326,28 @@ template <typename T> int64_t padded_tiles(const GemmArgs<T> &d, int bm, int bn)
   return (total + 7) / 8 * 8;
 }
 
+// complex64 C -= A B takes 64 x 64 tiles unless padding N to their width costs more
+// than they save: long launches on data with full mantissas run at the chip's power
+// limit, where the wider tile's fewer LDS and operand reads per product count (3744 x
+// 3744 x 256, 16 matrices: 148 -> 160 TFLOP/s; on data of few bits, below the limit,
+// both 170; 160 columns on 192: 146 -> 130).  complex128: 80 and 81, the narrow one kept.
+template <typename T> constexpr int kSubN = sizeof(T) == 8 ? 64 : kTileN;  // the wider one
+template <typename T> int sub_tile_n(int64_t N) {
+  const int64_t narrow = (N + kTileN - 1) / kTileN * kTileN, wide = (N + 63) / 64 * 64;
+  return 15 * wide <= 16 * narrow ? kSubN<T> : kTileN;
+}
+
 template <typename T>
 void launch_tiles(hipStream_t s, const GemmArgs<T> &d, int ta, int cfg) {
   const bool tall = cfg == GEMM_UPDATE_TALL;
   const int bm = tall ? 128 : kTileM;
   const bool wide = d.A == d.C || !tile_spans_fit(d, ta, bm);
-  const int64_t padded = wide ? padded_tiles(d, kTileM, 64) : padded_tiles(d, bm, tall ? 64 : kTileN);
-  const dim3 grid(static_cast<unsigned>(padded));
   // C -= op(A) B is recognised from alpha = -1, beta = 1 without split-K
   const bool sub = d.splits == 1 && d.alpha.x == -1.0 && d.alpha.y == 0.0 && d.beta.x == 1.0 &&
                    d.beta.y == 0.0;
+  const int bn = wide || tall ? 64 : ta == 0 && sub ? sub_tile_n<T>(d.N) : kTileN;
+  const int64_t padded = padded_tiles(d, wide ? kTileM : bm, bn);
+  const dim3 grid(static_cast<unsigned>(padded));
   auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, d, padded); };
   if (wide) {
     if (ta == 0)
@@ -346,11 +358,11 @@ void launch_tiles(hipStream_t s, const GemmArgs<T> &d, int ta, int cfg) {
     if (tall)
       go(k_gemm_update<T, 128, 64>);
     else if (cfg == GEMM_UPDATE)
-      go(k_gemm_update<T, kTileM, kTileN>);
+      bn == kTileN ? go(k_gemm_update<T, kTileM, kTileN>) : go(k_gemm_update<T, kTileM, kSubN<T>>);
     else if (cfg == GEMM_SOLVE)
       go(k_gemm_solve<T>);
     else
-      go(k_gemm<T, 0, true>);
+      bn == kTileN ? go(k_gemm<T, 0, true>) : go(k_gemm<T, 0, true, kSubN<T>>);
   } else if (ta == 0) {
     go(k_gemm<T, 0, false>);
   } else {
