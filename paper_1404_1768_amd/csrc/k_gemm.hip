@@ -388,16 +388,17 @@ template <typename T> void launch_splitk_reduce(hipStream_t s, const GemmArgs<T>
                      s, d);
 }
 
-// Products of at most kSmallTiles 64 x 64 output tiles (no more than compute
-// units: each unit would run one 64 x 64 workgroup at most) take k_gemm_ks; above, the 64 x 64 tiles read less per flop and are as fast or
-// faster (512 tiles, K = 128: 42 us against 46; 1024 tiles, K = 40: 42 against
-// 58).  In-place products (C is A or B) need one workgroup per column block and
-// keep the 64 x 64 tiles.  Sixteen wavefronts while that leaves units idle
+// Products of fewer than kSmallTiles output tiles (two a compute unit) take k_gemm_ks;
+// from there on the tiles read less per flop and are as fast or faster (complex128, us:
+// 1000 x 1000 x 100 and 8 x 1000 x 128 x 128, 512 tiles each, 24 -> 20 and 28 -> 23;
+// below, 2 x 2000 x 160 x 1000, 320 tiles, 98 against 136).  In-place products (C is A
+// or B) need one workgroup per column block and keep the tiles.  Sixteen wavefronts
+// while that leaves units idle
 // (157 x 157 x 4001, 100 tiles: 41 us against 46 with eight); 32 x 16 tiles for
 // many tiles, where the operands' traffic counts: eight wavefronts for a long sum
 // (4000 x 160 x 4000: 349 us against 380), four for a short one, so that all
 // workgroups fit at once (4000 x 160 x 160: 24 us against 26).
-constexpr int64_t kSmallTiles = 256;
+constexpr int64_t kSmallTiles = 512;
 
 template <typename T>
 void gemm_small(hipStream_t s, GemmArgs<T> d, int ta, int64_t work_elems) {
@@ -432,23 +433,18 @@ void gemm_impl(hipStream_t s, GemmArgs<T> d, int ta, int cfg, int64_t work_elems
   }
   d.splits = 1;
   d.kchunk = d.K > 0 ? d.K : 1;
-  if (d.A != d.C && d.B != d.C && cfg != GEMM_UPDATE_TALL &&
-      ((d.M + 63) / 64) * ((d.N + 63) / 64) * d.batch <= kSmallTiles)
+  const int64_t tiles =
+      ((d.M + kTileM - 1) / kTileM) * ((d.N + kTileN - 1) / kTileN) * d.batch;
+  // Long sums over one to four tiles a compute unit: four ranges of K, if the caller has
+  // a workspace (complex128, us: 4000 x 160 x 4000, 315 tiles, 349 -> 318; 6000 x 60 x
+  // 6000, 188 tiles, 337 -> 309; op = ^* and fewer tiles are no faster)
+  const bool split = d.work && ta == 0 && d.K >= 2048 && tiles >= 160 && tiles < 2 * kSmallTiles &&
+                     4 * d.batch * d.M * d.N <= work_elems;
+  if (d.A != d.C && d.B != d.C && cfg != GEMM_UPDATE_TALL && !split && tiles < kSmallTiles)
     return gemm_small<T>(s, d, ta, work_elems);
-  const int64_t tiles = ((d.M + 63) / 64) * ((d.N + 63) / 64);
-  // Split K when the output is too small to fill the chip (aiming at about
-  // three workgroups per compute unit, each K chunk at least 64 long: the
-  // Gram products of an n x m block, m <= 160, are otherwise a few long
-  // workgroups).
-  if (d.work && d.K >= 512 && tiles * d.batch < 512) {
-    int64_t sp = (768 + tiles * d.batch - 1) / (tiles * d.batch);
-    sp = std::min<int64_t>(sp, d.K / 64);
-    while (sp > 1 && sp * d.batch * d.M * d.N > work_elems) --sp;
-    if (sp > 1) {
-      d.splits = static_cast<int32_t>(sp);
-      d.kchunk = ((d.K + sp - 1) / sp + 15) / 16 * 16;
-      d.splits = static_cast<int32_t>((d.K + d.kchunk - 1) / d.kchunk);
-    }
+  if (split) {
+    d.kchunk = ((d.K + 3) / 4 + kTileK - 1) / kTileK * kTileK;
+    d.splits = 4;
   }
   launch_tiles<T>(s, d, ta, ta == 0 ? cfg : static_cast<int>(GEMM_SQUARE));
   if (d.splits > 1) launch_splitk_reduce<T>(s, d);

@@ -113,3 +113,16 @@ def test_filter_of_matrices_with_far_rows(batched):
             plan = fm.Plan(p.n, p.m, p.center, p.radius, p.nodes, prec=fm.MIXED)
             out.append(plan.filter(A, B, V).cpu().numpy())
     assert np.max(np.abs(out[0] - out[1])) <= 1e-12 * np.max(np.abs(out[0]))
+
+
+@pytest.mark.parametrize("n,m", [(2049, 150), (2600, 97)])
+def test_projection_products_over_ranges_of_k(n, m):
+    # A U_1 and B U_1 of a plan (which has room for partial sums): four ranges of K
+    rng = np.random.default_rng(n)
+    A, B, X = crand(rng, n, n), crand(rng, n, n), crand(rng, n, m)
+    plan = fm.Plan(n, m, 0.0, 1.0, 1)
+    U1, AU, BU, _, _ = plan.project(*(torch.from_numpy(x).to(DEV) for x in (A, B, X)))
+    U1 = U1.cpu().numpy()
+    zero = np.zeros((n, m))
+    check(AU.cpu().numpy(), A, U1, zero, 1.0 + 0j, 0j)
+    check(BU.cpu().numpy(), B, U1, zero, 1.0 + 0j, 0j)
