@@ -756,10 +756,12 @@ __global__ __launch_bounds__(256) void k_lu_small(const GrpMat *__restrict__ grp
 template <typename T>
 __global__ __launch_bounds__(256) void k_diag_inv(const T *__restrict__ Mall, int64_t ld_in,
                                                   int64_t stride, int64_t n_in, int64_t blk0,
-                                                  bool lower, T *__restrict__ out,
-                                                  int64_t out_stride,
+                                                  bool lower_in, T *__restrict__ out_in,
+                                                  T *__restrict__ other, int64_t out_stride,
                                                   const GrpMat *__restrict__ grp, int nodes) {
   __shared__ T S[64][kTP];
+  const bool lower = blockIdx.z == 0 ? lower_in : !lower_in;  // (z = 1: the other triangle)
+  T *out = blockIdx.z == 0 ? out_in : other;
   const int64_t I = blk0 + blockIdx.x;
   const int b = blockIdx.y;
   const MatRef<const T> mr = mat_of<const T>(grp, nodes, Mall, ld_in, stride, n_in, b);
@@ -794,16 +796,20 @@ __global__ __launch_bounds__(256) void k_diag_inv(const T *__restrict__ Mall, in
 // off-diagonal 64 x 64 block C of the factor:
 //   lower (unit):  [L11 0; C L22]^{-1} = [I1 0; -(I2 C) I1  I2]
 //   upper:         [U11 C; 0 U22]^{-1} = [I1  -(I1 C) I2; 0 I2]
-// One workgroup per (block, matrix); the two 64 x 64 x 64 products run on the
+// One workgroup per (block, matrix, triangle); the two 64 x 64 x 64 products run on the
 // matrix cores from LDS, one 16-row strip of the output per wavefront.  (16
 // complex128 matrices of order 200: 94 us a launch with each thread summing its
 // entries from LDS, 35 us so.)
 template <typename T>
 __global__ __launch_bounds__(256) void k_inv_pair(const T *__restrict__ F, int64_t ld,
                                                   int64_t fstride, int64_t n,
-                                                  const T *__restrict__ inv64, int64_t istride,
-                                                  T *__restrict__ inv128, int64_t istride2,
-                                                  bool lower) {
+                                                  const T *__restrict__ Linv,
+                                                  const T *__restrict__ Uinv, int64_t istride,
+                                                  T *__restrict__ Linv2, T *__restrict__ Uinv2,
+                                                  int64_t istride2) {
+  const bool lower = blockIdx.z == 0;
+  const T *inv64 = lower ? Linv : Uinv;
+  T *inv128 = lower ? Linv2 : Uinv2;
   __shared__ T sA[64][kTP];
   __shared__ T sB[64][kTP];
   const int64_t B = blockIdx.x, b = blockIdx.y;
@@ -860,27 +866,46 @@ __global__ __launch_bounds__(256) void k_inv_pair(const T *__restrict__ F, int64
 }
 
 // n: order (pivot vectors of the batch are n_stride apart; grouped batches read
-// each matrix's order from grp)
-__global__ __launch_bounds__(256) void k_perm(const int32_t *__restrict__ ipiv_all,
-                                              int32_t *__restrict__ perm_all, int64_t n_stride,
-                                              const GrpMat *__restrict__ grp, int nodes) {
+// each matrix's order from grp).
+// Bound by latency: one exchange after the other costs an LDS round trip each.  So
+// every wavefront takes 64 exchanges and follows, in registers, the 64 positions i and
+// the 64 positions ipiv[i] back through them to where their entries come from (which
+// depends on no entry); only moving the entries goes one wavefront after the other.
+// n = 1000: 53 -> 8.6 us.
+__global__ __launch_bounds__(1024) void k_perm(const int32_t *__restrict__ ipiv_all,
+                                               int32_t *__restrict__ perm_all, int64_t n_stride,
+                                               const GrpMat *__restrict__ grp, int nodes) {
   extern __shared__ int32_t sp[];
   const int b = blockIdx.x;
-  const int64_t n = grp ? grp[b / nodes].n : n_stride;
+  const int n = static_cast<int>(grp ? grp[b / nodes].n : n_stride);
   const int32_t *ipiv = ipiv_all + b * n_stride;
   int32_t *perm = perm_all + b * n_stride;
-  for (int64_t i = threadIdx.x; i < n; i += 256) sp[i] = static_cast<int32_t>(i);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int64_t i = 0; i < n; ++i) {
-      const int32_t p = ipiv[i];
-      const int32_t x = sp[i];
-      sp[i] = sp[p];
-      sp[p] = x;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int i = threadIdx.x; i < n; i += 1024) sp[i] = i;
+  for (int k0 = 0; k0 < n; k0 += 1024) {
+    const int i0 = k0 + 64 * wave, i = i0 + lane;
+    const int p = i < n ? ipiv[i] : i;
+    int a = i, c = p;
+    if (i0 < n) {
+#pragma unroll
+      for (int j = 63; j >= 0; --j) {
+        const int pj = __builtin_amdgcn_readlane(p, j), ij = i0 + j;
+        a = a == ij ? pj : a == pj ? ij : a;
+        c = c == ij ? pj : c == pj ? ij : c;
+      }
+    }
+    for (int w = 0; w < 16 && k0 + 64 * w < n; ++w) {
+      __syncthreads();
+      if (wave == w && i < n) {
+        const int32_t x = sp[a], y = sp[c];
+        wave_lds_order();  // every lane's entries are read before any is written
+        sp[i] = x;
+        sp[p] = y;  // (lanes with the same p write the same entry)
+      }
     }
   }
   __syncthreads();
-  for (int64_t i = threadIdx.x; i < n; i += 256) perm[i] = sp[i];
+  for (int i = threadIdx.x; i < n; i += 1024) perm[i] = sp[i];
 }
 
 __global__ void k_fill_i32(int32_t *p, int64_t count, int32_t v) {
@@ -1052,34 +1077,35 @@ template bool panel_cols<c64>(hipStream_t, c64 *, int64_t, int64_t, int32_t, int
 template <typename T>
 void diag_block_inverse(hipStream_t s, const T *M, int64_t ld, int64_t stride, int32_t batch,
                         int64_t n, int64_t blk0, int64_t blk1, bool lower, T *out,
-                        int64_t out_stride, const GrpMat *grp, int nodes) {
+                        int64_t out_stride, const GrpMat *grp, int nodes, T *other) {
   if (blk1 <= blk0) return;
-  hipLaunchKernelGGL((k_diag_inv<T>), dim3(static_cast<unsigned>(blk1 - blk0), batch), dim3(256),
-                     0, s, M, ld, stride, n, blk0, lower, out, out_stride, grp, nodes);
+  hipLaunchKernelGGL((k_diag_inv<T>), dim3(static_cast<unsigned>(blk1 - blk0), batch, other ? 2 : 1),
+                     dim3(256), 0, s, M, ld, stride, n, blk0, lower, out, other, out_stride, grp, nodes);
 }
 template void diag_block_inverse<z64>(hipStream_t, const z64 *, int64_t, int64_t, int32_t,
                                       int64_t, int64_t, int64_t, bool, z64 *, int64_t,
-                                      const GrpMat *, int);
+                                      const GrpMat *, int, z64 *);
 template void diag_block_inverse<c64>(hipStream_t, const c64 *, int64_t, int64_t, int32_t,
                                       int64_t, int64_t, int64_t, bool, c64 *, int64_t,
-                                      const GrpMat *, int);
+                                      const GrpMat *, int, c64 *);
 
 template <typename T>
 void inverse_pairs(hipStream_t s, const T *M, int64_t ld, int64_t stride, int32_t batch, int64_t n,
-                   const T *inv64, int64_t istride, T *inv128, int64_t istride2, bool lower) {
+                   const T *Linv, const T *Uinv, int64_t istride, T *Linv2, T *Uinv2,
+                   int64_t istride2) {
   const int64_t nb2 = (n + 127) / 128;
   if (nb2 <= 0 || batch <= 0) return;
-  hipLaunchKernelGGL((k_inv_pair<T>), dim3(static_cast<unsigned>(nb2), batch), dim3(256), 0, s, M,
-                     ld, stride, n, inv64, istride, inv128, istride2, lower);
+  hipLaunchKernelGGL((k_inv_pair<T>), dim3(static_cast<unsigned>(nb2), batch, 2), dim3(256), 0, s, M,
+                     ld, stride, n, Linv, Uinv, istride, Linv2, Uinv2, istride2);
 }
 template void inverse_pairs<z64>(hipStream_t, const z64 *, int64_t, int64_t, int32_t, int64_t,
-                                 const z64 *, int64_t, z64 *, int64_t, bool);
+                                 const z64 *, const z64 *, int64_t, z64 *, z64 *, int64_t);
 template void inverse_pairs<c64>(hipStream_t, const c64 *, int64_t, int64_t, int32_t, int64_t,
-                                 const c64 *, int64_t, c64 *, int64_t, bool);
+                                 const c64 *, const c64 *, int64_t, c64 *, c64 *, int64_t);
 
 void perm_from_ipiv(hipStream_t s, const int32_t *ipiv, int32_t *perm, int64_t n, int32_t batch,
                     const GrpMat *grp, int nodes) {
-  hipLaunchKernelGGL(k_perm, dim3(batch), dim3(256), static_cast<unsigned>(n * sizeof(int32_t)), s,
+  hipLaunchKernelGGL(k_perm, dim3(batch), dim3(1024), static_cast<unsigned>(n * sizeof(int32_t)), s,
                      ipiv, perm, n, grp, nodes);
 }
 

@@ -139,8 +139,10 @@ __global__ __launch_bounds__(256) void k_weighted_sum(const z64 *__restrict__ Y,
 }
 
 __global__ __launch_bounds__(256) void k_copy_block(const z64 *__restrict__ X, int64_t ldx,
-                                                    int64_t n, int64_t m, z64 *__restrict__ Y,
-                                                    int64_t ldy) {
+                                                    int64_t sX, int64_t n, int64_t m,
+                                                    z64 *__restrict__ Y, int64_t ldy, int64_t sY) {
+  X += blockIdx.z * sX;
+  Y += blockIdx.z * sY;
   ROWWISE_FOR(n, m, row, col) Y[row * ldy + col] = X[row * ldx + col];
 }
 
@@ -782,11 +784,11 @@ void weighted_sum(hipStream_t s, const z64 *Y, int64_t ldy, int64_t sY, const z6
 }
 
 void copy_block_z(hipStream_t s, const z64 *X, int64_t ldx, int64_t n, int64_t m, z64 *Y,
-                  int64_t ldy) {
+                  int64_t ldy, int32_t batch, int64_t sX, int64_t sY) {
   const int64_t tot = n * m;
-  if (tot <= 0) return;
-  hipLaunchKernelGGL(k_copy_block, rowwise_grid(n, m, 1), dim3(256), 0, s,
-                     X, ldx, n, m, Y, ldy);
+  if (tot <= 0 || batch <= 0) return;
+  hipLaunchKernelGGL(k_copy_block, rowwise_grid(n, m, batch), dim3(256), 0, s,
+                     X, ldx, sX, n, m, Y, ldy, sY);
 }
 
 void z_to_c(hipStream_t s, const z64 *X, int64_t ldx, int64_t sX, int64_t n, int64_t m,

@@ -144,17 +144,20 @@ int panel_update_max_width();
 // Inverses of the diagonal blocks of the unit-lower L (lower=true) or of the
 // upper U (lower=false) factor: block I covers rows/cols [64 I, min(n, 64 (I+1))).
 // out[b][I] is a 64 x 64 row-major block (ld 64, zero padded).  Blocks [blk0, blk1).
+// other (optional): the inverses of the other triangle, in the same launch.
 template <typename T>
 void diag_block_inverse(hipStream_t s, const T *M, int64_t ld, int64_t stride, int32_t batch,
                         int64_t n, int64_t blk0, int64_t blk1, bool lower, T *out,
-                        int64_t out_stride, const GrpMat *grp = nullptr, int nodes = 1);
+                        int64_t out_stride, const GrpMat *grp = nullptr, int nodes = 1,
+                        T *other = nullptr);
 
-// Inverted 128-row diagonal blocks (row-major 128 x 128, istride2 apart per
-// matrix) built from the inverted 64-row blocks of diag_block_inverse (istride
-// apart) and the factor's off-diagonal 64 x 64 blocks.
+// Inverted 128-row diagonal blocks of both triangles (row-major 128 x 128, istride2
+// apart per matrix) built from the inverted 64-row blocks of diag_block_inverse
+// (istride apart) and the factor's off-diagonal 64 x 64 blocks.
 template <typename T>
 void inverse_pairs(hipStream_t s, const T *M, int64_t ld, int64_t stride, int32_t batch, int64_t n,
-                   const T *inv64, int64_t istride, T *inv128, int64_t istride2, bool lower);
+                   const T *Linv, const T *Uinv, int64_t istride, T *Linv2, T *Uinv2,
+                   int64_t istride2);
 
 // perm[b][i] = original row at position i of P_b (from LAPACK-order ipiv).
 void perm_from_ipiv(hipStream_t s, const int32_t *ipiv, int32_t *perm, int64_t n, int32_t batch,
@@ -218,7 +221,7 @@ void weighted_sum(hipStream_t s, const z64 *Y, int64_t ldy, int64_t sY, const z6
 // (nrm2 on the device: the squared Frobenius norm of the right-hand side,
 // cnt its number of entries; nrm2 = nullptr: no scaling).
 void copy_block_z(hipStream_t s, const z64 *X, int64_t ldx, int64_t n, int64_t m, z64 *Y,
-                  int64_t ldy);
+                  int64_t ldy, int32_t batch = 1, int64_t sX = 0, int64_t sY = 0);
 void z_to_c(hipStream_t s, const z64 *X, int64_t ldx, int64_t sX, int64_t n, int64_t m,
             int32_t batch, c64 *Y, int64_t ldy, int64_t sY, const double *nrm2 = nullptr,
             double cnt = 1.0);
