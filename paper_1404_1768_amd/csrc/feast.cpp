@@ -65,6 +65,116 @@ void panel(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch, int64
   }
 }
 
+// Scratch of the batched calls that own no plan (factorisation, solves with given
+// factors): a hipMalloc (and hipFree) of tens of megabytes per call took 80 us of a
+// 640 us solve.  Idle blocks are kept per device, at most kIdleBytes of them
+// altogether; a block that kIdleCalls further calls did not use is freed, and all of
+// them when a device allocation fails.  A block is leased to one call at a time and
+// returns to the pool only once the call's stream has run dry, so any threads and
+// streams may share the pool.
+class ScratchPool {
+ public:
+  struct Block {
+    void *p = nullptr;
+    size_t bytes = 0;
+    int dev = -1;
+    uint64_t used = 0;
+  };
+  Block take(size_t want) {
+    int dev = 0;
+    HIPCHK(hipGetDevice(&dev));
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      ++calls_;
+      auto best = idle_.end();
+      for (auto it = idle_.begin(); it != idle_.end(); ++it)
+        if (it->dev == dev && it->bytes >= want && it->bytes / 8 <= want &&
+            (best == idle_.end() || it->bytes < best->bytes))
+          best = it;
+      if (best != idle_.end()) {
+        const Block b = *best;
+        idle_.erase(best);
+        bytes_ -= b.bytes;
+        return b;
+      }
+    }
+    Block b;
+    b.bytes = (want + 65535) / 65536 * 65536;
+    b.dev = dev;
+    hipError_t e = hipMalloc(&b.p, b.bytes);
+    if (e == hipErrorOutOfMemory) {
+      (void)hipGetLastError();
+      trim();
+      e = hipMalloc(&b.p, b.bytes);
+    }
+    if (e != hipSuccess) throw HipError{e, "hipMalloc"};
+    return b;
+  }
+  void give(Block b) noexcept {
+    std::vector<Block> out;
+    try {
+      std::lock_guard<std::mutex> lock(mu_);
+      b.used = calls_;
+      if (bytes_ + b.bytes <= kIdleBytes) {
+        idle_.push_back(b);
+        bytes_ += b.bytes;
+        b.p = nullptr;
+      }
+      drop([&](const Block &x) { return x.used + kIdleCalls < calls_; }, out);
+    } catch (...) {  // (no memory for the lists: what could not be kept is freed)
+    }
+    if (b.p) (void)hipFree(b.p);
+    for (const Block &x : out) (void)hipFree(x.p);
+  }
+  // Frees every idle block.
+  void trim() {
+    std::vector<Block> out;
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      drop([](const Block &) { return true; }, out);
+    }
+    for (const Block &x : out) (void)hipFree(x.p);
+  }
+
+ private:
+  static constexpr size_t kIdleBytes = size_t(1) << 30;
+  static constexpr uint64_t kIdleCalls = 64;
+  template <typename F> void drop(F &&away, std::vector<Block> &out) {
+    out.reserve(idle_.size());
+    for (size_t i = 0; i < idle_.size();) {
+      if (away(idle_[i])) {
+        out.push_back(idle_[i]);
+        bytes_ -= idle_[i].bytes;
+        idle_.erase(idle_.begin() + static_cast<std::ptrdiff_t>(i));
+      } else {
+        ++i;
+      }
+    }
+  }
+  std::mutex mu_;
+  std::vector<Block> idle_;
+  size_t bytes_ = 0;
+  uint64_t calls_ = 0;
+};
+
+ScratchPool &scratch_pool() {
+  static ScratchPool *pool = new ScratchPool;  // (never destroyed: the runtime may be gone first)
+  return *pool;
+}
+
+// A block of the pool for work on stream s.
+struct ScratchLease {
+  hipStream_t s;
+  ScratchPool::Block b;
+  ScratchLease(hipStream_t stream, size_t bytes) : s(stream), b(scratch_pool().take(bytes)) {}
+  ScratchLease(const ScratchLease &) = delete;
+  ScratchLease &operator=(const ScratchLease &) = delete;
+  ~ScratchLease() {
+    (void)hipStreamSynchronize(s);  // (the calls have waited already, unless they threw)
+    scratch_pool().give(b);
+  }
+};
+
 struct LuProf {
   std::vector<hipEvent_t> *ev = nullptr;  // pairs around trailing-update launches
   int used = 0;
@@ -595,6 +705,8 @@ constexpr double kNearOrthonormal = 0.1;  // ||X^* X - I||_F
 
 // Helpers shared with the batched driver (declared in plan.h).
 namespace feast_drv {
+
+void trim_scratch() { scratch_pool().trim(); }
 
 int fail(feast_plan *p, int code, const std::string &msg) {
   if (p) p->err = msg;
@@ -1890,16 +2002,13 @@ int feast_zgetrf_batched(int64_t n, int32_t batch, feast_z *dM, int64_t ldm, int
   return guarded(nullptr, [&]() {
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t nblk = (n + 63) / 64;
-    DevBuf Li, Ui;
-    Li.alloc(sizeof(z64) * batch * nblk * 64 * 64);
-    Ui.alloc(sizeof(z64) * batch * nblk * 64 * 64);
+    const int64_t blocks = batch * nblk * 64 * 64;
+    const ScratchLease ws(s, sizeof(z64) * 2 * blocks);
+    z64 *Li = static_cast<z64 *>(ws.b.p), *Ui = Li + blocks;
     lu_batched<z64>(LuStreams{s, nullptr, nullptr, nullptr}, reinterpret_cast<z64 *>(dM), ldm,
-                    strideM, batch, n, b, dPiv, dInfo, Li.as<z64>(), Ui.as<z64>(),
-                    nblk * 64 * 64);
+                    strideM, batch, n, b, dPiv, dInfo, Li, Ui, nblk * 64 * 64);
     HIPCHK(hipStreamSynchronize(s));
     HIPCHK(hipGetLastError());
-    Li.release();
-    Ui.release();
     return FEAST_OK;
   });
 }
@@ -2002,11 +2111,10 @@ int feast_zgetrs_batched(int64_t n, int64_t nrhs, int32_t batch, const feast_z *
   if (nrhs == 0) return FEAST_OK;
   return guarded(nullptr, [&]() {
     hipStream_t s = static_cast<hipStream_t>(stream);
-    DevBuf ws;
-    ws.alloc(getrs_scratch_bytes(n, nrhs, batch));
+    const ScratchLease ws(s, getrs_scratch_bytes(n, nrhs, batch));
     zgetrs_enqueue(s, n, nrhs, batch, reinterpret_cast<const z64 *>(dLU), ldm, strideM, dPiv,
                    reinterpret_cast<z64 *>(dX), ldx, strideX, trans,
-                   carve_getrs(ws.p, n, nrhs, batch));
+                   carve_getrs(ws.b.p, n, nrhs, batch));
     HIPCHK(hipStreamSynchronize(s));
     HIPCHK(hipGetLastError());
     return FEAST_OK;

@@ -37,6 +37,9 @@ struct HipError {
     if (e_ != hipSuccess) throw HipError{e_, #x};   \
   } while (0)
 
+// Frees the idle scratch of the calls that own no plan.
+void trim_scratch();
+
 struct DevBuf {
   void *p = nullptr;
   size_t bytes = 0;
@@ -45,6 +48,11 @@ struct DevBuf {
     release();
     if (b == 0) return;
     hipError_t e = hipMalloc(&p, b);
+    if (e == hipErrorOutOfMemory) {
+      (void)hipGetLastError();
+      trim_scratch();
+      e = hipMalloc(&p, b);
+    }
     if (e != hipSuccess) {
       p = nullptr;
       bytes = 0;
