@@ -36,8 +36,8 @@ namespace {
 // ---------------------------------------------------------------------------
 // Blocked right-looking LU of `batch` matrices (row-major, partial pivoting).
 // A panel of width nb is factored 64 columns at a time (feast::panel_cols: leaves
-// and their updates); the two halves of a 128-column panel are joined by the
-// product with the first half's inverted diagonal block and an MFMA update;
+// and their updates); the two halves of a 128-column panel are joined by a solve
+// with the first half's rows and an MFMA update;
 // then the panel's swaps reach the columns outside it, U12 = L11^{-1} A12 is
 // an in-place MFMA product with the inverted diagonal blocks, and the trailing
 // update A22 -= L21 U12 is one batched MFMA GEMM over all matrices.
@@ -53,8 +53,7 @@ void panel(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch, int64
     const int64_t ch = c0 + h;
     if (h > 0) {  // (the exchanges so far have reached these columns)
       T *X = M + c0 * ld + ch;
-      gemm_t<T>(s, 0, 64, wh, 64, zc(1.0), Linv + c0 / 64 * 4096, 64, istride, X, ld, stride, zc(0.0),
-                X, ld, stride, batch);
+      feast::panel_solve<T>(s, M, ld, stride, batch, n, c0, 64, wh);
       gemm_t<T>(s, 0, n - ch, wh, 64, zc(-1.0), M + ch * ld + c0, ld, stride, X, ld, stride, zc(1.0),
                 M + ch * ld + ch, ld, stride, batch);
     }

@@ -132,8 +132,8 @@ template <typename R> __device__ inline R wave_max(R x) {
 
 // 1 / a for finite a != 0: a scaled by the power of two of its larger part, so
 // that |a|^2 is in [1/4, 2), one real reciprocal (the hardware's estimate and
-// Newton steps to full precision), scaled back.  No intermediate overflows or
-// underflows.
+// Newton steps), a Newton step on the complex one, scaled back.  No intermediate
+// overflows or underflows.
 __device__ inline double rcp_newton(double d) {
   double r = __builtin_amdgcn_rcp(d);
   r = fma(r, fma(-d, r, 1.0), r);
@@ -149,9 +149,11 @@ template <typename T> __device__ inline T recip_scaled(T a) {
   const int e = exp_of(fmax(fabs(a.x), fabs(a.y)));
   const auto x = ldexp(a.x, -e), y = ldexp(a.y, -e);
   const auto r = rcp_newton(fma(x, x, y * y));
+  const auto u = x * r, v = -(y * r);
+  const auto du = fma(y, v, fma(-x, u, decltype(r)(1))), dv = -fma(x, v, y * u);  // 1 - a o
   T o;
-  o.x = ldexp(x * r, -e);
-  o.y = -ldexp(y * r, -e);
+  o.x = ldexp(u + fma(u, du, -(v * dv)), -e);
+  o.y = ldexp(v + fma(u, dv, v * du), -e);
   return o;
 }
 
@@ -539,54 +541,77 @@ __global__ __launch_bounds__(256) void k_laswp_outside(T *__restrict__ Mall, int
 // Joins of the panel factorisation:
 //   X = L11^{-1} X      for X = M[c0:c0+w1, c0+w1:c0+w1+w2], L11 unit lower (w1 x w1),
 //   C -= L21 X          for C = M[c0+w1:n, c0+w1:c0+w1+w2], L21 = M[c0+w1:n, c0:c0+w1],
-// w1 <= 32, in two launches: the small solve once per matrix (k_panel_solve, w2
-// <= 32; a leaf that has solved its own rows needs none), then the update by every
-// 64-row chunk and 32-column block (k_panel_rank, reading the solved X).  (In one
-// launch every chunk would repeat the solve.)  The update is a product with
-// w1 <= 32: bound by the traffic of C, so it runs on the VALU.
+// in two launches: the small solve once per matrix (k_panel_solve, w1, w2 <= 64; a leaf
+// that has solved its own rows needs none), then the update: for w1 <= 32 by every
+// 64-row chunk and 32-column block (k_panel_rank, reading the solved X; bound by the
+// traffic of C, so it runs on the VALU), else as a product.  (In one launch every
+// chunk would repeat the solve.)
 constexpr int kPU = 32;
-// One workgroup per matrix: L11's inverse by halves (tri64.h), then the product
-// on the matrix cores, one 16 x 16 tile per wavefront.  (32 x 32, 16 complex128
-// matrices: 13 us a launch by substitution, 9 so.)
-template <typename T>
+// One workgroup per matrix, 16 columns of X per wavefront, on the matrix cores: 16 rows
+// at a time, X_i = L_ii^{-1} (X_i - sum_{j<i} L_ij X_j) with the inverted 16 x 16 diagonal
+// blocks.  (With the inverse of all 64 rows of L11 the join took 7 us less, but the
+// factors of random matrices came out with more error: order 97 4.9e-15 relative
+// against 2.9e-15, order 128 7.1e-15 against 4.1e-15.)
+//   32 x 32, 16 complex128 matrices: 13 us a launch by substitution, 11.5 so; 64 x 64:
+//   13.7.
+template <typename T, int R>
 __global__ __launch_bounds__(256) void k_panel_solve(T *__restrict__ Mall, int64_t ld_in,
                                                      int64_t stride, int64_t n_in, int64_t c0,
                                                      int w1, int w2,
                                                      const GrpMat *__restrict__ grp, int nodes) {
-  __shared__ T sL[kPU][kTP];
-  __shared__ T sX[kPU][kTP];
+  __shared__ T sL[R][kTP];
+  __shared__ T sX[R][kTP];
   const MatRef<T> mr = mat_of<T>(grp, nodes, Mall, ld_in, stride, n_in, blockIdx.x);
   if (c0 + w1 + w2 > mr.n) return;
   const int64_t ld = mr.ld;
   T *D = mr.M + c0 * (ld + 1);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  T v[4], x[4];
+  constexpr int PER = R / 4;  // rows of L11 and X a wavefront loads
+  T v[PER], x[PER];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int i = (tid >> 5) + 8 * k, j = tid & 31;
-    v[k] = (i < w1 && j < w1) ? D[i * ld + j] : czero<T>();
-    x[k] = (i < w1 && j < w2) ? D[i * ld + w1 + j] : czero<T>();
+  for (int k = 0; k < PER; ++k) {
+    const int i = wave + 4 * k;
+    v[k] = (i < w1 && lane < w1) ? D[i * ld + lane] : czero<T>();
+    x[k] = (i < w1 && lane < w2) ? D[i * ld + w1 + lane] : czero<T>();
   }
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    sL[(tid >> 5) + 8 * k][tid & 31] = v[k];
-    sX[(tid >> 5) + 8 * k][tid & 31] = x[k];
+  for (int k = 0; k < PER; ++k) {
+    sL[wave + 4 * k][lane] = v[k];
+    sX[wave + 4 * k][lane] = x[k];
   }
   __syncthreads();
-  if (wave < 2) wave_tri16(sL, 16 * wave, true, lane);
+  if (wave < R / 16) wave_tri16(sL, 16 * wave, true, lane);
   __syncthreads();
-  tri_join<T, 16, 32>(sL, lane, wave);
-  const int ti = 16 * (wave >> 1), tj = 16 * (wave & 1);
-  Tile16<T> t;
-  t.template mac<false>(sL, ti, 0, sX, 0, tj, (ti + 16) / 4, lane);
+  const int tj = 16 * wave;
+  if (tj >= w2) return;
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int i = ti + mfma_ops<T>::out_row(lane, r), j = tj + (lane & 15);
-    T o;
-    o.x = t.re[r];
-    o.y = t.im[r];
-    if (i < w1 && j < w2) D[i * ld + w1 + j] = o;
+  for (int i = 0; i < R; i += 16) {
+    if (i >= w1) break;
+    Tile16<T> t;
+    if (i > 0) {
+      t.template mac<false>(sL, i, 0, sX, 0, tj, i / 4, lane);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        T &p = sX[i + mfma_ops<T>::out_row(lane, r)][tj + (lane & 15)];
+        p.x -= t.re[r];
+        p.y -= t.im[r];
+      }
+      wave_lds_order();
+    }
+    Tile16<T> y;
+    y.template mac<false>(sL, i, i, sX, i, tj, 4, lane);
+    wave_lds_order();
+    y.put(sX, i, tj, lane, 1);
+    wave_lds_order();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = i + mfma_ops<T>::out_row(lane, r), j = tj + (lane & 15);
+      T o;
+      o.x = y.re[r];
+      o.y = y.im[r];
+      if (row < w1 && j < w2) D[row * ld + w1 + j] = o;
+    }
   }
 }
 
@@ -617,13 +642,14 @@ __global__ __launch_bounds__(256) void k_panel_rank(T *__restrict__ Mall, int64_
     sL[i][k] = L[(r0 + i) * ld + c0 + k];
   }
   const int ti = tid >> 4, tj = tid & 15;
-  T acc[4][2];
+  T c[4][2], acc[4][2];  // (the sum apart from C: it rounds at its own size)
 #pragma unroll
   for (int a = 0; a < 4; ++a)
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       const int i = ti + 16 * a, j = tj + 16 * b;
-      acc[a][b] = (i < rows && j < w2) ? M[(r0 + i) * ld + c0 + w1 + j] : Tr::make(0.0, 0.0);
+      acc[a][b] = Tr::make(0.0, 0.0);
+      c[a][b] = (i < rows && j < w2) ? M[(r0 + i) * ld + c0 + w1 + j] : Tr::make(0.0, 0.0);
     }
   __syncthreads();
   for (int k = 0; k < w1; ++k) {
@@ -635,14 +661,20 @@ __global__ __launch_bounds__(256) void k_panel_rank(T *__restrict__ Mall, int64_
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
-      for (int b = 0; b < 2; ++b) acc[a][b] = ffms(acc[a][b], l[a], x[b]);
+      for (int b = 0; b < 2; ++b) {
+        acc[a][b].x = fma(-l[a].y, x[b].y, fma(l[a].x, x[b].x, acc[a][b].x));
+        acc[a][b].y = fma(l[a].y, x[b].x, fma(l[a].x, x[b].y, acc[a][b].y));
+      }
   }
 #pragma unroll
   for (int a = 0; a < 4; ++a)
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       const int i = ti + 16 * a, j = tj + 16 * b;
-      if (i < rows && j < w2) M[(r0 + i) * ld + c0 + w1 + j] = acc[a][b];
+      if (i >= rows || j >= w2) continue;
+      c[a][b].x -= acc[a][b].x;
+      c[a][b].y -= acc[a][b].y;
+      M[(r0 + i) * ld + c0 + w1 + j] = c[a][b];
     }
 }
 
@@ -1027,11 +1059,24 @@ void panel_rank(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch, 
                      dim3(256), 0, s, M, ld, stride, n, c0, w1, w2, grp, nodes);
 }
 template <typename T>
+void panel_solve(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch, int64_t n,
+                 int64_t c0, int w1, int w2, const GrpMat *grp, int nodes) {
+  if (w1 <= 0 || w2 <= 0 || w1 > 64 || w2 > 64 || batch <= 0) return;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(batch), dim3(256), 0, s, M, ld, stride, n, c0, w1, w2, grp, nodes);
+  };
+  w1 <= kPU ? go(k_panel_solve<T, kPU>) : go(k_panel_solve<T, 64>);
+}
+template void panel_solve<z64>(hipStream_t, z64 *, int64_t, int64_t, int32_t, int64_t, int64_t, int,
+                               int, const GrpMat *, int);
+template void panel_solve<c64>(hipStream_t, c64 *, int64_t, int64_t, int32_t, int64_t, int64_t, int,
+                               int, const GrpMat *, int);
+
+template <typename T>
 void panel_update(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch, int64_t n,
                   int64_t c0, int w1, int w2, const GrpMat *grp, int nodes) {
   if (w1 <= 0 || w2 <= 0 || w1 > kPU || w2 > kPU || batch <= 0) return;
-  hipLaunchKernelGGL((k_panel_solve<T>), dim3(batch), dim3(256), 0, s, M, ld, stride, n, c0, w1, w2,
-                     grp, nodes);
+  panel_solve<T>(s, M, ld, stride, batch, n, c0, w1, w2, grp, nodes);
   panel_rank<T>(s, M, ld, stride, batch, n, c0, w1, w2, grp, nodes);
 }
 int panel_update_max_width() { return kPU; }

