@@ -55,14 +55,6 @@ __device__ inline void swap_pair(double v, double &a, double &b) {
   a = __builtin_bit_cast(double, static_cast<uint64_t>(x[0]) | (static_cast<uint64_t>(y[0]) << 32));
   b = __builtin_bit_cast(double, static_cast<uint64_t>(x[1]) | (static_cast<uint64_t>(y[1]) << 32));
 }
-template <bool ROWS16>
-__device__ inline void swap_pair(int v, int &a, int &b) {
-  const unsigned u = static_cast<unsigned>(v);
-  const auto x = ROWS16 ? __builtin_amdgcn_permlane16_swap(u, u, false, false)
-                        : __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  a = static_cast<int>(x[0]);
-  b = static_cast<int>(x[1]);
-}
 
 // v of lane l (l wave-uniform) in every lane, through scalar registers
 __device__ inline double lane_at(double v, int l) {
@@ -72,32 +64,17 @@ __device__ inline double lane_at(double v, int l) {
   return __builtin_bit_cast(double, static_cast<uint64_t>(lo) | (static_cast<uint64_t>(hi) << 32));
 }
 
-// (key, idx) of the lane with the largest key, the lowest index on ties, in
-// every lane of the wavefront (all 64 lanes active)
-__device__ inline void wave_argmax(double &key, int &idx) {
-  auto take = [&](double ok, int oi) {
-    if (ok > key || (ok == key && oi < idx)) {
-      key = ok;
-      idx = oi;
-    }
-  };
+// The largest key of the wavefront, in every lane (all 64 lanes active, no NaN).
+__device__ inline double wave_max(double key) {
   // partners: lane ^ 1, lane ^ 2, 7 - lane mod 8, 15 - lane mod 16
-  take(dpp_f64<0xB1>(key), __builtin_amdgcn_mov_dpp(idx, 0xB1, 0xF, 0xF, false));
-  take(dpp_f64<0x4E>(key), __builtin_amdgcn_mov_dpp(idx, 0x4E, 0xF, 0xF, false));
-  take(dpp_f64<0x141>(key), __builtin_amdgcn_mov_dpp(idx, 0x141, 0xF, 0xF, false));
-  take(dpp_f64<0x140>(key), __builtin_amdgcn_mov_dpp(idx, 0x140, 0xF, 0xF, false));
-  double k0, k1;
-  int i0, i1;
-  swap_pair<true>(key, k0, k1);  // rows 2r and 2r + 1
-  swap_pair<true>(idx, i0, i1);
-  key = k0;
-  idx = i0;
-  take(k1, i1);
-  swap_pair<false>(key, k0, k1);  // the two halves
-  swap_pair<false>(idx, i0, i1);
-  key = k0;
-  idx = i0;
-  take(k1, i1);
+  key = fmax(key, dpp_f64<0xB1>(key));
+  key = fmax(key, dpp_f64<0x4E>(key));
+  key = fmax(key, dpp_f64<0x141>(key));
+  key = fmax(key, dpp_f64<0x140>(key));
+  double a, b;
+  swap_pair<true>(key, a, b);  // rows 2r and 2r + 1
+  swap_pair<false>(fmax(a, b), a, b);  // the two halves
+  return fmax(a, b);
 }
 
 constexpr int kBandCH = 32;  // rows staged per chunk (LU: CSR rows; solves: factor and block rows)
@@ -137,6 +114,11 @@ __device__ inline z64 band_recip(double x, double y) {
 //   takes the staged row's entry as row k + kl + 1 (the owner of column k
 //   starts column k + WC, zero above the new row).
 // The multipliers are double-buffered by the parity of k.
+// Bound by the length of one wavefront's column step.  n = 4800, kl = ku = 22, 16
+// nodes, from both ends: 4.46 -> 3.49 ms with the pivot found by a maximum and a ballot
+// (not a maximum with its index through every exchange), the leaving slot zeroed while
+// its posts are on their way (not by a multiply of every entry) and two-level slot
+// branches.
 template <int W>
 __global__ __launch_bounds__(256) void k_band_lu(const int32_t *__restrict__ rp,
                                                  const int32_t *__restrict__ ci,
@@ -289,6 +271,9 @@ __global__ __launch_bounds__(256) void k_band_lu(const int32_t *__restrict__ rp,
         if (tid == ck) {
 #pragma unroll
           for (int i = 0; i < W; ++i) colbuf[i] = w[i];  // (rows past k + kl are not read)
+          // its slot starts column k + WC: zero (while the posts are on their way)
+#pragma unroll
+          for (int i = 0; i < W; ++i) w[i] = zmake(0.0, 0.0);
         }
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -296,11 +281,9 @@ __global__ __launch_bounds__(256) void k_band_lu(const int32_t *__restrict__ rp,
         const bool valid = i < KR && k + i < n;
         const z64 v = valid ? colbuf[i] : zmake(0.0, 0.0);
         const double a1 = zabs1(v);
-        double key = valid ? (a1 == a1 ? a1 : -1.0) : -2.0;
-        int idx = valid ? i : 1 << 30;
-        wave_argmax(key, idx);
-        key = lane_at(key, 0);  // (every lane holds it: a scalar from here on)
-        const int p = __builtin_amdgcn_readfirstlane(idx < KR ? idx : 0);
+        const double key_i = valid ? (a1 == a1 ? a1 : -1.0) : -2.0;
+        const double key = lane_at(wave_max(key_i), 0);  // (a scalar from here on)
+        const int p = static_cast<int>(__builtin_ctzll(__builtin_amdgcn_ballot_w64(key_i == key)));
         const double ux = lane_at(v.x, p), uy = lane_at(v.y, p);
         const double v0x = lane_at(v.x, 0), v0y = lane_at(v.y, 0);
         const bool zero = !(key > 0.0);
@@ -324,19 +307,27 @@ __global__ __launch_bounds__(256) void k_band_lu(const int32_t *__restrict__ rp,
           int jo = tid - ck;  // this column's offset from column k
           if (jo < 0) jo += WC;
           // exchange rows k and k + p (row k's slot is dead after the step):
-          // one uniform branch per slot, the empty asm keeping each arm a
-          // branch rather than a select of four registers per slot
+          // one uniform branch per eight slots and per slot of the eight, the
+          // empty asm keeping each arm a branch rather than a select of four
+          // registers per slot
           z64 rpv = w[0];
           if (p != 0) {
 #pragma unroll
-            for (int i = 1; i < W; ++i)
-              if (i == p) {
+            for (int h = 0; h < W; h += 8)
+              if (p >= h && p < h + 8) {
                 asm volatile("" ::: "memory");
-                rpv = w[i];
-                w[i] = w[0];
+#pragma unroll
+                for (int i = h; i < h + 8 && i < W; ++i)
+                  if (i > 0 && i == p) {
+                    asm volatile("" ::: "memory");
+                    rpv = w[i];
+                    w[i] = w[0];
+                  }
               }
           }
-          U[k * WC + jo] = (rev || k + jo < N0) ? rpv : zmake(0.0, 0.0);
+          // (column k's slot holds zeros by now, and its entry of row k is the pivot)
+          const z64 urow = jo == 0 ? zmake(ux, uy) : rpv;
+          U[k * WC + jo] = (rev || k + jo < N0) ? urow : zmake(0.0, 0.0);
           // the incoming row k + KR at this slot's next column (k + jo, or
           // k + WC for the slot of column k): staged index WC - 1 or jo - 1
           const z64 nv = (kk < cnt) ? SRc[kk * WC + (jo == 0 ? WC - 1 : jo - 1)] : zmake(0.0, 0.0);
@@ -355,29 +346,20 @@ __global__ __launch_bounds__(256) void k_band_lu(const int32_t *__restrict__ rp,
             for (int t = 0; t < G; ++t)
               if (g + t < W) w[g + t] = band_fms(w[g + t], lr[t], rpv);
           }
-          // rows move up one slot; the slot of column k (leaving) starts column
-          // k + WC with zeros above the incoming row: one multiply by 1 or 0
-          // per entry does both (the window's entries are finite).  The widest
-          // window has no registers for the products: it zeroes, then moves.
-          if constexpr (W <= 48) {
-            const double keep = jo == 0 ? 0.0 : 1.0;
+          // rows move up one slot
 #pragma unroll
-            for (int i = 0; i + 1 < W; ++i) w[i] = zmake(w[i + 1].x * keep, w[i + 1].y * keep);
-          } else {
-            if (jo == 0) {
-              asm volatile("" ::: "memory");
-#pragma unroll
-              for (int i = 0; i < W; ++i) w[i] = zmake(0.0, 0.0);
-            }
-#pragma unroll
-            for (int i = 0; i + 1 < W; ++i) w[i] = w[i + 1];
-          }
+          for (int i = 0; i + 1 < W; ++i) w[i] = w[i + 1];
           w[W - 1] = zmake(0.0, 0.0);
 #pragma unroll
-          for (int i = 0; i < W; ++i)
-            if (i == KR - 1) {
+          for (int h = 0; h < W; h += 8)
+            if (KR - 1 >= h && KR - 1 < h + 8) {
               asm volatile("" ::: "memory");
-              w[i] = nv;
+#pragma unroll
+              for (int i = h; i < h + 8 && i < W; ++i)
+                if (i == KR - 1) {
+                  asm volatile("" ::: "memory");
+                  w[i] = nv;
+                }
             }
         }
       }
@@ -425,11 +407,10 @@ __global__ __launch_bounds__(256) void k_band_mid(const z64 *__restrict__ mid, i
     if (wave == 0) {
       const z64 v = S[lane][k];
       const double a1 = zabs1(v);
-      double key = lane >= k && lane < s ? (a1 == a1 ? a1 : -1.0) : -2.0;
-      int idx = lane >= k && lane < s ? lane : 1 << 30;
-      wave_argmax(key, idx);
-      const int p = __builtin_amdgcn_readfirstlane(idx < s ? idx : k);
-      const bool zero = !(lane_at(key, 0) > 0.0);
+      const double key_i = lane >= k && lane < s ? (a1 == a1 ? a1 : -1.0) : -2.0;
+      const double key = lane_at(wave_max(key_i), 0);
+      const int p = static_cast<int>(__builtin_ctzll(__builtin_amdgcn_ballot_w64(key_i == key)));
+      const bool zero = !(key > 0.0);
       if (zero && bad == 0) bad = k + 1;
       const z64 inv = zero ? zmake(0.0, 0.0) : band_recip(lane_at(v.x, p), lane_at(v.y, p));
       if (lane == 0) {
