@@ -388,18 +388,27 @@ template <typename T> void launch_splitk_reduce(hipStream_t s, const GemmArgs<T>
                      s, d);
 }
 
-// Products of fewer than kSmallTiles output tiles (two a compute unit) take k_gemm_ks;
-// from there on the tiles read less per flop and are as fast or faster (complex128, us:
-// 1000 x 1000 x 100 and 8 x 1000 x 128 x 128, 512 tiles each, 24 -> 20 and 28 -> 23;
-// below, 2 x 2000 x 160 x 1000, 320 tiles, 98 against 136).  In-place products (C is A
-// or B) need one workgroup per column block and keep the tiles.  Sixteen wavefronts
-// while that leaves units idle
-// (157 x 157 x 4001, 100 tiles: 41 us against 46 with eight); 32 x 16 tiles for
-// many tiles, where the operands' traffic counts: eight wavefronts for a long sum
-// (4000 x 160 x 4000: 349 us against 380), four for a short one, so that all
-// workgroups fit at once (4000 x 160 x 160: 24 us against 26).
-constexpr int64_t kSmallTiles = 512;
+// Output tiles below which a product takes k_gemm_ks; from there on the tiles read less
+// per flop and are as fast or faster.  complex128, us (k_gemm_ks, tiles):
+//   op = 1: 448 tiles, K = 100 24, 20; 384, K = 364 50, 55; 400, K = 364 54, 54; 800,
+//     K = 1500 322, 369; 960, K = 1500 407, 371
+//   op = ^* (each K step reads other rows): 400, K = 100 21, 20; 800, K = 364 87, 101;
+//     960, K = 1500 387, 406
+// complex64, and complex128 with the tiles' three-product form: 400, K = 364 34, 28; 308,
+// K = 364 25, 28.
+template <typename T> int64_t small_tiles(int ta, int cfg, int64_t K) {
+  if (ta != 0) return K > 128 ? 1024 : 512;
+  const bool m3 = kM3<T> || cfg == GEMM_SOLVE || cfg == GEMM_UPDATE;
+  return m3 || K < 512 ? 400 : K < 1024 ? 512 : 832;
+}
 
+// In-place products (C is A or B) need one workgroup per column block and keep the
+// tiles.  In k_gemm_ks: sixteen wavefronts while that leaves units idle and the sum is
+// long enough for them (157 x 157 x 4001, 100 tiles: 41 us against 46 with eight); four
+// for a sum of up to 64; 32 x 16 tiles for many tiles, where the operands' traffic
+// counts: eight wavefronts for a long sum (4000 x 160 x 4000: 349 us against 380), four
+// for a short one, so that all workgroups fit at once (4000 x 160 x 160: 24 us against
+// 26).
 template <typename T>
 void gemm_small(hipStream_t s, GemmArgs<T> d, int ta, int64_t work_elems) {
   const int64_t t16 = ((d.M + 15) / 16) * ((d.N + 15) / 16) * d.batch;
@@ -413,7 +422,9 @@ void gemm_small(hipStream_t s, GemmArgs<T> d, int ta, int64_t work_elems) {
       d.splits = static_cast<int32_t>((d.K + d.kchunk - 1) / d.kchunk);
     }
   }
-  if (t16 * d.splits <= 256 && t16 <= 128)
+  if (t16 <= 1024 && d.K <= 64)
+    launch_ks<T, 1, 1, 4>(s, d, ta);
+  else if (t16 * d.splits <= 256 && t16 <= 128)
     launch_ks<T, 1, 1, 16>(s, d, ta);
   else if (t16 > 1024 && d.K >= 1024)
     launch_ks<T, 2, 1, 8>(s, d, ta);
@@ -438,9 +449,10 @@ void gemm_impl(hipStream_t s, GemmArgs<T> d, int ta, int cfg, int64_t work_elems
   // Long sums over one to four tiles a compute unit: four ranges of K, if the caller has
   // a workspace (complex128, us: 4000 x 160 x 4000, 315 tiles, 349 -> 318; 6000 x 60 x
   // 6000, 188 tiles, 337 -> 309; op = ^* and fewer tiles are no faster)
-  const bool split = d.work && ta == 0 && d.K >= 2048 && tiles >= 160 && tiles < 2 * kSmallTiles &&
+  const bool split = d.work && ta == 0 && d.K >= 2048 && tiles >= 160 && tiles < 1024 &&
                      4 * d.batch * d.M * d.N <= work_elems;
-  if (d.A != d.C && d.B != d.C && cfg != GEMM_UPDATE_TALL && !split && tiles < kSmallTiles)
+  if (d.A != d.C && d.B != d.C && cfg != GEMM_UPDATE_TALL && !split &&
+      tiles < small_tiles<T>(ta, cfg, d.K))
     return gemm_small<T>(s, d, ta, work_elems);
   if (split) {
     d.kchunk = ((d.K + 3) / 4 + kTileK - 1) / kTileK * kTileK;
