@@ -1413,7 +1413,7 @@ static int solve_impl(feast_plan *p, const feast_z *dA, int64_t lda, const feast
 // solutions are the filter's solves with right-hand side Y itself (mixed plans
 // apply one FP64 refinement sweep: there is no outer iteration to absorb
 // complex64 solve errors); the moments are weighted node sums; the SVD step's
-// orthonormal basis of the moment block comes from shifted Cholesky QR3 (the
+// orthonormal basis of the moment block comes from shifted Cholesky QR (the
 // Rayleigh-Ritz pencil depends on the span only, so it has the eigenvalues the
 // SVD's left factor gives); the Rayleigh-Ritz steps reuse the projection, host eigensolver
 // and Ritz-residual pieces of Algorithm 5.
@@ -1750,7 +1750,7 @@ int feast_plan_set_m(feast_plan *p, int64_t m) {
 // are GPU products; the rank-revealing step is the pivoted Cholesky of the
 // s_dagger x s_dagger Gram matrix on the host (the pivots and |R_ii| of the
 // column-pivoted QR of the block); the basis U_1 of the t leading pivot
-// columns is orthonormalised on the GPU (shifted Cholesky QR3).
+// columns is orthonormalised on the GPU (shifted Cholesky QR).
 int feast_search(feast_plan *p, const feast_z *dA, int64_t lda, const feast_z *dB, int64_t ldb,
                  const feast_z *dY, int64_t ldy, int64_t ycols, int32_t p0, double alpha,
                  double tau, feast_z *dU1, int64_t ldu, feast_search_info *info) {
