@@ -543,7 +543,7 @@ void solve_nodes_mixed(feast_plan *p, const z64 *A, int64_t lda, const z64 *B, i
   const int N = p->N;
   hipStream_t s = p->s;
   z64 *Y = p->Y.as<z64>();
-  c64 *Yc = p->Yc.as<c64>();
+  c64 *Yc = p->Yc.as<c64>(), *Ycs = Yc + n * ldY;
   z64 *T1 = p->T1.as<z64>(), *T2 = p->T2.as<z64>();
   const c64 *F = p->F.as<c64>();
   const int32_t *perm = p->perm.as<int32_t>();
@@ -557,7 +557,7 @@ void solve_nodes_mixed(feast_plan *p, const z64 *A, int64_t lda, const z64 *B, i
            [&]() { feast::gather_rows<z64>(s, R, ldr, 0, perm, n, m, N, T1, ldY, sY); });
     ktimed(p, FEAST_K_Z2C, 24.0 * n * ldY,
            [&]() { feast::z_to_c(s, T1, ldY, 0, n, ldY, 1, Yc, ldY, 0, rn, rcnt); });
-    plan_trsolve<c64>(p, s, Yc, p->Yc2.as<c64>(), m, ldY, sY, 0);
+    plan_trsolve<c64>(p, s, Yc, Ycs, m, ldY, sY, 0);
     ktimed(p, FEAST_K_C2Z, 24.0 * n * ldY,
            [&]() { feast::c_to_z(s, Yc, ldY, 0, n, ldY, 1, Y, ldY, 0, rn, rcnt); });
   }
@@ -606,7 +606,7 @@ void solve_nodes_mixed(feast_plan *p, const z64 *A, int64_t lda, const z64 *B, i
            [&]() { feast::gather_rows<z64>(s, T1, ldY, sY, perm, n, m, N, T2, ldY, sY); });
     ktimed(p, FEAST_K_Z2C, 24.0 * n * ldY,
            [&]() { feast::z_to_c(s, T2, ldY, 0, n, ldY, 1, Yc, ldY, 0, rn, rcnt); });
-    plan_trsolve<c64>(p, s, Yc, p->Yc2.as<c64>(), m, ldY, sY, 0);
+    plan_trsolve<c64>(p, s, Yc, Ycs, m, ldY, sY, 0);
     if (sweep == 0) {
       // the first correction relative to the solution it corrects: about the
       // forward error of the complex64 solves, u32 cond(z_j B - A)
@@ -764,8 +764,7 @@ void ensure_workspace(feast_plan *p, bool with_nodes) {
   if (p->mixed() && with_nodes) {
     p->T1.alloc(zs * n * m * N);
     p->T2.alloc(zs * n * m * N);
-    p->Yc.alloc(sizeof(c64) * n * m * N);
-    p->Yc2.alloc(sizeof(c64) * n * m * N);
+    p->Yc.alloc(2 * sizeof(c64) * n * m * N);
   }
 }
 
@@ -1020,7 +1019,7 @@ int feast_plan_destroy(feast_plan *p) {
   for (hipEvent_t e : {p->ev_fork, p->ev_join, p->ev_orth})
     if (e) (void)hipEventDestroy(e);
   for (DevBuf *b : {&p->dz, &p->dw, &p->dwc, &p->adj, &p->adj_piv, &p->adj_info, &p->adj_inv, &p->F, &p->piv, &p->perm, &p->info, &p->Linv, &p->Uinv, &p->Linv2, &p->Uinv2, &p->cirr_w, &p->R,
-                    &p->Y, &p->Y2, &p->T1, &p->T2, &p->Yc, &p->Yc2, &p->W, &p->G, &p->splitws, &p->splitws2, &p->part, &p->nrm,
+                    &p->Y, &p->Y2, &p->T1, &p->T2, &p->Yc, &p->W, &p->G, &p->splitws, &p->splitws2, &p->part, &p->nrm,
                     &p->flag, &p->small, &p->fp, &p->rn})
     b->release();
   for (DevBuf *b : {&p->sp.rp, &p->sp.ci, &p->sp.va, &p->sp.vb, &p->sp.map, &p->sp.perm, &p->sp.Lf,
