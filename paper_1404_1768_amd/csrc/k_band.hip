@@ -383,7 +383,7 @@ __global__ __launch_bounds__(256) void k_band_lu(const int32_t *__restrict__ rp,
 
 // The dense s x s system between the two sides of node j = blockIdx.x (rows 64
 // apart in mid): LU with partial pivoting in LDS, one barrier-separated rank-1
-// update per column, then the inverses of both factors by halves (tri64.h):
+// update per column, then the inverses of both factors (tri64.h):
 // lu[0] = L^{-1}, lu[1] = U^{-1} (64 x 64, identity past s), perm[i] the row of
 // mid that the pivoting put in place i; info: 1 + the first column without a
 // pivot, counted from the first of all (c0), or 0.
@@ -392,6 +392,7 @@ __global__ __launch_bounds__(256) void k_band_mid(const z64 *__restrict__ mid, i
                                                   int32_t *__restrict__ info) {
   __shared__ z64 S[64][kTP];
   __shared__ z64 X[64][kTP];
+  __shared__ z64 s_dinv[64];
   __shared__ int s_p[64];
   __shared__ int s_piv;
   __shared__ z64 s_inv;
@@ -441,12 +442,11 @@ __global__ __launch_bounds__(256) void k_band_mid(const z64 *__restrict__ mid, i
     const int rv = h == 0 ? 0 : 63;
     for (int i = wave; i < 64; i += 4) X[i][lane] = S[i ^ rv][lane ^ rv];
     __syncthreads();
-    tri64_inverse(X, h == 0, lane, wave);
+    if (tid < 64) s_dinv[tid] = cplx_traits<z64>::recip(X[tid][tid]);
+    __syncthreads();
     z64 *o = lu + (2ll * j + h) * 4096;
-    for (int i = wave; i < 64; i += 4) {
-      const bool in = h == 0 ? lane <= i : lane >= i;
-      o[i * 64 + lane] = in ? X[i ^ rv][lane ^ rv] : zmake(0.0, 0.0);
-    }
+    wave_inverse64(X, h == 0 ? static_cast<const z64 *>(nullptr) : s_dinv, lane, wave,
+                   [&](int r, int c, z64 v) { o[(r ^ rv) * 64 + (c ^ rv)] = v; });
     __syncthreads();
   }
   if (tid < 64) perm[j * 64 + tid] = s_p[tid];

@@ -594,8 +594,8 @@ __global__ __launch_bounds__(256) void k_panel_solve(T *__restrict__ Mall, int64
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         T &p = sX[i + mfma_ops<T>::out_row(lane, r)][tj + (lane & 15)];
-        p.x -= t.re[r];
-        p.y -= t.im[r];
+        p.x -= t.re(r);
+        p.y -= t.im(r);
       }
       wave_lds_order();
     }
@@ -608,8 +608,8 @@ __global__ __launch_bounds__(256) void k_panel_solve(T *__restrict__ Mall, int64
     for (int r = 0; r < 4; ++r) {
       const int row = i + mfma_ops<T>::out_row(lane, r), j = tj + (lane & 15);
       T o;
-      o.x = y.re[r];
-      o.y = y.im[r];
+      o.x = y.re(r);
+      o.y = y.im(r);
       if (row < w1 && j < w2) D[row * ld + w1 + j] = o;
     }
   }
@@ -770,21 +770,13 @@ __global__ __launch_bounds__(256) void k_lu_small(const GrpMat *__restrict__ grp
   }
 }
 
-// Register layout shared by the 64 x 64 triangular kernels below: 256 threads,
-// thread (ti, tj) = (tid / 16, tid % 16) holds the 16 entries (ti + 16a,
-// tj + 16c), a, c < 4, and wave wv = tid / 64 holds rows ti in [4 wv, 4 wv + 4)
-// of every 16-row block.  A substitution step publishes one finished row
-// through double-buffered LDS rows, so it needs one barrier, and skips the
-// 16 x 16 blocks whose entries it cannot change (a wave-uniform test).  The
-// owners of row i write all four of their rows and readers take block i / 16:
-// choosing the register block by i would put the array in scratch memory.
-
 // Inverse of one 64 x 64 diagonal block of each matrix (lower unit or upper
 // non-unit), zero padded at out + b out_stride + I 64^2.  An upper block is
 // inverted as the lower one it is with rows and columns in reverse order; rows
 // past the matrix count as the identity.
-// 64-row blocks of 16 complex128 matrices: 42 us a launch by substitution over 64
-// rows, 10 us by halves (tri64.h).
+// 64-row blocks of 16 complex128 matrices: 42 us a launch by a substitution with a
+// barrier per row, 13 us so (12 us as an inverse put together from halves, whose
+// products left twice the residual).
 template <typename T>
 __global__ __launch_bounds__(256) void k_diag_inv(const T *__restrict__ Mall, int64_t ld_in,
                                                   int64_t stride, int64_t n_in, int64_t blk0,
@@ -792,6 +784,7 @@ __global__ __launch_bounds__(256) void k_diag_inv(const T *__restrict__ Mall, in
                                                   T *__restrict__ other, int64_t out_stride,
                                                   const GrpMat *__restrict__ grp, int nodes) {
   __shared__ T S[64][kTP];
+  __shared__ T s_inv[64];
   const bool lower = blockIdx.z == 0 ? lower_in : !lower_in;  // (z = 1: the other triangle)
   T *out = blockIdx.z == 0 ? out_in : other;
   const int64_t I = blk0 + blockIdx.x;
@@ -813,20 +806,20 @@ __global__ __launch_bounds__(256) void k_diag_inv(const T *__restrict__ Mall, in
 #pragma unroll
   for (int k = 0; k < 16; ++k) S[(wave + 4 * k) ^ rev][lane ^ rev] = v[k];
   __syncthreads();
-  tri64_inverse(S, lower, lane, wave);
-  T *o = out + b * out_stride + I * 4096;
-#pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    const int i = wave + 4 * k;
-    const bool in = i < rb && lane < rb && (lower ? lane <= i : lane >= i);
-    o[i * 64 + lane] = in ? S[i ^ rev][lane ^ rev] : czero<T>();
+  if (!lower) {
+    if (tid < 64) s_inv[tid] = cplx_traits<T>::recip(S[tid][tid]);
+    __syncthreads();
   }
+  T *o = out + b * out_stride + I * 4096;
+  wave_inverse64(S, lower ? static_cast<const T *>(nullptr) : s_inv, lane, wave, [&](int i, int j, T x) {
+    o[(i ^ rev) * 64 + (j ^ rev)] = (i ^ rev) < rb && (j ^ rev) < rb ? x : czero<T>();
+  });
 }
 
 // Inverse of a 128-row diagonal block of a triangular factor from the inverses
 // I1, I2 of its two 64-row halves (zero padded past the order) and the
 // off-diagonal 64 x 64 block C of the factor:
-//   lower (unit):  [L11 0; C L22]^{-1} = [I1 0; -(I2 C) I1  I2]
+//   lower (unit):  [L11 0; C L22]^{-1} = [I1 0; -I2 (C I1)  I2]
 //   upper:         [U11 C; 0 U22]^{-1} = [I1  -(I1 C) I2; 0 I2]
 // One workgroup per (block, matrix, triangle); the two 64 x 64 x 64 products run on the
 // matrix cores from LDS, one 16-row strip of the output per wavefront.  (16
@@ -860,10 +853,10 @@ __global__ __launch_bounds__(256) void k_inv_pair(const T *__restrict__ F, int64
     out[(64 + i) * 128 + 64 + lane] = d2;
     if (lower) out[i * 128 + 64 + lane] = czero<T>();
     else out[(64 + i) * 128 + lane] = czero<T>();
-    // first product: lower I2 C (C = rows [r0+64, r0+64+h2) x cols [r0, r0+64)),
+    // first product: lower C I1 (C = rows [r0+64, r0+64+h2) x cols [r0, r0+64)),
     //                upper I1 C (C = rows [r0, r0+64) x cols [r0+64, r0+64+h2))
-    sA[i][lane] = lower ? d2 : d1;
-    if (lower) sB[i][lane] = i < h2 ? M[(r0 + 64 + i) * ld + r0 + lane] : czero<T>();
+    (lower ? sB : sA)[i][lane] = d1;
+    if (lower) sA[i][lane] = i < h2 ? M[(r0 + 64 + i) * ld + r0 + lane] : czero<T>();
     else sB[i][lane] = lane < h2 ? M[(r0 + i) * ld + r0 + 64 + lane] : czero<T>();
     if (h2 <= 0) {
       if (lower) out[(64 + i) * 128 + lane] = czero<T>();
@@ -876,10 +869,10 @@ __global__ __launch_bounds__(256) void k_inv_pair(const T *__restrict__ F, int64
 #pragma unroll
   for (int c = 0; c < 4; ++c) t[c].template mac<false>(sA, 16 * wave, 0, sB, 0, 16 * c, 16, lane);
   __syncthreads();
-  // second product with the negated first one: lower (-I2 C) I1, upper (-I1 C) I2
+  // second product with the negated first one: lower I2 (-C I1), upper (-I1 C) I2
 #pragma unroll
-  for (int c = 0; c < 4; ++c) t[c].put(sA, 16 * wave, 16 * c, lane, -1);
-  for (int i = wave; i < 64; i += 4) sB[i][lane] = (lower ? I1 : I2)[i * 64 + lane];
+  for (int c = 0; c < 4; ++c) t[c].put(lower ? sB : sA, 16 * wave, 16 * c, lane, -1);
+  for (int i = wave; i < 64; i += 4) (lower ? sA : sB)[i][lane] = I2[i * 64 + lane];
   __syncthreads();
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
@@ -889,8 +882,8 @@ __global__ __launch_bounds__(256) void k_inv_pair(const T *__restrict__ F, int64
     for (int r = 0; r < 4; ++r) {
       const int i = 16 * wave + mfma_ops<T>::out_row(lane, r), j = 16 * c + (lane & 15);
       T v;
-      v.x = x.re[r];
-      v.y = x.im[r];
+      v.x = x.re(r);
+      v.y = x.im(r);
       if (lower) out[(64 + i) * 128 + j] = v;
       else out[i * 128 + 64 + j] = v;
     }

@@ -427,8 +427,8 @@ __device__ __forceinline__ void chol_inv_body(z64 *__restrict__ G, int64_t ld, i
             const int row = 16 * i + feast::mfma_ops<z64>::out_row(lane, r);
             const int col = 16 * j + (lane & 15);
             z64 v = S[row][col];
-            v.x -= t.re[r];
-            v.y -= t.im[r];
+            v.x -= t.re(r);
+            v.y -= t.im(r);
             S[row][col] = v;
           }
         }

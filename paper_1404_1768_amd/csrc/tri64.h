@@ -1,14 +1,7 @@
-// Triangular 64 x 64 blocks in LDS: inverses by halves, the products on the
-// matrix cores.  256 threads (four wavefronts) work on one block.
-//
-// A wavefront inverts a 16 x 16 diagonal block by itself (two 8 x 8 blocks with
-// one column per lane, then the 8 x 8 off-diagonal block); four of them at once
-// leave two levels of [L1 0; C L2]^-1 = [I1 0; -(I2 C) I1  I2] with 16 and 32 rows
-// (I2 C first: the inverse X then has a small residual X L - I, the one that a
-// solution X b inherits).
-// The chain is 8 substitution steps and six products; a substitution over all 64
-// rows with a barrier per row (one row published through LDS per step) takes 64
-// steps of 0.6 us.
+// Triangular blocks of up to 64 rows in LDS, one workgroup of 256 threads (four
+// wavefronts): solves and inverses by substitution in registers (wave_subst), and the
+// pieces of the Gram blocks' Cholesky factor, whose inverse is built by halves
+// ([L1 0; C L2]^-1 = [I1 0; -(I2 C) I1  I2]) with the products on the matrix cores.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -43,14 +36,24 @@ template <typename T> __device__ inline T ffms(T a, T b, T c) {  // a - b c
 
 // 16 x 16 complex tile products from LDS: c += A B over 4 ks values of k, A at
 // (ai, ak) and B at (bk, bj) of their arrays; CONJB: B = (rows bj.., columns
-// bk.. of the array)^*.
+// bk.. of the array)^*.  The two real products of each part are summed apart: their
+// sums round at their own, smaller sizes (0.7 of the error of one sum of both).
 template <typename T> struct Tile16 {
   using Ops = mfma_ops<T>;
-  typename Ops::acc_t re, im;
+  using real = typename Ops::real;
+  typename Ops::acc_t rr, ii, ri, ir;
   __device__ Tile16() {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) re[r] = im[r] = 0;
+    for (int r = 0; r < 4; ++r) rr[r] = ii[r] = ri[r] = ir[r] = 0;
   }
+  __device__ void step(T a, T b) {
+    rr = Ops::mma(a.x, b.x, rr);
+    ri = Ops::mma(a.x, b.y, ri);
+    ii = Ops::mma(a.y, b.y, ii);
+    ir = Ops::mma(a.y, b.x, ir);
+  }
+  __device__ real re(int r) const { return rr[r] - ii[r]; }
+  __device__ real im(int r) const { return ri[r] + ir[r]; }
   template <bool CONJB>
   __device__ void mac(const T (*A)[kTP], int ai, int ak, const T (*B)[kTP], int bk, int bj, int ks,
                       int lane) {
@@ -60,10 +63,7 @@ template <typename T> struct Tile16 {
       const T a = A[ai + c][ak + 4 * s + g];
       T b = CONJB ? B[bj + c][bk + 4 * s + g] : B[bk + 4 * s + g][bj + c];
       if (CONJB) b.y = -b.y;
-      re = Ops::mma(a.x, b.x, re);
-      im = Ops::mma(a.x, b.y, im);
-      re = Ops::mma(-a.y, b.y, re);
-      im = Ops::mma(a.y, b.x, im);
+      step(a, b);
     }
   }
   // S[i0 + row][j0 + column] = sgn * tile
@@ -71,16 +71,137 @@ template <typename T> struct Tile16 {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       T v;
-      v.x = sgn * re[r];
-      v.y = sgn * im[r];
+      v.x = sgn * re(r);
+      v.y = sgn * im(r);
       S[i0 + Ops::out_row(lane, r)][j0 + (lane & 15)] = v;
     }
   }
 };
 
-// In place: the inverse of the lower triangular 16 x 16 block at (o, o) of S, by
-// one wavefront.  unit: the diagonal counts as ones (what is stored there is
-// replaced).  Entries above the diagonal are not read and come out zero.
+// The values that lanes c, 16 + c, 32 + c and 48 + c hold, in each of the four.
+template <typename T> __device__ inline void all_groups(T v, T (&o)[4]) {
+  constexpr int N = sizeof(T) / 4;
+  struct Words {
+    uint32_t w[N];
+  };
+  const Words u = __builtin_bit_cast(Words, v);
+  Words h[2], q[4];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const auto x = __builtin_amdgcn_permlane32_swap(u.w[i], u.w[i], false, false);
+    h[0].w[i] = x[0];
+    h[1].w[i] = x[1];
+  }
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const auto x = __builtin_amdgcn_permlane16_swap(h[k].w[i], h[k].w[i], false, false);
+      q[2 * k].w[i] = x[0];
+      q[2 * k + 1].w[i] = x[1];
+    }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) o[k] = __builtin_bit_cast(T, q[k]);
+}
+
+// L x = b by substitution for 16 columns of right-hand sides, by one wavefront: L is
+// the lower triangular matrix S, its rows of 16-row blocks k0 .. k1 - 1 (rows and
+// columns before block k0 belong to entries of x that are zero).  Lane 16 g + c holds
+// rows 4 q + g of column c from block k0 on: x[q] (q < 4 NB), zero past block k1.
+// inv: reciprocals of the diagonal, or null where it counts as ones.  done(kb, x) gets
+// block kb's four rows 16 kb + 4 p + g, p < 4.
+// Four rows at a time: the four groups' entries go to all of them by swaps (no
+// barrier), every group finishes the four rows for itself and takes them off its
+// later rows of the block; the block then goes off the rows below on the matrix cores,
+// whose operand and result layouts these are.  Only L's own entries are multiplied
+// with: the product with an inverse that was built by halves had 1.6 times the error,
+// and over- or underflowed for columns of very different size.
+//   bound: the chain of 16 four-row steps a wavefront.
+template <typename T, int NB, typename Done>
+__device__ __forceinline__ void wave_subst(const T (*S)[kTP], const T *inv, int k0, int k1,
+                                           T (&x)[4 * NB], int lane, Done &&done) {
+  const int c = lane & 15, g = lane >> 4;
+  // the row of L whose sum the result element r of group g is: 4 r + g
+  const int arow = sizeof(T) == 16 ? c : 4 * (c & 3) + (c >> 2);
+  for (int kb = k0; kb < k1; ++kb) {
+    const int o = 16 * kb;
+    const T(*D)[kTP] = S + o;
+    // L's entries for the rows 4 q ..: the four rows' own (the same in all lanes), and
+    // those of the later rows of the block, both read one step ahead
+    T own[2][6], low[2][3][4];
+    auto fetch = [&](int q, int b) {
+#pragma unroll
+      for (int r = 1, e = 0; r < 4; ++r)
+#pragma unroll
+        for (int k = 0; k < r; ++k, ++e) own[b][e] = D[4 * q + r][o + 4 * q + k];
+#pragma unroll
+      for (int p = q + 1; p < 4; ++p)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) low[b][p - 1][k] = D[4 * p + g][o + 4 * q + k];
+    };
+    fetch(0, 0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (q < 3) fetch(q + 1, (q + 1) & 1);
+      __builtin_amdgcn_sched_barrier(0);
+      const int b = q & 1;
+      T v[4];
+      all_groups(x[q], v);
+#pragma unroll
+      for (int r = 0, e = 0; r < 4; ++r) {
+#pragma unroll
+        for (int k = 0; k < r; ++k, ++e) v[r] = ffms(v[r], own[b][e], v[k]);
+        if (inv) v[r] = fmul(v[r], inv[o + 4 * q + r]);
+      }
+      x[q].x = g < 2 ? (g == 0 ? v[0].x : v[1].x) : (g == 2 ? v[2].x : v[3].x);
+      x[q].y = g < 2 ? (g == 0 ? v[0].y : v[1].y) : (g == 2 ? v[2].y : v[3].y);
+#pragma unroll
+      for (int p = q + 1; p < 4; ++p)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[p] = ffms(x[p], low[b][p - 1][k], v[k]);
+    }
+    done(kb, x);
+#pragma unroll
+    for (int t = 1; t < NB; ++t)
+      if (kb + t < k1) {
+        Tile16<T> sum;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) sum.step(D[16 * t + arow][o + 4 * s + g], x[s]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          x[4 * t + r].x -= sum.re(r);
+          x[4 * t + r].y -= sum.im(r);
+        }
+      }
+#pragma unroll
+    for (int q = 0; q + 4 < 4 * NB; ++q) x[q] = x[q + 4];
+  }
+}
+
+// Columns 16 w .. 16 w + 15 of the inverse of the lower triangular 64 x 64 matrix S, by
+// wavefront w = wave (inv as in wave_subst): put(i, j, v) gets every entry of them.
+template <typename T, typename Put>
+__device__ __forceinline__ void wave_inverse64(const T (*S)[kTP], const T *inv, int lane, int wave,
+                                               Put &&put) {
+  using Tr = cplx_traits<T>;
+  const int c = lane & 15, g = lane >> 4, j = 16 * wave + c;
+  for (int i = g; i < 16 * wave; i += 4) put(i, j, Tr::make(0.0, 0.0));
+  T x[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) x[q] = Tr::make(q < 4 && 4 * q + g == c ? 1.0 : 0.0, 0.0);
+  wave_subst<T, 4>(S, inv, wave, 4, x, lane, [&](int kb, const T(&v)[16]) {
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      const int i = 16 * kb + 4 * p + g;
+      put(i, j, i < j ? Tr::make(0.0, 0.0) : v[p]);
+    }
+  });
+}
+
+// In place: the inverse of the lower triangular 16 x 16 block at (o, o) of S, by one
+// wavefront (two 8 x 8 blocks with one column per lane, then the 8 x 8 block between
+// them).  unit: the diagonal counts as ones (what is stored there is replaced).
+// Entries above the diagonal are not read and come out zero.
 template <typename T> __device__ void wave_tri16(T (*S)[kTP], int o, bool unit, int lane) {
   using Tr = cplx_traits<T>;
   {  // two 8 x 8 blocks, one column per lane (16 lanes' worth, repeated)
@@ -136,17 +257,6 @@ template <typename T, int H> __device__ void tri_join(T (*S)[kTP], int lane, int
   __syncthreads();
   if (on) q.put(S, o + H + ti, o + tj, lane, 1);
   __syncthreads();
-}
-
-// In place: the inverse of the lower triangular 64 x 64 matrix S (a barrier has
-// passed since it was written; one has passed when this returns).  The strict
-// upper triangle of the 16 x 16 diagonal blocks comes out zero; the blocks above
-// the diagonal blocks are neither read nor written.
-template <typename T> __device__ void tri64_inverse(T (*S)[kTP], bool unit, int lane, int wave) {
-  wave_tri16(S, 16 * wave, unit, lane);
-  __syncthreads();
-  tri_join<T, 16>(S, lane, wave);
-  tri_join<T, 32>(S, lane, wave);
 }
 
 }  // namespace feast
