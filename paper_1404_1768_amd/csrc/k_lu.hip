@@ -547,72 +547,42 @@ __global__ __launch_bounds__(256) void k_laswp_outside(T *__restrict__ Mall, int
 // traffic of C, so it runs on the VALU), else as a product.  (In one launch every
 // chunk would repeat the solve.)
 constexpr int kPU = 32;
-// One workgroup per matrix, 16 columns of X per wavefront, on the matrix cores: 16 rows
-// at a time, X_i = L_ii^{-1} (X_i - sum_{j<i} L_ij X_j) with the inverted 16 x 16 diagonal
-// blocks.  (With the inverse of all 64 rows of L11 the join took 7 us less, but the
-// factors of random matrices came out with more error: order 97 4.9e-15 relative
-// against 2.9e-15, order 128 7.1e-15 against 4.1e-15.)
-//   32 x 32, 16 complex128 matrices: 13 us a launch by substitution, 11.5 so; 64 x 64:
-//   13.7.
+// One workgroup per matrix, 16 columns of X per wavefront, by substitution (wave_subst).
+//   64 x 64, 16 complex128 matrices: 12.2 us a launch (13.6 with products with inverted
+//   16-row diagonal blocks, which left 1.6 times the residual).
 template <typename T, int R>
 __global__ __launch_bounds__(256) void k_panel_solve(T *__restrict__ Mall, int64_t ld_in,
                                                      int64_t stride, int64_t n_in, int64_t c0,
                                                      int w1, int w2,
                                                      const GrpMat *__restrict__ grp, int nodes) {
   __shared__ T sL[R][kTP];
-  __shared__ T sX[R][kTP];
   const MatRef<T> mr = mat_of<T>(grp, nodes, Mall, ld_in, stride, n_in, blockIdx.x);
   if (c0 + w1 + w2 > mr.n) return;
   const int64_t ld = mr.ld;
   T *D = mr.M + c0 * (ld + 1);
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  constexpr int PER = R / 4;  // rows of L11 and X a wavefront loads
+  constexpr int PER = R / 4;  // rows of L11 a wavefront loads, rows of X a lane holds
+  const int j = 16 * wave + (lane & 15);
   T v[PER], x[PER];
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
-    const int i = wave + 4 * k;
+    const int i = wave + 4 * k, r = 4 * k + g;
     v[k] = (i < w1 && lane < w1) ? D[i * ld + lane] : czero<T>();
-    x[k] = (i < w1 && lane < w2) ? D[i * ld + w1 + lane] : czero<T>();
+    x[k] = (r < w1 && j < w2) ? D[r * ld + w1 + j] : czero<T>();
   }
 #pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    sL[wave + 4 * k][lane] = v[k];
-    sX[wave + 4 * k][lane] = x[k];
-  }
+  for (int k = 0; k < PER; ++k) sL[wave + 4 * k][lane] = v[k];
   __syncthreads();
-  if (wave < R / 16) wave_tri16(sL, 16 * wave, true, lane);
-  __syncthreads();
-  const int tj = 16 * wave;
-  if (tj >= w2) return;
+  if (16 * wave >= w2) return;
+  wave_subst<T, R / 16>(sL, static_cast<const T *>(nullptr), 0, (w1 + 15) / 16, x, lane,
+                        [&](int kb, const T(&y)[PER]) {
 #pragma unroll
-  for (int i = 0; i < R; i += 16) {
-    if (i >= w1) break;
-    Tile16<T> t;
-    if (i > 0) {
-      t.template mac<false>(sL, i, 0, sX, 0, tj, i / 4, lane);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        T &p = sX[i + mfma_ops<T>::out_row(lane, r)][tj + (lane & 15)];
-        p.x -= t.re(r);
-        p.y -= t.im(r);
-      }
-      wave_lds_order();
+    for (int p = 0; p < 4; ++p) {
+      const int r = 16 * kb + 4 * p + g;
+      if (r < w1 && j < w2) D[r * ld + w1 + j] = y[p];
     }
-    Tile16<T> y;
-    y.template mac<false>(sL, i, i, sX, i, tj, 4, lane);
-    wave_lds_order();
-    y.put(sX, i, tj, lane, 1);
-    wave_lds_order();
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row = i + mfma_ops<T>::out_row(lane, r), j = tj + (lane & 15);
-      T o;
-      o.x = y.re(r);
-      o.y = y.im(r);
-      if (row < w1 && j < w2) D[row * ld + w1 + j] = o;
-    }
-  }
+  });
 }
 
 template <typename T>

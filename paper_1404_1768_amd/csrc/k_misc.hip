@@ -405,7 +405,7 @@ __device__ __forceinline__ void chol_inv_body(z64 *__restrict__ G, int64_t ld, i
         X[o + (e >> 4)][o + (e & 15)] =
             (e & 15) <= (e >> 4) ? S[o + (e >> 4)][o + (e & 15)] : make_double2(0.0, 0.0);
       feast::wave_lds_order();
-      feast::wave_tri16(X, o, false, lane);
+      feast::wave_tri16(X, o, lane);
     }
     __syncthreads();
     if (wave > k && wave < nb16) {  // L_ik = A_ik L_kk^{-*} for the wavefront's row block

@@ -200,9 +200,8 @@ __device__ __forceinline__ void wave_inverse64(const T (*S)[kTP], const T *inv, 
 
 // In place: the inverse of the lower triangular 16 x 16 block at (o, o) of S, by one
 // wavefront (two 8 x 8 blocks with one column per lane, then the 8 x 8 block between
-// them).  unit: the diagonal counts as ones (what is stored there is replaced).
-// Entries above the diagonal are not read and come out zero.
-template <typename T> __device__ void wave_tri16(T (*S)[kTP], int o, bool unit, int lane) {
+// them).  Entries above the diagonal are not read and come out zero.
+template <typename T> __device__ void wave_tri16(T (*S)[kTP], int o, int lane) {
   using Tr = cplx_traits<T>;
   {  // two 8 x 8 blocks, one column per lane (16 lanes' worth, repeated)
     const int d = o + (lane & 8), j = lane & 7;
@@ -211,7 +210,7 @@ template <typename T> __device__ void wave_tri16(T (*S)[kTP], int o, bool unit, 
     for (int i = 0; i < 8; ++i) x[i] = Tr::make(i == j ? 1.0 : 0.0, 0.0);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      if (!unit) x[i] = fmul(x[i], Tr::recip(S[d + i][d + i]));
+      x[i] = fmul(x[i], Tr::recip(S[d + i][d + i]));
 #pragma unroll
       for (int r = i + 1; r < 8; ++r) x[r] = ffms(x[r], S[d + r][d + i], x[i]);
     }
