@@ -324,9 +324,10 @@ __global__ __launch_bounds__(256) void k_add_shift(z64 *__restrict__ G, int64_t 
 // triangle; the strict upper one holds nothing of use), by one wavefront: lane
 // (g, c) = (lane / 16, lane % 16) holds the entries (c, 4 e + g), e < 4, and a
 // step passes its column through LDS, divided by nothing: the columns are scaled
-// by 1 / sqrt(pivot) at the end, together.
+// by 1 / sqrt(pivot) at the end, together.  rows: those of the matrix (the block's
+// others are the identity's).
 // Returns 1 + the first non-positive pivot of the block, or 0.
-__device__ inline int chol16(z64 (*S)[feast::kTP], int o, int lane) {
+__device__ inline int chol16(z64 (*S)[feast::kTP], int o, int rows, int lane) {
   const int c = lane & 15, g = lane >> 4;
   z64 a[4];
 #pragma unroll
@@ -351,6 +352,7 @@ __device__ inline int chol16(z64 (*S)[feast::kTP], int o, int lane) {
     double rd = __builtin_amdgcn_rcp(d);  // (d is a positive Gram entry; two Newton steps)
     rd = fma(rd, fma(-d, rd, 1.0), rd);
     rd = fma(rd, fma(-d, rd, 1.0), rd);
+    if (c >= rows) rd = 0.0;  // (1 / d may be infinite: not into the rows past the matrix)
     const double qr = ai.x * rd, qi = ai.y * rd;
     // a_cj -= (a_ck / d) conj(a_jk) for j > k (columns of finished steps are dead)
 #pragma unroll
@@ -398,7 +400,7 @@ __device__ __forceinline__ void chol_inv_body(z64 *__restrict__ G, int64_t ld, i
   for (int k = 0; k < nb16; ++k) {
     const int o = 16 * k;
     if (wave == 0) {
-      const int bad = chol16(S, o, lane);
+      const int bad = chol16(S, o, jb - o, lane);
       if (bad && lane == 0 && flag[0] == 0) flag[0] = col0 + o + bad;
       feast::wave_lds_order();
       for (int e = lane; e < 256; e += 64)
