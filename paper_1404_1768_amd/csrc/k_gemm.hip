@@ -337,36 +337,38 @@ template <typename T> int sub_tile_n(int64_t N) {
   return 15 * wide <= 16 * narrow ? kSubN<T> : kTileN;
 }
 
+// (each launch's grid is counted in the tiles of the kernel that it names)
 template <typename T>
 void launch_tiles(hipStream_t s, const GemmArgs<T> &d, int ta, int cfg) {
-  const bool tall = cfg == GEMM_UPDATE_TALL;
-  const int bm = tall ? 128 : kTileM;
-  const bool wide = d.A == d.C || !tile_spans_fit(d, ta, bm);
   // C -= op(A) B is recognised from alpha = -1, beta = 1 without split-K
   const bool sub = d.splits == 1 && d.alpha.x == -1.0 && d.alpha.y == 0.0 && d.beta.x == 1.0 &&
                    d.beta.y == 0.0;
-  const int bn = wide || tall ? 64 : ta == 0 && sub ? sub_tile_n<T>(d.N) : kTileN;
-  const int64_t padded = padded_tiles(d, wide ? kTileM : bm, bn);
-  const dim3 grid(static_cast<unsigned>(padded));
-  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, d, padded); };
+  const bool tall = cfg == GEMM_UPDATE_TALL && ta == 0 && sub;
+  const bool wide = d.A == d.C || !tile_spans_fit(d, ta, tall ? 128 : kTileM);
+  auto go = [&](auto kernel, int bm, int bn) {
+    const int64_t padded = padded_tiles(d, bm, bn);
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(padded)), dim3(256), 0, s, d, padded);
+  };
+  constexpr int M = kTileM, N = kTileN, NS = kSubN<T>;
   if (wide) {
     if (ta == 0)
-      sub ? go(k_gemm_wide<T, 0, true>) : go(k_gemm_wide<T, 0, false>);
+      sub ? go(k_gemm_wide<T, 0, true>, M, 64) : go(k_gemm_wide<T, 0, false>, M, 64);
     else
-      sub ? go(k_gemm_wide<T, 2, true>) : go(k_gemm_wide<T, 2, false>);
+      sub ? go(k_gemm_wide<T, 2, true>, M, 64) : go(k_gemm_wide<T, 2, false>, M, 64);
   } else if (ta == 0 && sub) {
+    const bool narrow = sub_tile_n<T>(d.N) == N;
     if (tall)
-      go(k_gemm_update<T, 128, 64>);
-    else if (cfg == GEMM_UPDATE)
-      bn == kTileN ? go(k_gemm_update<T, kTileM, kTileN>) : go(k_gemm_update<T, kTileM, kSubN<T>>);
+      go(k_gemm_update<T, 128, 64>, 128, 64);
     else if (cfg == GEMM_SOLVE)
-      go(k_gemm_solve<T>);
+      go(k_gemm_solve<T>, M, N);
+    else if (cfg == GEMM_UPDATE)
+      narrow ? go(k_gemm_update<T, M, N>, M, N) : go(k_gemm_update<T, M, NS>, M, NS);
     else
-      bn == kTileN ? go(k_gemm<T, 0, true>) : go(k_gemm<T, 0, true, kSubN<T>>);
+      narrow ? go(k_gemm<T, 0, true>, M, N) : go(k_gemm<T, 0, true, NS>, M, NS);
   } else if (ta == 0) {
-    go(k_gemm<T, 0, false>);
+    go(k_gemm<T, 0, false>, M, N);
   } else {
-    sub ? go(k_gemm<T, 2, true>) : go(k_gemm<T, 2, false>);
+    sub ? go(k_gemm<T, 2, true>, M, N) : go(k_gemm<T, 2, false>, M, N);
   }
 }
 
