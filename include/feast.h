@@ -552,7 +552,10 @@ int feast_zgetrs_batched_noalloc(int64_t n, int64_t nrhs, int32_t batch, const f
 
 /* C_b = alpha op(A_b) B_b + beta C_b with op(A) = A (transA = 0, A is M x K)
  * or op(A) = A^* (transA = 2, A stored K x M); B is K x N, C is M x N.  The
- * FP64 MFMA complex GEMM used by every dense step of the path. */
+ * FP64 MFMA complex GEMM used by every dense step of the path.  dC may be dA
+ * (N <= 64, and M <= 64 unless transA = 0 with the same leading dimension and
+ * stride) or dB (M <= 64, and N <= 64 unless leading dimension and stride are
+ * the same); otherwise C overlaps neither. */
 int feast_zgemm_batched(int32_t transA, int64_t M, int64_t N, int64_t K, feast_z alpha,
                         const feast_z *dA, int64_t lda, int64_t strideA, const feast_z *dB,
                         int64_t ldb, int64_t strideB, feast_z beta, feast_z *dC, int64_t ldc,

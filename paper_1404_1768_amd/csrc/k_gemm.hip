@@ -36,8 +36,8 @@ void k_gemm(const GemmArgs<T> d, int64_t grid_total) {
       d, xcd_remap(blockIdx.x, grid_total));
 }
 
-// Strides past the reach of a 32-bit offset, and C on A (row blocks no wider than a
-// tile, hence 64 columns): 64-bit addresses.
+// Strides past the reach of a 32-bit offset, and C on A or on B's rows of another
+// length (no wider than a tile, hence 64 columns): 64-bit addresses.
 template <typename T, int TA, bool SUB>
 __global__ __launch_bounds__(256)
 void k_gemm_wide(const GemmArgs<T> d, int64_t grid_total) {
@@ -344,7 +344,10 @@ void launch_tiles(hipStream_t s, const GemmArgs<T> &d, int ta, int cfg) {
   const bool sub = d.splits == 1 && d.alpha.x == -1.0 && d.alpha.y == 0.0 && d.beta.x == 1.0 &&
                    d.beta.y == 0.0;
   const bool tall = cfg == GEMM_UPDATE_TALL && ta == 0 && sub;
-  const bool wide = d.A == d.C || !tile_spans_fit(d, ta, tall ? 128 : kTileM);
+  // C on A, or on B with rows of another length: an output of at most 64 x 64 has one
+  // workgroup (64 columns), which has read all its operands when it writes
+  const bool wide = d.A == d.C || (d.B == d.C && (d.ldb != d.ldc || d.sB != d.sC)) ||
+                    !tile_spans_fit(d, ta, tall ? 128 : kTileM);
   auto go = [&](auto kernel, int bm, int bn) {
     const int64_t padded = padded_tiles(d, bm, bn);
     hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(padded)), dim3(256), 0, s, d, padded);

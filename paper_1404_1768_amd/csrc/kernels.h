@@ -50,7 +50,8 @@ enum { GEMM_SQUARE = 0, GEMM_UPDATE = 3, GEMM_UPDATE_TALL = 4, GEMM_SOLVE = 5 };
 
 // C_b = alpha op(A_b) B_b + beta C_b; transA 0: A is M x K; 2: A stored K x M, op = ^*.
 // `work` (optional, work_elems entries) enables split-K for small outputs.
-// In-place products (C is B) need M <= 64: one workgroup per column block.
+// In-place products need one workgroup per block of rows (C is A: N <= 64) or columns
+// (C is B: M <= 64, and N <= 64 unless their rows and strides are the same).
 void zgemm(hipStream_t s, int transA, int64_t M, int64_t N, int64_t K, z64 alpha, const z64 *A,
            int64_t lda, int64_t sA, const z64 *B, int64_t ldb, int64_t sB, z64 beta, z64 *C,
            int64_t ldc, int64_t sC, int32_t batch, z64 *work = nullptr, int64_t work_elems = 0,
