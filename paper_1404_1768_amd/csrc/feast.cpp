@@ -103,7 +103,7 @@ class ScratchPool {
     hipError_t e = hipMalloc(&b.p, b.bytes);
     if (e == hipErrorOutOfMemory) {
       (void)hipGetLastError();
-      trim();
+      trim_scratch();
       e = hipMalloc(&b.p, b.bytes);
     }
     if (e != hipSuccess) throw HipError{e, "hipMalloc"};
@@ -384,13 +384,60 @@ void trsolve(hipStream_t s, const T *F, int64_t ld, int64_t fstride, int32_t bat
 }
 
 // The plan's solves: leaves on its inverted 128 x 128 diagonal blocks; S as
-// Y (same leading dimension and node stride).
+// Y (same leading dimension and node stride), or null: in place, on the 64 x 64 ones.
 template <typename T>
 void plan_trsolve(feast_plan *p, hipStream_t s, T *Y, T *S, int64_t m, int64_t ldy, int64_t sY,
                   int trans) {
-  trsolve<T>(s, p->F.as<T>(), p->n, p->fstride(), p->N, p->n, p->Linv2.as<T>(), p->Uinv2.as<T>(),
-             p->istride2(), Y, m, ldy, sY, S, ldy, sY, trans, 128);
+  if (S)
+    trsolve<T>(s, p->F.as<T>(), p->n, p->fstride(), p->N, p->n, p->Linv2.as<T>(), p->Uinv2.as<T>(),
+               p->istride2(), Y, m, ldy, sY, S, ldy, sY, trans, 128);
+  else
+    trsolve<T>(s, p->F.as<T>(), p->n, p->fstride(), p->N, p->n, p->Linv.as<T>(), p->Uinv.as<T>(),
+               p->istride(), Y, m, ldy, sY, Y, ldy, sY, trans, kIB);
 }
+
+// The plans that may own solve scratch.  (Never destroyed, as the pool.)
+struct SolvePlans {
+  std::mutex mu;
+  std::vector<feast_plan *> all;
+};
+SolvePlans &solve_plans() {
+  static SolvePlans *plans = new SolvePlans;
+  return *plans;
+}
+
+// Holds a plan's solve scratch while its solves are enqueued: block<T>() is null where
+// there is no memory for it.
+struct SolveScratch {
+  feast_plan *p;
+  explicit SolveScratch(feast_plan *plan, size_t bytes) : p(plan) {
+    {
+      std::lock_guard<std::mutex> lock(solve_plans().mu);
+      auto &all = solve_plans().all;
+      if (std::find(all.begin(), all.end(), p) == all.end()) all.push_back(p);
+      p->y2_held = true;
+    }
+    try {
+      p->Y2.alloc(bytes);
+    } catch (const HipError &e) {
+      if (e.e != hipErrorOutOfMemory) {
+        drop();
+        throw;
+      }
+      (void)hipGetLastError();
+    }
+  }
+  SolveScratch(const SolveScratch &) = delete;
+  SolveScratch &operator=(const SolveScratch &) = delete;
+  ~SolveScratch() { drop(); }
+  template <typename T> T *block() const { return p->Y2.as<T>(); }
+
+ private:
+  void drop() {
+    std::lock_guard<std::mutex> lock(solve_plans().mu);
+    p->y2_held = false;
+  }
+};
 
 // ---------------------------------------------------------------------------
 // Plan helpers
@@ -522,8 +569,8 @@ void solve_nodes_z(feast_plan *p, const z64 *R, int64_t ldr, int64_t cols) {
   ktimed(p, FEAST_K_GATHER, 16.0 * n * cols * (1 + p->N), [&]() {
     feast::gather_rows<z64>(p->s, R, ldr, 0, p->perm.as<int32_t>(), n, cols, p->N, Y, ldY, m);
   });
-  p->Y2.alloc(sizeof(z64) * n * ldY);
-  plan_trsolve<z64>(p, p->s, Y, p->Y2.as<z64>(), cols, ldY, m, 0);
+  const SolveScratch scratch(p, sizeof(z64) * n * ldY);
+  plan_trsolve<z64>(p, p->s, Y, scratch.block<z64>(), cols, ldY, m, 0);
 }
 
 // Mixed form: complex64 LU solves; FP64 residual r_j = R - (z_j B - A) Y_j of
@@ -543,7 +590,9 @@ void solve_nodes_mixed(feast_plan *p, const z64 *A, int64_t lda, const z64 *B, i
   const int N = p->N;
   hipStream_t s = p->s;
   z64 *Y = p->Y.as<z64>();
-  c64 *Yc = p->Yc.as<c64>(), *Ycs = Yc + n * ldY;
+  c64 *Yc = p->Yc.as<c64>();
+  const SolveScratch scratch(p, sizeof(c64) * n * ldY);
+  c64 *Ycs = scratch.block<c64>();
   z64 *T1 = p->T1.as<z64>(), *T2 = p->T2.as<z64>();
   const c64 *F = p->F.as<c64>();
   const int32_t *perm = p->perm.as<int32_t>();
@@ -705,7 +754,12 @@ constexpr double kNearOrthonormal = 0.1;  // ||X^* X - I||_F
 // Helpers shared with the batched driver (declared in plan.h).
 namespace feast_drv {
 
-void trim_scratch() { scratch_pool().trim(); }
+void trim_scratch() {
+  scratch_pool().trim();
+  std::lock_guard<std::mutex> lock(solve_plans().mu);
+  for (feast_plan *p : solve_plans().all)  // (hipFree waits for the solves under way)
+    if (!p->y2_held) p->Y2.release();
+}
 
 int fail(feast_plan *p, int code, const std::string &msg) {
   if (p) p->err = msg;
@@ -764,7 +818,7 @@ void ensure_workspace(feast_plan *p, bool with_nodes) {
   if (p->mixed() && with_nodes) {
     p->T1.alloc(zs * n * m * N);
     p->T2.alloc(zs * n * m * N);
-    p->Yc.alloc(2 * sizeof(c64) * n * m * N);
+    p->Yc.alloc(sizeof(c64) * n * m * N);
   }
 }
 
@@ -1005,6 +1059,11 @@ int feast_plan_create(feast_plan **plan, int64_t n, int64_t m, const feast_conto
 
 int feast_plan_destroy(feast_plan *p) {
   if (!p) return FEAST_OK;
+  {
+    std::lock_guard<std::mutex> lock(solve_plans().mu);
+    auto &all = solve_plans().all;
+    all.erase(std::remove(all.begin(), all.end(), p), all.end());
+  }
   if (p->s) (void)hipStreamSynchronize(p->s);
   for (hipEvent_t e : p->ev) (void)hipEventDestroy(e);
   for (hipEvent_t e : p->kev) (void)hipEventDestroy(e);

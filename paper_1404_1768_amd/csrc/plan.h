@@ -37,7 +37,7 @@ struct HipError {
     if (e_ != hipSuccess) throw HipError{e_, #x};   \
   } while (0)
 
-// Frees the idle scratch of the calls that own no plan.
+// Frees idle scratch: of the calls that own no plan, and of the plans' node solves.
 void trim_scratch();
 
 struct DevBuf {
@@ -101,9 +101,12 @@ struct feast_plan {
   DevBuf Linv2, Uinv2;  // inverted 128 x 128 diagonal blocks (the solves' leaves)
   double normA = 0.0, normB = 0.0;  // Frobenius norms of A and B (refinement test)
   // workspaces
-  DevBuf Y2;  // scratch of the FP64 node solves (as Y, allocated by the first dense one)
-  // Yc: solutions of the complex64 node solves, then the scratch of these solves, in one
-  // allocation: a second one made the making of a plan 20 us slower (n = 2003, m = 64, N = 16).
+  // Scratch of the dense node solves (as large as their solutions: Y, or Yc in the mixed
+  // form), allocated by the first of them.  The solves go without where there is no
+  // memory for it, and an allocation that fails takes it back from the plans whose
+  // solves are not being enqueued (y2_held).
+  DevBuf Y2;
+  bool y2_held = false;
   DevBuf R, Y, T1, T2, Yc, W, G, splitws, splitws2, part, nrm, flag, small;
   DevBuf rn;  // mixed form: ||R||_F^2 at rn[0] (scale of the complex64 solves), ||d_1||^2 and
               // ||Y_0||^2 of the first correction at rn[1], rn[2]; partials from rn[8]
