@@ -169,8 +169,12 @@ struct ScratchLease {
   ScratchLease(const ScratchLease &) = delete;
   ScratchLease &operator=(const ScratchLease &) = delete;
   ~ScratchLease() {
-    (void)hipStreamSynchronize(s);  // (the calls have waited already, unless they threw)
-    scratch_pool().give(b);
+    // (the calls have waited already, unless they threw; a stream that does not run dry
+    // may still use the block: freeing it waits for the device)
+    if (hipStreamSynchronize(s) == hipSuccess)
+      scratch_pool().give(b);
+    else
+      (void)hipFree(b.p);
   }
 };
 
