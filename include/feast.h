@@ -521,7 +521,9 @@ int feast_stop_rule(int32_t k, int32_t c_k, double e_k, int32_t c_prev, double e
  * P_b M_b = L_b U_b (L unit lower).  dPiv[b*n + i] is the 0-based row swapped
  * with row i at step i (LAPACK order).  dInfo[b] = 0, or 1 + the first column
  * with an exact zero pivot.  nb = panel width (64 or 128, 0 = automatic).  Synchronous
- * on `stream`.  The pivot test uses |re| + |im|, ties to the lowest row. */
+ * on `stream`.  The pivot test uses |re| + |im|, ties to the lowest row.
+ * Device scratch of this call and of feast_zgetrs_batched is kept for further
+ * ones, at most 1 GiB of it idle; feast_release_scratch gives it back. */
 int feast_zgetrf_batched(int64_t n, int32_t batch, feast_z *dM, int64_t ldm, int64_t strideM,
                          int32_t *dPiv, int32_t *dInfo, int32_t nb, void *stream);
 
@@ -560,6 +562,14 @@ int feast_zgemm_batched(int32_t transA, int64_t M, int64_t N, int64_t K, feast_z
                         const feast_z *dA, int64_t lda, int64_t strideA, const feast_z *dB,
                         int64_t ldb, int64_t strideB, feast_z beta, feast_z *dC, int64_t ldc,
                         int64_t strideC, int32_t batch, void *stream);
+
+/* Free the idle device scratch that the library keeps between calls: that of
+ * feast_zgetrf_batched and feast_zgetrs_batched, and of every plan the second
+ * block of its node solves (taken again by the next solve).  Scratch of calls
+ * that other threads are making stays theirs.  For programs that share the
+ * GPU's memory with other allocators; the library's own allocations do this by
+ * themselves before they fail. */
+int feast_release_scratch(void);
 
 /* Library version (major*10000 + minor*100 + patch). */
 int feast_version(void);

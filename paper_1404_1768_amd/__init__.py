@@ -12,4 +12,5 @@ from .binding import (FEAST_OK, FEAST_SINGULAR, FEAST_REFINE_STAGNATED, FEAST_EI
                       FP64, MIXED, FeastError, Plan, SolveResult, feast_filter, feast_project,
                       feast_solve, feast_nodes, feast_reduced_eig, feast_stop_rule, load,
                       zgemm_batched, zgetrf_batched, zgetrs_batched, zgetrs_batched_noalloc, LIB_PATH, feast_eig,
-                      Batch, BatchResult, enclosing_circle, region_inside, solve_region, csr_order)
+                      Batch, BatchResult, enclosing_circle, region_inside, solve_region, csr_order,
+                      release_scratch)

@@ -42,7 +42,7 @@ EXPORTED = [
     "feast_batch_last_error", "feast_batch_filter", "feast_batch_solve",
     "feast_search", "feast_plan_set_m", "feast_solve_from", "feast_enclosing_circle",
     "feast_region_select", "feast_cirr", "feast_zgetrs_batched_noalloc", "feast_solve_csr",
-    "feast_csr_order",
+    "feast_csr_order", "feast_release_scratch",
 ]
 
 
@@ -701,6 +701,13 @@ def zgetrs_batched_noalloc(LU, piv, X, trans: int = 0, stream=None):
     """As zgetrs_batched, with the library's fixed device scratch instead of
     allocations; asynchronous on the stream."""
     return _zgetrs("feast_zgetrs_batched_noalloc", LU, piv, X, trans, stream)
+
+
+def release_scratch():
+    """Free the device scratch that the library keeps idle between calls."""
+    rc = load().feast_release_scratch()
+    if rc != FEAST_OK:
+        raise FeastError(rc, "feast_release_scratch")
 
 
 def _zgetrs(name, LU, piv, X, trans, stream):

@@ -940,6 +940,13 @@ extern "C" {
 
 int feast_version(void) { return 10000; }
 
+int feast_release_scratch(void) {
+  return guarded(nullptr, []() {
+    trim_scratch();
+    return FEAST_OK;
+  });
+}
+
 void feast_opts_default(feast_opts *o) {
   if (!o) return;
   o->eps = 1e-10;
