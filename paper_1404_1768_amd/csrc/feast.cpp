@@ -1705,8 +1705,8 @@ int prepare_sparse(feast_plan *p, const feast_csr *A, const feast_csr *B) {
   const int N = p->N;
   const int64_t WC = kl + ku + 1;
   const feast::BandSplit bs = feast::BandSplit::of(n, sp.kl, sp.ku);
-  const int64_t vrows = 2 * static_cast<int64_t>(N) * bs.stride();  // rows of both sides of all nodes
-  sp.Lf.alloc(sizeof(z64) * vrows * std::max(bs.lmax(), 1));
+  const int64_t vrows = N * bs.node_rows();  // rows of both sides of all nodes
+  sp.Lf.alloc(sizeof(z64) * std::max<int64_t>(N * bs.node_l(), 1));
   sp.Uf.alloc(sizeof(z64) * vrows * WC);
   sp.Dinv.alloc(sizeof(z64) * vrows);
   sp.piv.alloc(sizeof(int32_t) * vrows);

@@ -23,6 +23,8 @@
 // are one wavefront's walk along the rows, so two of half the length halve their
 // time: n = 4800, kl = ku = 22, 16 nodes, 40 columns: LU 8.4 -> 4.5 ms, one
 // filter's solves 3.2 -> 1.7.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 #include "tri64.h"
@@ -119,34 +121,33 @@ __device__ inline z64 band_recip(double x, double y) {
 // (not a maximum with its index through every exchange), the leaving slot zeroed while
 // its posts are on their way (not by a multiply of every entry) and two-level slot
 // branches.
+//
+// One block of LDS, so that the per-column arrays sit at the low addresses (immediate
+// offsets) whatever the allocator's order.
+struct BandLuLds {
+  z64 sl[2][64];  // multipliers of column k (index 1 .. kl), by the parity of k
+  z64 colbuf[64];
+  int32_t srp[kBandCH + 1];
+  int info;
+  // the staged rows of two chunks (row q of a chunk at SR[b][q WC + c -
+  // (row - kl)], c its column); the first window's rows 0 .. kl pass
+  // through SR[0] kBandCH at a time
+  z64 SR[2][kBandCH * 64];
+};
 template <int W>
-__global__ __launch_bounds__(256) void k_band_lu(const int32_t *__restrict__ rp,
-                                                 const int32_t *__restrict__ ci,
-                                                 const z64 *__restrict__ va,
-                                                 const z64 *__restrict__ vb,
-                                                 const z64 *__restrict__ zn, const BandSplit sp,
-                                                 z64 *__restrict__ Lf, z64 *__restrict__ Uf,
-                                                 z64 *__restrict__ Dinv, int32_t *__restrict__ piv,
-                                                 z64 *__restrict__ mid,
-                                                 int32_t *__restrict__ info) {
+__device__ __forceinline__ void band_lu_side(BandLuLds &sm, const int32_t *__restrict__ rp,
+                                             const int32_t *__restrict__ ci,
+                                             const z64 *__restrict__ va,
+                                             const z64 *__restrict__ vb,
+                                             const z64 *__restrict__ zn, const BandSplit &sp,
+                                             z64 *__restrict__ Lf, z64 *__restrict__ Uf,
+                                             z64 *__restrict__ Dinv, int32_t *__restrict__ piv,
+                                             z64 *__restrict__ mid, int32_t *__restrict__ info) {
   const bool rev = blockIdx.y != 0;
   // this side's matrix: n rows (of N0 in all), nc columns to eliminate
   const int64_t N0 = sp.n, n = sp.rows(rev), nc = sp.cols(rev);
   const int kl = sp.lower(rev);
   const int KR = kl + 1, WC = sp.kl + sp.ku + 1;
-  // one block, so that the per-column arrays sit at the low LDS addresses
-  // (immediate offsets) whatever the allocator's order
-  struct Lds {
-    z64 sl[2][64];  // multipliers of column k (index 1 .. kl), by the parity of k
-    z64 colbuf[64];
-    int32_t srp[kBandCH + 1];
-    int info;
-    // the staged rows of two chunks (row q of a chunk at SR[b][q WC + c -
-    // (row - kl)], c its column); the first window's rows 0 .. kl pass
-    // through SR[0] kBandCH at a time
-    z64 SR[2][kBandCH * 64];
-  };
-  __shared__ Lds sm;
   auto &sl = sm.sl;
   auto &colbuf = sm.colbuf;
   auto &srp = sm.srp;
@@ -156,10 +157,10 @@ __global__ __launch_bounds__(256) void k_band_lu(const int32_t *__restrict__ rp,
   const int64_t v = 2 * static_cast<int64_t>(j) + blockIdx.y;  // this side of node j
   const int tid = threadIdx.x, lane = tid & 63;
   const z64 z = zn[j];
-  z64 *L = Lf + v * sp.stride() * sp.lmax();
-  z64 *U = Uf + v * sp.stride() * WC;
-  z64 *Di = Dinv + v * sp.stride();
-  int32_t *pv = piv + v * sp.stride();
+  z64 *L = Lf + sp.first_l(j, rev);
+  z64 *U = Uf + sp.first(j, rev) * WC;
+  z64 *Di = Dinv + sp.first(j, rev);
+  int32_t *pv = piv + sp.first(j, rev);
 
   // stage rows r0 .. r0 + cnt - 1 (all < n) into SR (row q at SR[q WC + c - (r0 + q - kl)]);
   // the bottom side's row r and column c are the matrix's N0 - 1 - r and N0 - 1 - c
@@ -379,6 +380,23 @@ __global__ __launch_bounds__(256) void k_band_lu(const int32_t *__restrict__ rp,
   }
   __syncthreads();
   if (tid == 0) info[v] = s_info;
+}
+// WA, WB: register windows of the top and the bottom side.
+template <int WA, int WB>
+__global__ __launch_bounds__(256) void k_band_lu(const int32_t *__restrict__ rp,
+                                                 const int32_t *__restrict__ ci,
+                                                 const z64 *__restrict__ va,
+                                                 const z64 *__restrict__ vb,
+                                                 const z64 *__restrict__ zn, const BandSplit sp,
+                                                 z64 *__restrict__ Lf, z64 *__restrict__ Uf,
+                                                 z64 *__restrict__ Dinv, int32_t *__restrict__ piv,
+                                                 z64 *__restrict__ mid,
+                                                 int32_t *__restrict__ info) {
+  __shared__ BandLuLds sm;
+  if (WA == WB || blockIdx.y == 0)
+    band_lu_side<WA>(sm, rp, ci, va, vb, zn, sp, Lf, Uf, Dinv, piv, mid, info);
+  else
+    band_lu_side<WB>(sm, rp, ci, va, vb, zn, sp, Lf, Uf, Dinv, piv, mid, info);
 }
 
 // The dense s x s system between the two sides of node j = blockIdx.x (rows 64
@@ -613,18 +631,23 @@ __device__ inline z64 band_fwd_row(z64 (&w)[N], const z64 *f, int p, z64 nv, int
   return y;
 }
 
+// Two chunks' staging (wave 1 fills one while wave 0 solves from the other).
+template <int WF> struct BandFwdLds {
+  z64 fac[2][kBandCH * WF];  // per row: 0, then the kl multipliers, zero-padded
+  z64 rows[2][kBandCH][64];  // the rows of R entering the window (both halves load them)
+  int32_t piv[2][kBandCH];
+};
 template <int WF>
-__global__ __launch_bounds__(128) void k_band_fwd(const z64 *__restrict__ Lf,
-                                                  const int32_t *__restrict__ piv,
-                                                  const BandSplit sp, const z64 *__restrict__ R,
-                                                  int64_t ldr, int64_t m, z64 *__restrict__ Y,
-                                                  int64_t ldy, int64_t sY) {
+__device__ __forceinline__ void band_fwd_side(BandFwdLds<WF> &sm, const z64 *__restrict__ Lf,
+                                              const int32_t *__restrict__ piv,
+                                              const BandSplit &sp, const z64 *__restrict__ R,
+                                              int64_t ldr, int64_t m, z64 *__restrict__ Y,
+                                              int64_t ldy, int64_t sY) {
   constexpr int UF = kBandU, H = WF / 2;
   static_assert(WF % 2 == 0, "two halves of the window");
-  // two chunks' staging (wave 1 fills one while wave 0 solves from the other)
-  __shared__ z64 fac[2][kBandCH * WF];  // per row: 0, then the kl multipliers, zero-padded
-  __shared__ z64 rows[2][kBandCH][64];  // the rows of R entering the window (both halves load them)
-  __shared__ int32_t s_piv[2][kBandCH];
+  auto &fac = sm.fac;
+  auto &rows = sm.rows;
+  auto &s_piv = sm.piv;
   const int j = blockIdx.x, wv = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5;
   const int64_t col = static_cast<int64_t>(blockIdx.y) * 32 + (lane & 31);
   const bool act = col < m;
@@ -634,9 +657,8 @@ __global__ __launch_bounds__(128) void k_band_fwd(const z64 *__restrict__ Lf,
   const bool rev = blockIdx.z != 0;
   const int64_t n = sp.rows(rev), nc = sp.cols(rev);  // (as in k_band_lu)
   const int kl = sp.lower(rev);
-  const int64_t v = 2 * static_cast<int64_t>(j) + blockIdx.z;
-  const z64 *L = Lf + v * sp.stride() * sp.lmax();
-  const int32_t *pv = piv + v * sp.stride();
+  const z64 *L = Lf + sp.first_l(j, rev);
+  const int32_t *pv = piv + sp.first(j, rev);
   z64 *Yj = Y + static_cast<int64_t>(j) * sY;
   if (rev) {  // rows in reverse order
     R += (sp.n - 1) * ldr;
@@ -701,6 +723,22 @@ __global__ __launch_bounds__(128) void k_band_fwd(const z64 *__restrict__ Lf,
   }
 }
 
+template <int WA, int WB>
+__global__ __launch_bounds__(128) void k_band_fwd(const z64 *__restrict__ Lf,
+                                                  const int32_t *__restrict__ piv,
+                                                  const BandSplit sp, const z64 *__restrict__ R,
+                                                  int64_t ldr, int64_t m, z64 *__restrict__ Y,
+                                                  int64_t ldy, int64_t sY) {
+  __shared__ union {
+    BandFwdLds<WA> a;
+    BandFwdLds<WB> b;
+  } sm;
+  if (WA == WB || blockIdx.z == 0)
+    band_fwd_side<WA>(sm.a, Lf, piv, sp, R, ldr, m, Y, ldy, sY);
+  else
+    band_fwd_side<WB>(sm.b, Lf, piv, sp, R, ldr, m, Y, ldy, sY);
+}
+
 // Across the four quarters of a wavefront (lanes l, l + 16, l + 32, l + 48 for
 // l < 16): the sum of v over the four, added in the same order in every lane,
 // and the value of the previous quarter (quarter 0 gets its own back).
@@ -727,7 +765,6 @@ __global__ __launch_bounds__(128) void k_band_bwd(const z64 *__restrict__ Uf,
   const int WC = sp.kl + sp.ku + 1, WU = sp.kl + sp.ku;
   const bool rev = blockIdx.z != 0;
   const int64_t n = sp.cols(rev);  // this side's rows
-  const int64_t v = 2 * static_cast<int64_t>(blockIdx.x) + blockIdx.z;
   // two chunks' staging (wave 1 fills one while wave 0 solves from the other)
   __shared__ z64 fac[2][kBandCH * WB];  // rows of U past the diagonal (WU each, zero-padded)
   __shared__ z64 rows[2][kBandCH][64];  // the forward results of those rows (all quarters)
@@ -736,8 +773,8 @@ __global__ __launch_bounds__(128) void k_band_bwd(const z64 *__restrict__ Uf,
   const int64_t col = static_cast<int64_t>(blockIdx.y) * 16 + (lane & 15);
   const bool act = col < m;
   const int64_t cc = act ? col : m - 1;
-  const z64 *U = Uf + v * sp.stride() * WC;
-  const z64 *Di = Dinv + v * sp.stride();
+  const z64 *U = Uf + sp.first(j, rev) * WC;
+  const z64 *Di = Dinv + sp.first(j, rev);
   z64 *Yj = Y + static_cast<int64_t>(j) * sY;
   if (rev) {  // rows in reverse order
     Yj += (sp.n - 1) * ldy;
@@ -860,14 +897,27 @@ namespace {
 // register window classes of the band kernels
 int band_class(int w) { return w <= 16 ? 16 : w <= 24 ? 24 : w <= 32 ? 32 : w <= 48 ? 48 : 64; }
 
-#define FEAST_BAND_DISPATCH(cls, KERNEL, ...)                                   \
-  switch (cls) {                                                               \
-    case 16: hipLaunchKernelGGL((KERNEL<16>), __VA_ARGS__); break;             \
-    case 24: hipLaunchKernelGGL((KERNEL<24>), __VA_ARGS__); break;             \
-    case 32: hipLaunchKernelGGL((KERNEL<32>), __VA_ARGS__); break;             \
-    case 48: hipLaunchKernelGGL((KERNEL<48>), __VA_ARGS__); break;             \
-    default: hipLaunchKernelGGL((KERNEL<64>), __VA_ARGS__); break;             \
+// launch(W): W an integral_constant
+template <typename F> void with_band_class(int w, F &&launch) {
+  switch (band_class(w)) {
+    case 16: return launch(std::integral_constant<int, 16>{});
+    case 24: return launch(std::integral_constant<int, 24>{});
+    case 32: return launch(std::integral_constant<int, 32>{});
+    case 48: return launch(std::integral_constant<int, 48>{});
+    default: return launch(std::integral_constant<int, 64>{});
   }
+}
+// launch(WA, WB): the windows of the two sides, one for both unless the split is steep
+// (kl = 1, ku = 60, n = 3000, 16 nodes: LU 5.45 ms and a filter's solves 1.40 with the
+// wide window for both sides and half of the rows each, 3.78 and 1.44 so; from the top
+// alone, with the narrow one, 4.12 and 2.01).
+template <typename F> void with_band_classes(const BandSplit &sp, F &&launch) {
+  using narrow = std::integral_constant<int, 16>;
+  using wide = std::integral_constant<int, 64>;
+  if (sp.two && BandSplit::steep(sp.kl, sp.ku))
+    return sp.kl < sp.ku ? launch(narrow{}, wide{}) : launch(wide{}, narrow{});
+  with_band_class((sp.two ? sp.lmax() : sp.kl) + 1, [&](auto w) { launch(w, w); });
+}
 }  // namespace
 
 // (kl + ku <= 63: kl + 1 <= 64 rows in the registers of a column owner, and at
@@ -876,8 +926,10 @@ void band_lu(hipStream_t s, const int32_t *rp, const int32_t *ci, const z64 *va,
              const z64 *z, int32_t N, const BandSplit &sp, z64 *Lf, z64 *Uf, z64 *Dinv,
              int32_t *piv, z64 *mid, z64 *midlu, int32_t *midperm, int32_t *info) {
   if (N <= 0 || sp.n <= 0) return;
-  FEAST_BAND_DISPATCH(band_class(sp.lmax() + 1), k_band_lu, dim3(N, sp.two ? 2 : 1), dim3(256), 0, s,
-                      rp, ci, va, vb, z, sp, Lf, Uf, Dinv, piv, mid, info)
+  with_band_classes(sp, [&](auto a, auto b) {
+    hipLaunchKernelGGL((k_band_lu<decltype(a)::value, decltype(b)::value>), dim3(N, sp.two ? 2 : 1),
+                       dim3(256), 0, s, rp, ci, va, vb, z, sp, Lf, Uf, Dinv, piv, mid, info);
+  });
   if (sp.two)
     hipLaunchKernelGGL(k_band_mid, dim3(N), dim3(256), 0, s, mid, sp.kl + sp.ku, sp.c, midlu, midperm,
                        info + 2 * N);
@@ -892,13 +944,17 @@ void band_solve(hipStream_t s, const z64 *Lf, const z64 *Uf, const z64 *Dinv, co
   const dim3 gf(N, static_cast<unsigned>((m + 31) / 32), sides);
   const dim3 gb(N, static_cast<unsigned>((m + 15) / 16), sides);
   // (a second wavefront per block stages the next chunk)
-  FEAST_BAND_DISPATCH(band_class(sp.lmax() + 1), k_band_fwd, gf, dim3(128), 0, s, Lf, piv, sp, R,
-                      ldr, m, Y, ldy, sY)
+  with_band_classes(sp, [&](auto a, auto b) {
+    hipLaunchKernelGGL((k_band_fwd<decltype(a)::value, decltype(b)::value>), gf, dim3(128), 0, s, Lf,
+                       piv, sp, R, ldr, m, Y, ldy, sY);
+  });
   if (sp.two && sp.kl + sp.ku > 0)
     hipLaunchKernelGGL(k_band_midsolve, dim3(N, static_cast<unsigned>((m + 31) / 32)), dim3(256), 0,
                        s, midlu, midperm, sp.kl + sp.ku, sp.c, m, Y, ldy, sY);
-  FEAST_BAND_DISPATCH(band_class(sp.kl + sp.ku), k_band_bwd, gb, dim3(128), 0, s, Uf, Dinv, sp, m, Y,
-                      ldy, sY)
+  with_band_class(sp.kl + sp.ku, [&](auto w) {
+    hipLaunchKernelGGL((k_band_bwd<decltype(w)::value>), gb, dim3(128), 0, s, Uf, Dinv, sp, m, Y, ldy,
+                       sY);
+  });
 }
 
 void csr_spmm(hipStream_t s, const int32_t *rp, const int32_t *ci, const z64 *va, const z64 *vb,

@@ -305,30 +305,42 @@ void identity(hipStream_t s, z64 *X, int64_t t);
 // (side 1, where kl and ku change places), and a dense system of the kl + ku
 // columns between them; or all from the top.  rows: the rows a side works on (those
 // it eliminates and the ones its window holds at the end); arrays of factors hold
-// side sd of node j at v = 2 j + sd, stride() rows apart.
+// side sd of node j from row first(j, sd) on (first_l: its multipliers).
 struct BandSplit {
   int64_t n, c;
   int kl, ku;
   bool two;
   // The two sides take half the time of one (a walk of n / 2 rows each); a
-  // matrix that is little more than its windows is left to the top side.
-  __host__ static BandSplit of(int64_t n, int kl, int ku) {
-    const bool two = n >= 4 * static_cast<int64_t>(kl + ku) + 64;
-    return BandSplit{n, two ? (n - kl - ku) / 2 : n, kl, ku, two};
+  // matrix that is little more than its windows is left to the top side.  Where one
+  // side's window is wider than 48 rows (steep: the other's is then at most 16, since
+  // kl + ku <= 63) a row costs it about twice as much, and it gets 0.35 of them.
+  __host__ static BandSplit of(int64_t n, int kl, int ku, bool both = true) {
+    const bool two = both && n >= 4 * static_cast<int64_t>(kl + ku) + 64;
+    const int64_t rows = n - kl - ku;
+    const int64_t c = !steep(kl, ku) ? rows / 2 : kl < ku ? rows * 13 / 20 : rows * 7 / 20;
+    return BandSplit{n, two ? c : n, kl, ku, two};
   }
+  __host__ static bool steep(int kl, int ku) { return (kl > ku ? kl : ku) >= 48; }
   __host__ __device__ int64_t cols(bool side) const { return side ? n - kl - ku - c : c; }
   __host__ __device__ int64_t rows(bool side) const {
     return two ? cols(side) + lower(side) : n;
   }
   __host__ __device__ int lower(bool side) const { return side ? ku : kl; }
   __host__ __device__ int lmax() const { return kl > ku ? kl : ku; }
-  __host__ __device__ int64_t stride() const { return two ? n - kl - ku - c : n; }
+  __host__ __device__ int64_t node_rows() const { return two ? n - kl - ku : n; }
+  __host__ __device__ int64_t node_l() const { return c * kl + (two ? cols(true) * ku : 0); }
+  __host__ __device__ int64_t first(int64_t j, bool side) const {
+    return j * node_rows() + (side ? c : 0);
+  }
+  __host__ __device__ int64_t first_l(int64_t j, bool side) const {
+    return j * node_l() + (side ? c * kl : 0);
+  }
 };
-// Band LU with partial pivoting of every node and side (one workgroup each): Lf
-// holds the multipliers of side v's column k at v stride lmax + k lower + i - 1
-// (rows k + i), Uf its row k of U at (v stride + k)(kl + ku + 1) + t (column
-// k + t), Dinv the reciprocal of U's diagonal entry k at v stride + k, piv the row
-// exchanged with k.  mid (64 x 64 per node): the system between the sides; midlu
+// Band LU with partial pivoting of every node and side v = 2 j + sd (one workgroup
+// each): Lf holds the multipliers of its column k at first_l + k lower + i - 1
+// (rows k + i), Uf its row k of U at (first + k)(kl + ku + 1) + t (column k + t),
+// Dinv the reciprocal of U's diagonal entry k at first + k, piv the row exchanged
+// with k.  mid (64 x 64 per node): the system between the sides; midlu
 // its inverted factors (two 64 x 64 blocks per node), midperm (64 per node) its
 // row order.  info[v], and info[2 N + j] for the systems between: the
 // first zero-pivot column + 1 (0: none).
