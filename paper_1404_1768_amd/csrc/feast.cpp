@@ -690,7 +690,7 @@ int filter_rhs(feast_plan *p, const z64 *A, int64_t lda, const z64 *B, int64_t l
     if (p->sp.on)
       feast::band_solve(p->s, p->sp.Lf.as<z64>(), p->sp.Uf.as<z64>(), p->sp.Dinv.as<z64>(),
                         p->sp.piv.as<int32_t>(), p->sp.midlu.as<z64>(), p->sp.midperm.as<int32_t>(),
-                        p->N, feast::BandSplit::of(p->n, p->sp.kl, p->sp.ku), R, ldr, cols,
+                        p->N, p->sp.split, R, ldr, cols,
                         p->Y.as<z64>(), p->ldY(), p->m);
     else
       solve_nodes_z(p, R, ldr, cols);
@@ -1633,7 +1633,8 @@ int feast_solve(feast_plan *p, const feast_z *dA, int64_t lda, const feast_z *dB
 // every node.
 constexpr int kBandMax = 63;  // kl + ku: LDS windows of the band kernels
 
-int prepare_sparse(feast_plan *p, const feast_csr *A, const feast_csr *B) {
+// (both: a node's columns may be eliminated from both ends)
+int prepare_sparse(feast_plan *p, const feast_csr *A, const feast_csr *B, bool both) {
   const int64_t n = p->n;
   hipStream_t s = p->s;
   feast_host::Pattern PA, PB;
@@ -1704,7 +1705,8 @@ int prepare_sparse(feast_plan *p, const feast_csr *A, const feast_csr *B) {
   }
   const int N = p->N;
   const int64_t WC = kl + ku + 1;
-  const feast::BandSplit bs = feast::BandSplit::of(n, sp.kl, sp.ku);
+  sp.split = feast::BandSplit::of(n, sp.kl, sp.ku, both);
+  const feast::BandSplit &bs = sp.split;
   const int64_t vrows = N * bs.node_rows();  // rows of both sides of all nodes
   sp.Lf.alloc(sizeof(z64) * std::max<int64_t>(N * bs.node_l(), 1));
   sp.Uf.alloc(sizeof(z64) * vrows * WC);
@@ -1750,10 +1752,10 @@ int feast_solve_csr(feast_plan *p, const feast_csr *A, const feast_csr *B, const
   if (p->mixed())
     return fail(p, FEAST_EINVAL, "feast_solve_csr: sparse pencils are factored in FP64 only");
   p->err.clear();
-  return guarded(p, [&]() -> int {
+  auto solve = [&](bool both) -> int {
     const int64_t n = p->n, m = p->m;
     Timer tf;
-    int st = prepare_sparse(p, A, B);
+    int st = prepare_sparse(p, A, B, both);
     const double t_fac = tf.ms();
     if (st != FEAST_OK) return st;
     struct Off {
@@ -1779,6 +1781,18 @@ int feast_solve_csr(feast_plan *p, const feast_csr *A, const feast_csr *B, const
     inf.band_kl = p->sp.kl;
     inf.band_ku = p->sp.ku;
     if (info) *info = inf;
+    return st;
+  };
+  return guarded(p, [&]() -> int {
+    int st = solve(true);
+    // Elimination from the top and from both ends are stable alike, but where the nodes'
+    // solutions grow past the type's range from one end to the other (kl much larger than
+    // ku and a pencil far from normal) rounding keeps the former's finite: what breaks
+    // down from both ends, or is singular, is what it is from the top.
+    if ((st == FEAST_ENUMERIC || st == FEAST_SINGULAR) && p->sp.split.two) {
+      p->err.clear();
+      st = solve(false);
+    }
     return st;
   });
 }

@@ -123,6 +123,7 @@ struct feast_plan {
     bool on = false;
     int kl = 0, ku = 0;
     int64_t nnz = 0;
+    feast::BandSplit split{};  // of the factors held
     DevBuf rp, ci, va, vb, map, perm;
     DevBuf Lf, Uf, Dinv, piv, info;
     DevBuf mid, midlu, midperm;  // the systems between the two sides of the nodes
