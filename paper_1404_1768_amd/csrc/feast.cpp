@@ -1707,11 +1707,22 @@ int prepare_sparse(feast_plan *p, const feast_csr *A, const feast_csr *B, bool b
   const int64_t WC = kl + ku + 1;
   sp.split = feast::BandSplit::of(n, sp.kl, sp.ku, both);
   const feast::BandSplit &bs = sp.split;
-  const int64_t vrows = N * bs.node_rows();  // rows of both sides of all nodes
-  sp.Lf.alloc(sizeof(z64) * std::max<int64_t>(N * bs.node_l(), 1));
-  sp.Uf.alloc(sizeof(z64) * vrows * WC);
-  sp.Dinv.alloc(sizeof(z64) * vrows);
-  sp.piv.alloc(sizeof(int32_t) * vrows);
+  auto alloc_factors = [&]() {
+    const int64_t rows = N * bs.node_rows();  // of both sides of all nodes
+    sp.Uf.alloc(sizeof(z64) * rows * WC);
+    sp.Dinv.alloc(sizeof(z64) * rows);
+    sp.piv.alloc(sizeof(int32_t) * rows);
+    sp.Lf.alloc(sizeof(z64) * std::max<int64_t>(N * bs.node_l(), 1));
+  };
+  try {
+    alloc_factors();
+  } catch (const HipError &e) {
+    // from the top alone the factors take less memory where kl < ku
+    if (e.e != hipErrorOutOfMemory || !bs.two || kl >= ku) throw;
+    (void)hipGetLastError();
+    sp.split = feast::BandSplit::of(n, sp.kl, sp.ku, false);
+    alloc_factors();
+  }
   sp.mid.alloc(sizeof(z64) * 4096 * N);
   sp.midlu.alloc(sizeof(z64) * 2 * 4096 * N);
   sp.midperm.alloc(sizeof(int32_t) * 64 * N);
