@@ -2,9 +2,7 @@
 
 For every order bucket and precision it factors a synthetic batch under each
 candidate configuration -- panel width 64 or 128, and the loop of the grouped
-trailing update (four real products per complex step; three products with
-operand pipelining; four products with operand pipelining) --
-and writes the fastest per bucket to ``csrc/batch_tune.h``, which
+trailing update (four or three real products per complex step) -- and writes the fastest per bucket to ``csrc/batch_tune.h``, which
 ``feast_batch_create`` consults (rebuild the library afterwards).
 
     python -m paper_1404_1768_amd.autotune [--out PATH] [--reps 3] [--summary PATH]
@@ -30,11 +28,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 BUCKETS = [(64, 384, 48), (384, 768, 32), (768, 1536, 24), (1536, 3072, 12), (3072, 16385, 4)]
 FP64, MIXED = 0, 1
 # candidates: (panel width, opts.batch_update): 1 = four products, 2 = three
-# products pipelined, 3 = four products pipelined
-CANDIDATES = {FP64: [(64, 1), (64, 2), (64, 3), (128, 1), (128, 2), (128, 3)],
-              MIXED: [(64, 1), (64, 2), (64, 3), (128, 1), (128, 2), (128, 3)]}
+CANDIDATES = [(64, 1), (64, 2), (128, 1), (128, 2)]
 # batch_update value -> the library's feast::GROUP_* code
-GROUP_CODE = {1: 0, 2: 1, 3: 2}
+GROUP_CODE = {1: 0, 2: 1}
 
 
 def _time_factor(fm, torch, ns, prec, nb, upd, As, Bs, Vs, reps):
@@ -74,7 +70,7 @@ def tune(reps: int = 3, seed: int = 1404):
         Vs = [torch.randn((n, 16), dtype=torch.complex128, device=dev, generator=gen) for n in ns]
         for prec in (FP64, MIXED):
             times = {}
-            for nb, upd in CANDIDATES[prec]:
+            for nb, upd in CANDIDATES:
                 t = _time_factor(fm, torch, ns, prec, nb, upd, As, Bs, Vs, reps)
                 times["nb%d_u%d" % (nb, upd)] = round(t, 3)
                 print("[autotune] orders %d..%d (%d pencils) %s nb=%d update=%d: %.2f ms" %
@@ -105,7 +101,7 @@ def write_header(results, path, device):
         "  int64_t lo, hi;  // bucket: lo <= n* < hi",
         "  int prec;        // FEAST_FP64 or FEAST_MIXED",
         "  int nb;          // panel width, 64 or 128",
-        "  int update;      // feast::GROUP_PLAIN, GROUP_UPDATE_M3 or GROUP_UPDATE_PIPE",
+        "  int update;      // feast::GROUP_PLAIN or GROUP_UPDATE_M3",
         "};",
         "",
         "inline constexpr Entry kBatch[] = {",

@@ -212,7 +212,7 @@ void choose_lu_config(feast_batch *b) {
       break;
     }
   if (b->o.nb != 0) nb = b->o.nb;
-  if (b->o.batch_update != 0) upd = b->o.batch_update - 1;
+  if (b->o.batch_update != 0) upd = b->o.batch_update == 2 ? feast::GROUP_UPDATE_M3 : feast::GROUP_PLAIN;
   b->lu_nb = nb;
   b->lu_update = upd;
 }

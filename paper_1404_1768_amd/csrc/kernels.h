@@ -77,10 +77,9 @@ void cupdate_persistent(hipStream_t s, int64_t M, int64_t N, int64_t K, const c6
 // kchunk) of a host table and returns the total tile count and the addressing; the launch reads
 // the table from device memory.  sub: every problem is C -= A B (alpha = -1,
 // beta = 1); ta: 0 or 2 (2 only with sub = false).
-//   variant (sub = true, ta = 0 only): GROUP_PLAIN and GROUP_UPDATE_PIPE, four real
-//   products per complex step (one kernel: its loop always reads operands ahead);
-//   GROUP_UPDATE_M3, three.
-enum { GROUP_PLAIN = 0, GROUP_UPDATE_M3 = 1, GROUP_UPDATE_PIPE = 2 };
+//   variant (sub = true, ta = 0 only): GROUP_PLAIN, four real products per complex
+//   step; GROUP_UPDATE_M3, three.
+enum { GROUP_PLAIN = 0, GROUP_UPDATE_M3 = 1 };
 struct GroupTiles {
   int64_t tiles;  // of all problems
   bool wide;      // some stride is past the reach of a 32-bit offset within a tile
