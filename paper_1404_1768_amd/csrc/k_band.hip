@@ -463,8 +463,11 @@ __global__ __launch_bounds__(256) void k_band_mid(const z64 *__restrict__ mid, i
     if (tid < 64) s_dinv[tid] = cplx_traits<z64>::recip(X[tid][tid]);
     __syncthreads();
     z64 *o = lu + (2ll * j + h) * 4096;
-    wave_inverse64(X, h == 0 ? static_cast<const z64 *>(nullptr) : s_dinv, lane, wave,
-                   [&](int r, int c, z64 v) { o[(r ^ rv) * 64 + (c ^ rv)] = v; });
+    for (int i = wave; i < 64; i += 4)
+      if (h == 0 ? lane > i : lane < i) o[i * 64 + lane] = zmake(0.0, 0.0);
+    auto put = [&](int r, int c, z64 v) { o[(r ^ rv) * 64 + (c ^ rv)] = v; };
+    if (h == 0) wave_inverse64<true>(X, s_dinv, 4, lane, wave, put);
+    else wave_inverse64<false>(X, s_dinv, 4, lane, wave, put);
     __syncthreads();
   }
   if (tid < 64) perm[j * 64 + tid] = s_p[tid];

@@ -575,7 +575,7 @@ __global__ __launch_bounds__(256) void k_panel_solve(T *__restrict__ Mall, int64
   for (int k = 0; k < PER; ++k) sL[wave + 4 * k][lane] = v[k];
   __syncthreads();
   if (16 * wave >= w2) return;
-  wave_subst<T, R / 16>(sL, static_cast<const T *>(nullptr), 0, (w1 + 15) / 16, x, lane,
+  wave_subst<T, R / 16, true>(sL, static_cast<const T *>(nullptr), 0, (w1 + 15) / 16, x, lane,
                         [&](int kb, const T(&y)[PER]) {
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
@@ -742,11 +742,12 @@ __global__ __launch_bounds__(256) void k_lu_small(const GrpMat *__restrict__ grp
 
 // Inverse of one 64 x 64 diagonal block of each matrix (lower unit or upper
 // non-unit), zero padded at out + b out_stride + I 64^2.  An upper block is
-// inverted as the lower one it is with rows and columns in reverse order; rows
-// past the matrix count as the identity.
-// 64-row blocks of 16 complex128 matrices: 42 us a launch by a substitution with a
-// barrier per row, 13 us so (12 us as an inverse put together from halves, whose
-// products left twice the residual).
+// inverted as the lower one it is with rows and columns in reverse order; a last
+// block is worked in the 16-row pieces that it has, filled up with the identity.
+// us a launch, complex128, by a substitution with a barrier per row, as an inverse put
+// together from halves (whose products left twice the residual), and so: one 64-row
+// block of 16 matrices 42, 12, 13; both triangles of 1024 matrices of order 64 71 (halves),
+// 79 so; of 4096 matrices of order 8 218, 108.
 template <typename T>
 __global__ __launch_bounds__(256) void k_diag_inv(const T *__restrict__ Mall, int64_t ld_in,
                                                   int64_t stride, int64_t n_in, int64_t blk0,
@@ -765,7 +766,8 @@ __global__ __launch_bounds__(256) void k_diag_inv(const T *__restrict__ Mall, in
   const T *D = mr.M + r0 * (ld + 1);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int rev = lower ? 0 : 63;  // index i of S is index i ^ rev of the block
+  T *o = out + b * out_stride + I * 4096;
+  const int nb = rb > 0 ? (rb + 15) / 16 : 0, last = 16 * nb - 1;  // 16-row blocks of the matrix
   T v[16];
 #pragma unroll
   for (int k = 0; k < 16; ++k) {
@@ -774,16 +776,32 @@ __global__ __launch_bounds__(256) void k_diag_inv(const T *__restrict__ Mall, in
     v[k] = in ? D[i * ld + lane] : cplx_traits<T>::make(i == lane ? 1.0 : 0.0, 0.0);
   }
 #pragma unroll
-  for (int k = 0; k < 16; ++k) S[(wave + 4 * k) ^ rev][lane ^ rev] = v[k];
+  for (int k = 0; k < 16; ++k) {
+    const int i = wave + 4 * k;
+    if (lower) S[i][lane] = v[k];
+    else if (i <= last && lane <= last) S[last - i][last - lane] = v[k];
+  }
   __syncthreads();
   if (!lower) {
-    if (tid < 64) s_inv[tid] = cplx_traits<T>::recip(S[tid][tid]);
+    if (tid <= last) s_inv[tid] = cplx_traits<T>::recip(S[tid][tid]);
     __syncthreads();
   }
-  T *o = out + b * out_stride + I * 4096;
-  wave_inverse64(S, lower ? static_cast<const T *>(nullptr) : s_inv, lane, wave, [&](int i, int j, T x) {
-    o[(i ^ rev) * 64 + (j ^ rev)] = (i ^ rev) < rb && (j ^ rev) < rb ? x : czero<T>();
-  });
+  // what the columns do not reach: the other triangle, and past the matrix
+  for (int i = wave; i < 64; i += 4)
+    if (i >= rb || lane >= rb || (lower ? lane > i : lane < i)) o[i * 64 + lane] = czero<T>();
+  // (column block w costs nb - w steps: every other workgroup gives them to its
+  // wavefronts in reverse order, so that a SIMD with one of each has its share)
+  const int w = ((blockIdx.y ^ (blockIdx.y >> 8)) & 1) ? nb - 1 - wave : wave;
+  if (w >= 0 && w < nb) {
+    if (lower)
+      wave_inverse64<true>(S, s_inv, nb, lane, w, [&](int i, int j, T x) {
+        if (i < rb) o[i * 64 + j] = x;
+      });
+    else
+      wave_inverse64<false>(S, s_inv, nb, lane, w, [&](int i, int j, T x) {
+        if (last - j < rb) o[(last - i) * 64 + last - j] = x;
+      });
+  }
 }
 
 // Inverse of a 128-row diagonal block of a triangular factor from the inverses

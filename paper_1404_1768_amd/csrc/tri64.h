@@ -108,7 +108,7 @@ template <typename T> __device__ inline void all_groups(T v, T (&o)[4]) {
 // the lower triangular matrix S, its rows of 16-row blocks k0 .. k1 - 1 (rows and
 // columns before block k0 belong to entries of x that are zero).  Lane 16 g + c holds
 // rows 4 q + g of column c from block k0 on: x[q] (q < 4 NB), zero past block k1.
-// inv: reciprocals of the diagonal, or null where it counts as ones.  done(kb, x) gets
+// inv: reciprocals of the diagonal, where it does not count as ones (UNIT).  done(kb, x) gets
 // block kb's four rows 16 kb + 4 p + g, p < 4.
 // Four rows at a time: the four groups' entries go to all of them by swaps (no
 // barrier), every group finishes the four rows for itself and takes them off its
@@ -117,7 +117,7 @@ template <typename T> __device__ inline void all_groups(T v, T (&o)[4]) {
 // with: the product with an inverse that was built by halves had 1.6 times the error,
 // and over- or underflowed for columns of very different size.
 //   bound: the chain of 16 four-row steps a wavefront.
-template <typename T, int NB, typename Done>
+template <typename T, int NB, bool UNIT, typename Done>
 __device__ __forceinline__ void wave_subst(const T (*S)[kTP], const T *inv, int k0, int k1,
                                            T (&x)[4 * NB], int lane, Done &&done) {
   const int c = lane & 15, g = lane >> 4;
@@ -126,39 +126,40 @@ __device__ __forceinline__ void wave_subst(const T (*S)[kTP], const T *inv, int 
   for (int kb = k0; kb < k1; ++kb) {
     const int o = 16 * kb;
     const T(*D)[kTP] = S + o;
-    // L's entries for the rows 4 q ..: the four rows' own (the same in all lanes), and
-    // those of the later rows of the block, both read one step ahead
-    T own[2][6], low[2][3][4];
+    // L's entries within the four rows 4 q .. (the same in all lanes), read one step ahead
+    T own[2][6], dia[2][4];
     auto fetch = [&](int q, int b) {
 #pragma unroll
-      for (int r = 1, e = 0; r < 4; ++r)
+      for (int r = 0, e = 0; r < 4; ++r) {
 #pragma unroll
         for (int k = 0; k < r; ++k, ++e) own[b][e] = D[4 * q + r][o + 4 * q + k];
-#pragma unroll
-      for (int p = q + 1; p < 4; ++p)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) low[b][p - 1][k] = D[4 * p + g][o + 4 * q + k];
+        if constexpr (!UNIT) dia[b][r] = inv[o + 4 * q + r];
+      }
     };
     fetch(0, 0);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      if (q < 3) fetch(q + 1, (q + 1) & 1);
-      __builtin_amdgcn_sched_barrier(0);
+      T v[4], low[3][4];  // (low: those of the later rows of the block)
+#pragma unroll
+      for (int p = q + 1; p < 4; ++p)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) low[p - 1][k] = D[4 * p + g][o + 4 * q + k];
       const int b = q & 1;
-      T v[4];
+      if (q < 3) fetch(q + 1, b ^ 1);
+      __builtin_amdgcn_sched_barrier(0);
       all_groups(x[q], v);
 #pragma unroll
       for (int r = 0, e = 0; r < 4; ++r) {
 #pragma unroll
         for (int k = 0; k < r; ++k, ++e) v[r] = ffms(v[r], own[b][e], v[k]);
-        if (inv) v[r] = fmul(v[r], inv[o + 4 * q + r]);
+        if constexpr (!UNIT) v[r] = fmul(v[r], dia[b][r]);
       }
       x[q].x = g < 2 ? (g == 0 ? v[0].x : v[1].x) : (g == 2 ? v[2].x : v[3].x);
       x[q].y = g < 2 ? (g == 0 ? v[0].y : v[1].y) : (g == 2 ? v[2].y : v[3].y);
 #pragma unroll
       for (int p = q + 1; p < 4; ++p)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) x[p] = ffms(x[p], low[b][p - 1][k], v[k]);
+        for (int k = 0; k < 4; ++k) x[p] = ffms(x[p], low[p - 1][k], v[k]);
     }
     done(kb, x);
 #pragma unroll
@@ -178,22 +179,22 @@ __device__ __forceinline__ void wave_subst(const T (*S)[kTP], const T *inv, int 
   }
 }
 
-// Columns 16 w .. 16 w + 15 of the inverse of the lower triangular 64 x 64 matrix S, by
-// wavefront w = wave (inv as in wave_subst): put(i, j, v) gets every entry of them.
-template <typename T, typename Put>
-__device__ __forceinline__ void wave_inverse64(const T (*S)[kTP], const T *inv, int lane, int wave,
-                                               Put &&put) {
+// Columns 16 w .. 16 w + 15 of the inverse of the lower triangular matrix S of nb blocks
+// of 16 rows, by one wavefront (inv as in wave_subst): put(i, j, v) gets every entry of
+// them that is not zero by position.
+template <bool UNIT, typename T, typename Put>
+__device__ __forceinline__ void wave_inverse64(const T (*S)[kTP], const T *inv, int nb, int lane,
+                                               int w, Put &&put) {
   using Tr = cplx_traits<T>;
-  const int c = lane & 15, g = lane >> 4, j = 16 * wave + c;
-  for (int i = g; i < 16 * wave; i += 4) put(i, j, Tr::make(0.0, 0.0));
+  const int c = lane & 15, g = lane >> 4, j = 16 * w + c;
   T x[16];
 #pragma unroll
   for (int q = 0; q < 16; ++q) x[q] = Tr::make(q < 4 && 4 * q + g == c ? 1.0 : 0.0, 0.0);
-  wave_subst<T, 4>(S, inv, wave, 4, x, lane, [&](int kb, const T(&v)[16]) {
+  wave_subst<T, 4, UNIT>(S, inv, w, nb, x, lane, [&](int kb, const T(&v)[16]) {
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
       const int i = 16 * kb + 4 * p + g;
-      put(i, j, i < j ? Tr::make(0.0, 0.0) : v[p]);
+      if (i >= j) put(i, j, v[p]);
     }
   });
 }
