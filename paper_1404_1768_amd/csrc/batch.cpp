@@ -747,8 +747,10 @@ std::vector<GrpMat> gmats(feast_batch *b, const std::vector<int> &act, z64 *(*bl
 z64 *gblk_of(feast_plan *q, int i) { return q->gblk(i); }
 z64 *wblk_of(feast_plan *q, int i) { return q->wblk(i); }
 
-// X_p <- orth(X_p) (n_p x m_p, leading dimension m_p) by shifted Cholesky QR3,
-// as the single-pencil plan does it; flags of list entry i at flags[8 i + slot + pass].
+// X_p <- orth(X_p) (n_p x m_p, leading dimension m_p) by shifted Cholesky QR in three
+// passes (the single-pencil plan's, which stops after two where it may: that takes a look
+// at the second Gram matrix by the host, which these recorded launches cannot wait for);
+// flags of list entry i at flags[8 i + slot + pass].
 void orth_grouped(feast_batch *b, Tables &t, const std::vector<int> &act, int xblk, int slot) {
   const bool rec = t.record;
   hipStream_t s = b->gs;

@@ -62,8 +62,8 @@ void k_gemm_solve(const GemmArgs<T> d, int64_t grid_total) {
 }
 
 // The LU trailing update C -= A B on a fixed number of persistent workgroups, each
-// filling one compute unit on its own: four tile groups of 256 threads and, with
-// `lds` bytes of dynamic LDS that nothing reads, about 100 KB of LDS, so that no
+// filling one compute unit on its own: four tile groups of 256 threads and about 100 KB
+// of LDS (in complex64 48 KB of it dynamic LDS that nothing reads), so that no
 // second workgroup of any kernel fits beside it.  The compute units left over
 // stay free for the next panel's factorisation on another stream.
 // Workgroup w runs on XCD w mod 8; XCD x works through the tile range

@@ -168,11 +168,11 @@ template <typename T> __device__ inline T recip_scaled(T a) {
 // posts are double-buffered by column parity, so one barrier per column
 // suffices.  Loads and stores walk along rows and turn through LDS of the
 // wavefront's own, without barriers.
-// Measured (us a leaf of 8 columns, all matrices at once, before -> now):
-// complex128 200 rows 18.3 -> 13.5, 1000 rows 24.7 -> 18.1, 2000 rows 30.7 -> 24.7;
-// complex64 1000 rows 16.7 -> 14.0, 2000 rows 22.6 -> 17.2, 4000 rows 33.0 -> 24.9.
-// A leaf costs 4.6 to 15 us (200 complex128 to 4000 complex64 rows) plus 0.9 to
-// 1.7 us a column.
+// Measured (us a leaf of 8 columns with the solve of its rows, 16 matrices): complex128
+// 200 rows 18.2, 1000 rows 23.2, 2000 rows 32.8; complex64 up to 1024 rows 15.2, up to
+// 2048 20.6, 32 matrices of up to 4000 rows 29.1.  (With a reduction for the pivot's
+// value and one for its row, and without the solve, the leaf took 18.3, 24.7, 30.7 and
+// 16.7, 22.6, 33.0.)
 template <typename T, int NT, int RPT, int IB>
 __global__ __launch_bounds__(NT) void k_leaf(T *__restrict__ Mall, int64_t ld_in, int64_t stride,
                                              int64_t n_in, int64_t c0, int w, int64_t pk0,
@@ -460,7 +460,7 @@ __global__ __launch_bounds__(NT) void k_leaf(T *__restrict__ Mall, int64_t ld_in
 // source is found by walking them backwards (all destinations at once, in LDS).
 // A workgroup moves 512-byte pieces of those rows, every piece read before any is
 // written.  One exchange after the other, each column waited for 128 memory round
-// trips: 58 us a 128-column panel of 16 complex128 matrices of order 1000, 22 us
+// trips: 58 us a 128-column panel of 16 complex128 matrices of order 1000, 26 us
 // so (124 us for 32 complex64 ones of order 4000, 95 to 107 so, 5 TB/s).
 template <typename T>
 __global__ __launch_bounds__(256) void k_laswp_outside(T *__restrict__ Mall, int64_t ld_in,
@@ -811,8 +811,8 @@ __global__ __launch_bounds__(256) void k_diag_inv(const T *__restrict__ Mall, in
 //   upper:         [U11 C; 0 U22]^{-1} = [I1  -(I1 C) I2; 0 I2]
 // One workgroup per (block, matrix, triangle); the two 64 x 64 x 64 products run on the
 // matrix cores from LDS, one 16-row strip of the output per wavefront.  (16
-// complex128 matrices of order 200: 94 us a launch with each thread summing its
-// entries from LDS, 35 us so.)
+// complex128 matrices of order 200: 94 us a triangle with each thread summing its
+// entries from LDS, 38 us for both so.)
 template <typename T>
 __global__ __launch_bounds__(256) void k_inv_pair(const T *__restrict__ F, int64_t ld,
                                                   int64_t fstride, int64_t n,
@@ -956,10 +956,11 @@ bool leaf_lu<z64>(hipStream_t s, z64 *M, int64_t ld, int64_t stride, int32_t bat
                   const GrpMat *grp, int nodes) {
   const int64_t rows = n - c0;
   if (w < 1 || w > leaf_max_width<z64>(rows) || pkb > 128) return false;
-  // (as few threads as give one row each up to 512 rows: 200 rows 13.5 us a leaf
-  // against 14.7 with 512 threads; 512 threads up to 2048 rows: 1000 rows 18.1 us
-  // against 19.8 with 256 and 20.4 with 1024 threads, 2000 rows 24.6 against 25.6
-  // with 1024)
+  // 256 threads up to 256 rows, where there may be many matrices (factorisations of 4096
+  // of order 8: 224 us, 254 with 512 threads; of 400 of order 200 1335 and 1350; of 16 of
+  // order 200 715 and 670); else 512: a leaf of 16 matrices of 1000 rows takes 23.2 us,
+  // 26.2 with 256 threads and 24.5 with 1024; of 2000 rows 32.8, 31.2 with 1024, the
+  // factorisation the same.
   if (rows <= 256)
     launch_leaf<z64, 1, 8, 256>(s, M, ld, stride, batch, n, c0, w, pk0, pkb, ue, ipiv, info, grp, nodes);
   else if (rows <= 512)
@@ -1060,7 +1061,6 @@ void panel_update(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch
   panel_solve<T>(s, M, ld, stride, batch, n, c0, w1, w2, grp, nodes);
   panel_rank<T>(s, M, ld, stride, batch, n, c0, w1, w2, grp, nodes);
 }
-int panel_update_max_width() { return kPU; }
 
 // Columns [c0, c0 + w), w <= 64, of each matrix: leaves of eight columns, each
 // of which solves its own rows over the rest of a block of `bw` columns and is

@@ -316,7 +316,7 @@ __global__ __launch_bounds__(256) void k_add_shift(z64 *__restrict__ G, int64_t 
 // inverses of the diagonal blocks then join to L^{-1} (tri64.h).  Bound by the
 // chain of 64 pivots (about 0.25 us each) and the barriers; a barrier per pivot
 // and per substitution row on 1024 threads took 60 us a 64-row block and 35 us a
-// 30-row one, this takes 36 and 19.
+// 30-row one, this takes 30 and 19.
 // flag[0] = 1 + col0 + k for the first non-positive pivot k (a unit pivot is
 // used in its place so the kernel finishes).
 

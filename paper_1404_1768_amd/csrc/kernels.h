@@ -128,7 +128,7 @@ void laswp_outside(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batc
                    int64_t r0, int kb, int64_t clo, int64_t chi, const int32_t *ipiv,
                    const GrpMat *grp = nullptr, int nodes = 1);
 
-// Joins of the panel (w1, w2 <= panel_update_max_width()):
+// Joins of the panel (panel_update: w1, w2 <= 32):
 //   X = L11^{-1} X for the unit-lower L11 = M[c0:c0+w1, c0:c0+w1] and
 //   X = M[c0:c0+w1, c0+w1:c0+w1+w2] (one workgroup per matrix), then
 //   M[c0+w1:n, c0+w1:c0+w1+w2] -= M[c0+w1:n, c0:c0+w1] X (64-row chunks).
@@ -142,7 +142,6 @@ void panel_update(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch
 template <typename T>
 void panel_rank(hipStream_t s, T *M, int64_t ld, int64_t stride, int32_t batch, int64_t n,
                 int64_t c0, int w1, int w2, const GrpMat *grp = nullptr, int nodes = 1);
-int panel_update_max_width();
 
 // Inverses of the diagonal blocks of the unit-lower L (lower=true) or of the
 // upper U (lower=false) factor: block I covers rows/cols [64 I, min(n, 64 (I+1))).
