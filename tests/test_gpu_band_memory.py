@@ -48,7 +48,7 @@ def test_less_memory_from_the_top():
     multipliers = 16 * nodes * 63 * (n - 63) * 7 // 20  # the bottom side's
     with fm.Plan(n, m, 0.0, 1.0, nodes, max_iter=10) as plan:
         hog, quiet = [], 0
-        while quiet < 3:  # (the driver takes back freed memory a little later)
+        while quiet < 3:  # (HIP takes back freed memory a little later)
             more = free() - (need - multipliers // 2)
             if more > (16 << 20):
                 hog.append(torch.empty(more, dtype=torch.uint8, device=DEV))

@@ -25,7 +25,7 @@ def free():
 
 
 def leave(nbytes):
-    """Tensors that leave about nbytes of device memory free (the driver takes back freed
+    """Tensors that leave about nbytes of device memory free (HIP takes back freed
     memory a little later: until that is seen no more)."""
     hog, quiet = [], 0
     while quiet < 3:

@@ -19,7 +19,7 @@ def free():
 
 
 def comes_back(want):
-    """Free memory reaches `want` (the driver takes back freed memory a little later)."""
+    """Free memory reaches `want` (HIP takes back freed memory a little later)."""
     for _ in range(50):
         if free() >= want - (32 << 20):
             return True
